@@ -1,5 +1,6 @@
 // Device helpers shared by the complex64 and complex-half kernels.
 #pragma once
+#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -37,6 +38,8 @@ __device__ __forceinline__ cptr<T> cmem(uint64_t a) {
 
 // unsigned atomic max on a workspace word (float bits of non-negative values)
 __device__ __forceinline__ void gmax_u32(uint64_t a, uint32_t v) { atomicMax((uint32_t*)a, v); }
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));  // MFMA accumulator
 
 // element accessors (HIP's float2 / __half2 classes cannot be copied
 // through an address-space-qualified reference; plain vectors can)
@@ -76,9 +79,9 @@ __device__ __forceinline__ void max_scale_mx(uint64_t base, int64_t i, uint32_t 
 // pass) maps to a logical tile so that XCD x works through the contiguous
 // logical range [start(x), start(x) + count(x)): neighbouring tiles, which
 // share operand data, then meet in the same L2.  A bijection on [0, total).
-__device__ __forceinline__ int64_t xcd_tile(int64_t vid, int64_t total) {
-  const int64_t q = total >> 3, r = total & 7;
-  const int64_t x = vid & 7, k = vid >> 3;
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t vid, uint32_t total) {
+  const uint32_t q = total >> 3, r = total & 7;
+  const uint32_t x = vid & 7, k = vid >> 3;
   return x * q + (x < r ? x : r) + k;
 }
 
@@ -93,14 +96,22 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t vid, int64_t total) {
 // instance far larger than the caches takes R = its size, so that the
 // instance streams from HBM once while the group's B instances are re-read
 // from the caches.  A bijection on [0, units * tiles) for any R >= 1 (a
-// short last block keeps the same order over its units).
-__device__ __forceinline__ void unit_tile(int64_t lt, int64_t units, int64_t tiles, int64_t R, int64_t& u,
-                                          int64_t& t) {
-  const int64_t blk = lt / (R * tiles);
-  const int64_t r = lt - blk * R * tiles;
-  const int64_t rows = units - blk * R < R ? units - blk * R : R;  // units in this block
-  u = blk * R + r % rows;
+// short last block keeps the same order over its units).  All counts fit in
+// 32 bits (a tile writes at least 64 elements of 4 bytes, so 2^31 of them
+// would not fit the card's memory) and tiles = 2^tbits: 64-bit divisions here
+// cost a few hundred cycles per tile, as much as two k steps.
+__device__ __forceinline__ void unit_tile(uint32_t lt, uint32_t units, int tbits, uint32_t R, uint32_t& u,
+                                          uint32_t& t) {
+  if (R == 1) {
+    u = lt >> tbits;
+    t = lt & ((1u << tbits) - 1u);
+    return;
+  }
+  const uint32_t blk = (lt >> tbits) / R;
+  const uint32_t r = lt - ((blk * R) << tbits);
+  const uint32_t rows = units - blk * R < R ? units - blk * R : R;  // units in this block
   t = r / rows;
+  u = blk * R + (r - t * rows);
 }
 
 template <typename P>
@@ -129,6 +140,29 @@ __device__ __forceinline__ void cmac(float2& c, float2 a, float2 b) {
   c.y = fmaf(a.y, b.x, c.y);
 }
 
+
+// An operand's staged element: an FP32 pair, or (complex-half plans, whose
+// FP32 steps may read an FP16-stored child) a half2 word converted exactly to
+// FP32 and multiplied by the instance's power of two 2^e.
+template <bool H>
+struct FStage;
+template <>
+struct FStage<false> {
+  typedef f32x2 type;
+  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return gmem<const f32x2>(base)[i]; }
+  static __device__ __forceinline__ float2 val(type r, float) { return make_float2(r.x, r.y); }
+};
+template <>
+struct FStage<true> {
+  typedef uint32_t type;
+  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return ldg_u32(base, i); }
+  static __device__ __forceinline__ float2 val(type r, float c) {
+    __half2 h;
+    __builtin_memcpy(&h, &r, 4);
+    const float2 v = __half22float2(h);
+    return make_float2(v.x * c, v.y * c);
+  }
+};
 
 // grid size for grid-stride loops
 static inline unsigned grid_for(int64_t blocks) {

@@ -11,6 +11,8 @@ namespace matnc {
 hipError_t launch_stream(const NodeDesc& d, uint64_t ws, const int64_t* sig, hipStream_t st);
 int mfma_config_count();
 int mfma_config_tn(int cfg);  // complex N columns of a tile configuration
+int mfma_config_tm_bits(int cfg);
+int mfma_config_tn_bits(int cfg);
 bool mfma_config_fits(int cfg, int mbits, int nbits, int kbits);
 hipError_t launch_mfma(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
 // fan-out tiles (d.fan_off / d.n_fan describe the grouping)
@@ -19,6 +21,11 @@ hipError_t launch_mfma_fan(const NodeDesc& d, int cfg, uint64_t ws, const int64_
 // the same, also recording each output instance's maximum (its scale slot
 // must have been cleared)
 hipError_t launch_mfma_fan_rec(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
+// the same steps with FP32 operands split into bfloat16 parts (same tile
+// configurations)
+hipError_t launch_split(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
+hipError_t launch_split_fan(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
+hipError_t launch_split_fan_rec(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
 // adds the root instances of slices sigma0 .. sigma0+nb-1 into rows[0..nrows)
 // of amps (root.gmap_off: local root instance of each row position)
 hipError_t launch_slice_sum(const OpDesc& root, uint64_t ws, const int64_t* sig, int nb, int64_t nrows,

@@ -29,31 +29,6 @@ namespace matnc {
 // ---------------------------------------------------------------------------
 // MFMA complex GEMM
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-// An operand's staged element: an FP32 pair, or (complex-half plans, whose
-// FP32 steps may read an FP16-stored child) a half2 word converted exactly to
-// FP32 and multiplied by the instance's power of two 2^e.
-template <bool H>
-struct FStage;
-template <>
-struct FStage<false> {
-  typedef f32x2 type;
-  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return gmem<const f32x2>(base)[i]; }
-  static __device__ __forceinline__ float2 val(type r, float) { return make_float2(r.x, r.y); }
-};
-template <>
-struct FStage<true> {
-  typedef uint32_t type;
-  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return ldg_u32(base, i); }
-  static __device__ __forceinline__ float2 val(type r, float c) {
-    __half2 h;
-    __builtin_memcpy(&h, &r, 4);
-    const float2 v = __half22float2(h);
-    return make_float2(v.x * c, v.y * c);
-  }
-};
-
 // Tile: TM = 32*RM*WM values of m, TN = 16*RN*WN complex n, TK complex k.
 // FAN: the tile's TN columns are TN >> nbits slots of 2^nbits columns, one
 // per output instance of a fan-table row (see NodeDesc); the A tile is
@@ -99,35 +74,35 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma(NodeDesc d, uint64_t ws, 
   const int wm = wave % WM;
   const int wn = wave / WM;
 
-  const int64_t mt_count = (int64_t)1 << (d.mbits - __builtin_ctz(TM));
-  const int64_t nt_count = FAN ? 1 : (int64_t)1 << (d.nbits - __builtin_ctz(TN));
-  const int64_t tiles = mt_count * nt_count;
+  const int nt_bits = FAN ? 0 : d.nbits - __builtin_ctz(TN);
+  const int tbits = d.mbits - __builtin_ctz(TM) + nt_bits;  // tiles per unit = 2^tbits
   const int ksteps = 1 << (d.kbits - __builtin_ctz(TK));
   const int64_t sigma0 = sig[0];
   // work units: output instances, or (slice, fan row) pairs
-  const int64_t units = FAN ? (d.n_inst / d.w) * d.n_fan : d.n_inst;
+  const uint32_t units = (uint32_t)(FAN ? ((uint32_t)d.n_inst / (uint32_t)d.w) * (uint32_t)d.n_fan : d.n_inst);
+  const uint32_t total = units << tbits;
   const gptr<const int32_t> fan = gmem<const int32_t>(ws + d.fan_off);
   const uint32_t nmask = (1u << d.nbits) - 1u;
   const int slots = FAN ? (TN >> d.nbits) : 1;
 
-  for (int64_t blk = blockIdx.x; blk < units * tiles; blk += gridDim.x) {
+  for (uint32_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
     // logical tile order: n tiles innermost (they share the A tile), then m
     // tiles, then instances / fan rows (fan rows in blocks, see unit_tile);
     // each XCD takes a contiguous range
-    const int64_t lt = xcd_tile(blk, units * tiles);
-    int64_t u, t;
-    unit_tile(lt, units, tiles, d.fan_rows > 0 ? (int64_t)d.fan_rows : (FAN ? 2 : 1), u, t);
-    const uint32_t m0 = (uint32_t)((t / nt_count) * TM);
-    const uint32_t n0 = (uint32_t)((t % nt_count) * TN);
+    const uint32_t lt = xcd_tile(blk, total);
+    uint32_t u, t;
+    unit_tile(lt, units, tbits, d.fan_rows > 0 ? (uint32_t)d.fan_rows : (FAN ? 2u : 1u), u, t);
+    const uint32_t m0 = (t >> nt_bits) * TM;
+    const uint32_t n0 = (t & ((1u << nt_bits) - 1u)) * TN;
     int64_t s, j;
     gptr<const int32_t> fj = nullptr;
     if (FAN) {
-      s = d.dep ? u / d.n_fan : 0;
-      fj = fan + (u - s * d.n_fan) * slots;
+      s = d.dep ? u / (uint32_t)d.n_fan : 0u;
+      fj = fan + (uint64_t)(u - (uint32_t)s * (uint32_t)d.n_fan) * slots;
       j = fj[0];
     } else {
-      s = d.dep ? u / d.w : 0;
-      j = d.dep ? u - s * d.w : u;
+      s = d.dep ? u / (uint32_t)d.w : 0u;
+      j = (int64_t)u - s * d.w;
     }
     const int64_t inst = s * d.w + j;  // output instance (slot 0 for fan tiles)
     const int64_t sigma = sigma0 + s;
@@ -373,6 +348,9 @@ bool mfma_config_fits(int cfg, int mbits, int nbits, int kbits) {
 }
 
 int mfma_config_tn(int cfg) { return cfg < 0 || cfg >= mfma_config_count() ? 0 : 1 << kMfmaCfgs[cfg].tn_bits; }
+
+int mfma_config_tm_bits(int cfg) { return kMfmaCfgs[cfg].tm_bits; }
+int mfma_config_tn_bits(int cfg) { return kMfmaCfgs[cfg].tn_bits; }
 
 bool mfma_fan_config_fits(int cfg, int mbits, int nbits, int kbits, int fan_tn) {
   if (cfg < 0 || cfg >= mfma_config_count()) return false;

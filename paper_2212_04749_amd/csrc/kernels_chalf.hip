@@ -28,7 +28,6 @@ namespace matnc {
 
 bool chalf_available() { return true; }
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint32_t h2bits(__half2 h) {
@@ -114,40 +113,40 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
   const int wave = tid >> 6;
   const int wm = wave % WM;
   const int wn = wave / WM;
-  const int64_t mt_count = (int64_t)1 << (d.mbits - __builtin_ctz(TM));
-  const int64_t nt_count = FAN ? 1 : (int64_t)1 << (d.nbits - __builtin_ctz(TN));
-  const int64_t tiles = mt_count * nt_count;
+  const int nt_bits = FAN ? 0 : d.nbits - __builtin_ctz(TN);
+  const int tbits = d.mbits - __builtin_ctz(TM) + nt_bits;  // tiles per unit = 2^tbits
   const int ksteps = 1 << (d.kbits - __builtin_ctz(TK));
   const int64_t sigma0 = sig[0];
   const int half = lane >> 5;
   const int l32 = lane & 31;
   const int dsel = l32 & 1;
   const int ncol = l32 >> 1;
-  const int64_t units = FAN ? (d.n_inst / d.w) * d.n_fan : d.n_inst;
+  const uint32_t units = (uint32_t)(FAN ? ((uint32_t)d.n_inst / (uint32_t)d.w) * (uint32_t)d.n_fan : d.n_inst);
+  const uint32_t total = units << tbits;
   const gptr<const int32_t> fan = gmem<const int32_t>(ws + d.fan_off);
   const uint32_t nmask = (1u << d.nbits) - 1u;
   const int slots = FAN ? (TN >> d.nbits) : 1;
   const uint64_t scB = ws + d.B.scale_off;
   const bool bstage = !BPART || tid < QB;
 
-  for (int64_t blk = blockIdx.x; blk < units * tiles; blk += gridDim.x) {
+  for (uint32_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
     // logical tile order: n tiles innermost (they share the A tile), then m
     // tiles, then instances / fan rows (fan rows in blocks, see unit_tile);
     // each XCD takes a contiguous range
-    const int64_t lt = xcd_tile(blk, units * tiles);
-    int64_t u, t;
-    unit_tile(lt, units, tiles, d.fan_rows > 0 ? (int64_t)d.fan_rows : (FAN ? 2 : 1), u, t);
-    const uint32_t m0 = (uint32_t)((t / nt_count) * TM);
-    const uint32_t n0 = (uint32_t)((t % nt_count) * TN);
+    const uint32_t lt = xcd_tile(blk, total);
+    uint32_t u, t;
+    unit_tile(lt, units, tbits, d.fan_rows > 0 ? (uint32_t)d.fan_rows : (FAN ? 2u : 1u), u, t);
+    const uint32_t m0 = (t >> nt_bits) * TM;
+    const uint32_t n0 = (t & ((1u << nt_bits) - 1u)) * TN;
     int64_t s, j;
     gptr<const int32_t> fj = nullptr;
     if (FAN) {
-      s = d.dep ? u / d.n_fan : 0;
-      fj = fan + (u - s * d.n_fan) * slots;
+      s = d.dep ? u / (uint32_t)d.n_fan : 0u;
+      fj = fan + (uint64_t)(u - (uint32_t)s * (uint32_t)d.n_fan) * slots;
       j = fj[0];
     } else {
-      s = d.dep ? u / d.w : 0;
-      j = d.dep ? u - s * d.w : u;
+      s = d.dep ? u / (uint32_t)d.w : 0u;
+      j = (int64_t)u - s * d.w;
     }
     const int64_t inst = s * d.w + j;
     const int64_t sigma = sigma0 + s;

@@ -103,6 +103,17 @@ constexpr uint64_t kAlign = 256;
 constexpr int64_t kAmpsPerHalfNode = 282;
 constexpr int kMaxHalfNodes = 16;
 
+// FP32-stored steps run on the split-bfloat16 kernel (kernels_split.hip),
+// which is faster and nearer to the 64-bit result than the FP32 instruction,
+// except in complex-half plans with more than this many FP16 tensors.  There a
+// change in an FP32 value's last bit decides some of the FP16 roundings after
+// it, each of which decides more of the next ones: after three or four FP16
+// tensors in a row every rounding is another one, and the amplitudes differ
+// from those of the FP32 instruction by the format's own error (1e-3; the
+// linear XEB by 4e-5) with no gain in accuracy.  Such plans keep the
+// instruction, so that their results stay the same bit for bit.
+constexpr int kMaxHalfSplit = 2;
+
 // bytes per stored element of node v: complex64 (8) unless the plan is
 // complex-half and v is an FP16-stored branch tensor (4)
 inline uint64_t eb_of(const Plan& P, int v) { return P.nodes[v].half_store ? 4 : 8; }
@@ -334,6 +345,7 @@ void build_steps(Plan& P) {
     P.nodes[v].half_store = half[v] != 0;
     P.n_half += half[v] ? 1 : 0;
   }
+  P.split = P.n_half <= kMaxHalfSplit;
   for (int v = nt; v < P.n_nodes; ++v) {
     PNode& V = P.nodes[v];
     const bool hm = V.half_store;  // FP16 output: FP16-product MFMA kernels
@@ -873,9 +885,12 @@ void launch_node(const Plan& P, const PNode& V, const NodeDesc& d, hipStream_t s
     // separate reduction pass (recording in the epilogue of the big tiles
     // raises their register use and cuts the occupancy)
     if (V.fan) {
-      e = V.rec_max ? launch_mfma_fan_rec(d, V.cfg, P.ws, sig, st) : launch_mfma_fan(d, V.cfg, P.ws, sig, st);
+      if (P.split)
+        e = V.rec_max ? launch_split_fan_rec(d, V.cfg, P.ws, sig, st) : launch_split_fan(d, V.cfg, P.ws, sig, st);
+      else
+        e = V.rec_max ? launch_mfma_fan_rec(d, V.cfg, P.ws, sig, st) : launch_mfma_fan(d, V.cfg, P.ws, sig, st);
     } else {
-      e = launch_mfma(d, V.cfg, P.ws, sig, st);
+      e = P.split ? launch_split(d, V.cfg, P.ws, sig, st) : launch_mfma(d, V.cfg, P.ws, sig, st);
       if (e == hipSuccess && V.rec_max) e = launch_absmax(d, P.ws, st);
     }
   } else if (V.kernel == 1) {
@@ -1160,7 +1175,7 @@ void launch_contract(const ContractCall& c, const void* A, const void* B, void* 
   d.nbits = c.nn;
   d.kbits = c.nk;
   const int64_t* sig = reinterpret_cast<const int64_t*>(base);
-  hipError_t e = c.kind == 1 ? launch_mfma(d, c.cfg, 0, sig, st) : launch_stream(d, 0, sig, st);
+  hipError_t e = c.kind == 1 ? launch_split(d, c.cfg, 0, sig, st) : launch_stream(d, 0, sig, st);
   hip_check(e, "contract launch");
 }
 

@@ -114,6 +114,7 @@ struct Plan {
   uint64_t memory_budget = 0;    // 0 = no limit
   int half_nodes = 0;            // complex-half: budget of FP16-stored intermediates
   int n_half = 0;                // complex-half: FP16-stored intermediates
+  bool split = true;  // FP32-stored MFMA steps run on the split-bfloat16 kernel
   int n_chunks = 1;
   std::vector<Chunk> chunks;
   std::vector<int> chunk_pos;    // node id -> position in chunked (-1 if not there)
