@@ -27,10 +27,8 @@
  *
  * Ownership: every host array passed in is copied before the call returns.
  * The library never allocates device memory: all device storage is the
- * caller's workspace (matnc_plan_bind) or the caller's output buffers, apart
- * from one 32 KiB device array per GPU owned by the library for
- * matnc_contract_noalloc.  The plan owns host metadata and, while bound, the
- * captured HIP graph.
+ * caller's workspace (matnc_plan_bind) or the caller's output buffers.  The
+ * plan owns host metadata and, while bound, the captured HIP graph.
  *
  * Errors: every call returns MATNC_OK (0) or one of the MATNC_E_* codes and
  * never throws or aborts across the ABI.  matnc_last_error() returns a
@@ -355,11 +353,10 @@ int matnc_queue_bind(matnc_queue q, void *dev_workspace, size_t bytes, void *hip
  * the first tile configuration that fits, 100 + c = MFMA tile configuration
  * c (0 <= c < matnc_mfma_config_count()).
  * dev_scratch: caller's device buffer of at least
- * matnc_contract_scratch_bytes() bytes, 256-byte aligned, holding the
- * offset tables of the call (the library allocates nothing).  The call
- * uploads them and waits for that copy; the contraction itself is
- * asynchronous on hip_stream.  Errors: MATNC_E_INVALID, MATNC_E_NOMEM
- * (scratch too small), MATNC_E_HIP.
+ * matnc_contract_scratch_bytes() bytes, 256-byte aligned (the library
+ * allocates nothing; the present kernels take the bit positions by value and
+ * leave the buffer alone).  One kernel launch, asynchronous on hip_stream.
+ * Errors: MATNC_E_INVALID, MATNC_E_NOMEM (scratch too small), MATNC_E_HIP.
  */
 size_t matnc_contract_scratch_bytes(void);
 int matnc_mfma_config_count(void);
@@ -375,14 +372,8 @@ int matnc_contract(const void *A, const void *B, void *C, int64_t batch,
  * matnc_contract_noalloc -- matnc_contract for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops): the same
  * arguments without dev_scratch, the same kernels and results (bit for bit).
- * The offset tables live in a library-owned device array of 32 KiB per GPU
- * (one call needs matnc_contract_scratch_bytes() = 24832 bytes of it), held
- * from the first call on a GPU until the process ends; they are written by a
- * kernel on hip_stream, so the call neither copies from the host nor waits.
- * The current device must be the device of hip_stream and of A, B, C.  Every
- * call on a GPU shares that GPU's array: calls that overlap on one GPU (on
- * different streams, or from different threads) race on it and must be
- * serialised by the caller.  Nothing is allocated by the call.
+ * The call neither copies from the host nor waits nor keeps state between
+ * calls; the current device must be the device of hip_stream and of A, B, C.
  * Errors: MATNC_E_INVALID (as matnc_contract), MATNC_E_HIP.
  */
 int matnc_contract_noalloc(const void *A, const void *B, void *C, int64_t batch,

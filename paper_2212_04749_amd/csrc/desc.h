@@ -66,6 +66,23 @@ struct NodeDesc {
   // tables), or about the number of units that share one A instance when
   // that instance is too large for the caches
   int32_t fan_rows;
+  int32_t flat;          // 1: output instance i reads instance i of A and of B (no gather map, no slices)
+  // Instances that the choice of an order of additions goes by: a plan's keys
+  // of the node, whatever the slice batch or key chunk of this launch, so that
+  // results do not depend on how slices and keys are grouped
+  int64_t n_ref;
+  int32_t keep_order;    // 1: sums keep the order of additions fixed by the shape (see kMaxHalfSplit)
+  int32_t ks_bits;       // long-sum kernel: 2^ks_bits lane groups share a sum
+  // split sums (matrix-core steps with few tiles and a long sum): the sum is
+  // cut into 2^ksplit parts, each a tile of its own writing to its own copy of
+  // the output at part_off (c layout, n_inst instances per part); a second
+  // kernel adds the copies in order
+  int32_t ksplit;
+  uint64_t part_off;
+  // storage bit of coordinate bit t, per table class: offsets from these cost
+  // a kernel two VALU operations per bit (none for wave-uniform coordinates)
+  // and no table in memory
+  int8_t pos[TAB_COUNT][32];
 };
 
 // Scaling of one stored instance in complex-half plans: true value = stored

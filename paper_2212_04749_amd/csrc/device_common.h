@@ -125,6 +125,38 @@ __device__ __forceinline__ uint32_t tlook_split(P T, uint32_t hi, uint32_t lo) {
   return T[lo] + T[256 + (hi & 255u)] + T[512 + ((hi >> 8) & 255u)] + T[768 + (hi >> 16)];
 }
 
+// offset of coordinate v (< 2^nbits) of class CLS, from the bit positions in
+// the descriptor; positions of bits that v does not have are not used
+template <int CLS>
+__device__ __forceinline__ uint32_t dep(const NodeDesc& d, int nbits, uint32_t v) {
+  uint32_t off = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    if (4 * q < nbits) {
+      uint32_t w;
+      __builtin_memcpy(&w, &d.pos[CLS][4 * q], 4);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) off |= ((v >> (4 * q + b)) & 1u) << ((w >> (8 * b)) & 31u);
+    }
+  }
+  return off;
+}
+
+// ... of the coordinate whose bits 4q .. 4q + 3 are e and the rest zero
+template <int CLS>
+__device__ __forceinline__ uint32_t dep_nibble(const NodeDesc& d, int q, uint32_t e) {
+  uint32_t w, off = 0;
+  __builtin_memcpy(&w, &d.pos[CLS][4 * q], 4);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) off |= ((e >> b) & 1u) << ((w >> (8 * b)) & 31u);
+  return off;
+}
+
+template <int C>
+struct Class {
+  static constexpr int value = C;
+};
+
 template <typename P>
 __device__ __forceinline__ int64_t operand_instance(const OpDesc& o, P gmap, int64_t j, int64_t s, int64_t sigma) {
   int64_t v = (int64_t)gmap[j] * o.nsv;

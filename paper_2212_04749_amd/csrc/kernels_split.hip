@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "desc.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -103,9 +105,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   __shared__ uint64_t s_cb[FAN ? TN : 1];
   __shared__ uint32_t s_mx[REC ? TN : 1];  // per-slot maxima (float bits)
   __shared__ float s_fb[(FAN && HB) ? TN : 1];  // per-slot factor 2^e of an FP16 B
+  // offsets of a tile's first row and column: [AM, CM, BN, CN][nibble][value];
+  // of a k step's change of bits 3 .. t: [AK, BK][t]
+  __shared__ uint32_t s_nib[4][8][16];
+  __shared__ uint32_t s_kx[2][32];
 
-  const gptr<const uint32_t> tab = gmem<const uint32_t>(ws + d.tab_off);
-  const cptr<const uint32_t> ctab = cmem<const uint32_t>(ws + d.tab_off);  // k-step lookups
   const gptr<const int32_t> glA = gmem<const int32_t>(ws + d.A.gmap_off);
   const gptr<const int32_t> glB = gmem<const int32_t>(ws + d.B.gmap_off);
   const int tid = threadIdx.x;
@@ -116,22 +120,80 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 
   const int nt_bits = FAN ? 0 : d.nbits - __builtin_ctz(TN);
   const int tbits = d.mbits - __builtin_ctz(TM) + nt_bits;  // tiles per unit = 2^tbits
-  const int ksteps = 1 << (d.kbits - __builtin_ctz(TK));
-  const int64_t sigma0 = sig[0];
+  const int ksteps = 1 << (d.kbits - d.ksplit - __builtin_ctz(TK));  // of this part
+  const int64_t sigma0 = d.flat ? 0 : sig[0];
   // work units: output instances, or (slice, fan row) pairs
   const uint32_t units = (uint32_t)(FAN ? ((uint32_t)d.n_inst / (uint32_t)d.w) * (uint32_t)d.n_fan : d.n_inst);
-  const uint32_t total = units << tbits;
+  const uint32_t upart = units << tbits;  // tiles of one part of the sum
+  const uint32_t total = upart << d.ksplit;
   const gptr<const int32_t> fan = gmem<const int32_t>(ws + d.fan_off);
   const uint32_t nmask = (1u << d.nbits) - 1u;
   const int slots = FAN ? (TN >> d.nbits) : 1;
+  const int half = lane >> 5;  // this lane's k quad
+  const int l32 = lane & 31;
+  const int dsel = l32 & 1;    // row of the real embedding: 0 real part, 1 imaginary part
+  const int ncol = l32 >> 1;
+
+  // Offsets inside a tile, the same for every tile of the launch (workgroups
+  // are persistent): a bit-by-bit deposit for each element here, a lookup of
+  // the tile's first row and column and of the k step's change in the loops.
+  // (Deposits or table reads in the loops cost 20-40% at 22/6/6 bits.)
+  if (lane < 16) {
+    auto nibbles = [&](auto cls, uint32_t(&tab)[8][16]) {
+      constexpr int C = decltype(cls)::value;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) tab[q][lane] = dep_nibble<C>(d, q, lane);
+    };
+    if (wave == 0) nibbles(Class<TAB_AM>(), s_nib[0]);
+    if (wave == 1) nibbles(Class<TAB_CM>(), s_nib[1]);
+    if (wave == 2) nibbles(Class<TAB_BN>(), s_nib[2]);
+    if (wave == 3) nibbles(Class<TAB_CN>(), s_nib[3]);
+  } else if (lane < 48) {
+    const uint32_t k = (2u << (lane - 16)) - 8u;
+    if (wave == 0) s_kx[0][lane - 16] = dep<TAB_AK>(d, d.kbits, k);
+    if (wave == 1) s_kx[1][lane - 16] = dep<TAB_BK>(d, d.kbits, k);
+  }
+  if (tid < TN) s_cn[tid] = dep<TAB_CN>(d, 8, FAN ? (tid & nmask) : tid);
   const bool astage = QA >= NT || tid < QA;
   const bool bstage = QB >= NT || tid < QB;
+
+  // A quad e of this thread covers m = amm[e], k = 4 akq[e] .. 4 akq[e] + 3 of
+  // the tile; likewise B quads over n
+  uint32_t aoff[EQA][4], boff[EQB][4];
+  int akq[EQA], bkq[EQB], amm[EQA], bnn[EQB];
+#pragma unroll
+  for (int e = 0; e < EQA; ++e) {
+    const int flat = astage ? e * NT + tid : 0;
+    amm[e] = flat % TM;
+    akq[e] = flat / TM;
+    const uint32_t om_ = dep<TAB_AM>(d, 8, amm[e]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) aoff[e][q] = om_ + dep<TAB_AK>(d, 4, 4 * akq[e] + q);
+  }
+#pragma unroll
+  for (int e = 0; e < EQB; ++e) {
+    const int flat = bstage ? e * NT + tid : 0;
+    bnn[e] = flat % TN;
+    bkq[e] = flat / TN;
+    const uint32_t on_ = dep<TAB_BN>(d, 8, FAN ? bnn[e] & nmask : bnn[e]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) boff[e][q] = on_ + dep<TAB_BK>(d, 4, 4 * bkq[e] + q);
+  }
+  uint32_t om[RM];  // output offsets of this lane's m values
+#pragma unroll
+  for (int i = 0; i < RM; ++i) om[i] = dep<TAB_CM>(d, 8, (wm * RM + i) * 32 + l32);
+  __syncthreads();
 
   for (uint32_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
     // logical tile order: n tiles innermost (they share the A tile), then m
     // tiles, then instances / fan rows (fan rows in blocks, see unit_tile);
     // each XCD takes a contiguous range
-    const uint32_t lt = xcd_tile(blk, total);
+    uint32_t lt = xcd_tile(blk, total);
+    uint32_t part = 0;
+    if (d.ksplit) {  // tiles of one part are neighbours: they share A and B
+      part = lt / upart;
+      lt -= part * upart;
+    }
     uint32_t u, t;
     unit_tile(lt, units, tbits, d.fan_rows > 0 ? (uint32_t)d.fan_rows : (FAN ? 2u : 1u), u, t);
     const uint32_t m0 = (t >> nt_bits) * TM;
@@ -148,57 +210,38 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
     }
     const int64_t inst = s * d.w + j;  // output instance (slot 0 for fan tiles)
     const int64_t sigma = sigma0 + s;
-    const int64_t ai = operand_instance(d.A, glA, j, s, sigma);
-    const int64_t bi = operand_instance(d.B, glB, j, s, sigma);
-    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes;
-    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes;
-    const gptr<f32x2> pc = gmem<f32x2>(ws + d.c_off + inst * d.c_inst_bytes);
+    const int64_t ai = !FAN && d.flat ? inst : operand_instance(d.A, glA, j, s, sigma);
+    const int64_t bi = !FAN && d.flat ? inst : operand_instance(d.B, glB, j, s, sigma);
+    // offsets of (m0, n0): lane 8c + q looks up nibble q of class c
+    uint32_t first = s_nib[(lane >> 3) & 3][lane & 7][((lane & 16 ? n0 : m0) >> (4 * (lane & 7))) & 15u];
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) first |= __shfl_xor(first, o);
+    const uint64_t oa0 = __builtin_amdgcn_readlane(first, 0), oc0 = (uint64_t)__builtin_amdgcn_readlane(first, 8) +
+                                                                     (uint64_t)__builtin_amdgcn_readlane(first, 24);
+    const uint64_t ob0 = __builtin_amdgcn_readlane(first, 16);
+    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes + oa0 * (HA ? 4 : 8);
+    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes + ob0 * (HB ? 4 : 8);
+    const uint64_t c_off = d.ksplit ? d.part_off + (uint64_t)part * (uint64_t)d.n_inst * d.c_inst_bytes : d.c_off;
+    const gptr<f32x2> pc = gmem<f32x2>(ws + c_off + inst * d.c_inst_bytes + oc0 * 8);
     const float ca = HA ? ldexpf(1.f, ldg_scale(ws + d.A.scale_off, ai).e) : 1.f;
     const float cb = HB ? ldexpf(1.f, ldg_scale(ws + d.B.scale_off, bi).e) : 1.f;
-    if (tid < TN) s_cn[tid] = tlook(tab + TAB_CN * kTabSize, FAN ? (tid & nmask) : n0 + tid);
     if (FAN && tid < slots) {
       // an empty slot reads slot 0's B into columns that are never stored
       const int jg = fj[tid];
       const int64_t bg = operand_instance(d.B, glB, jg < 0 ? j : jg, s, sigma);
       s_bb[tid] = d.B.off + bg * d.B.inst_bytes;
-      s_cb[tid] = jg < 0 ? 0 : d.c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes;
+      s_cb[tid] = jg < 0 ? 0 : c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes + oc0 * 8;
       if (REC) s_mx[tid] = 0u;
       if (HB) s_fb[tid] = ldexpf(1.f, ldg_scale(ws + d.B.scale_off, bg).e);
     }
-    __syncthreads();  // the column data above is read by every wave
+    if (FAN) __syncthreads();  // the column data above is read by every wave
 
-    // quad coordinates (fixed across k steps): A quad e of this thread covers
-    // m = amm[e], k = 4 akq[e] .. 4 akq[e] + 3 of the k step; likewise B over n
-    uint32_t aoff[EQA][4], boff[EQB][4];
-    int akq[EQA], bkq[EQB], amm[EQA], bnn[EQB];
-#pragma unroll
-    for (int e = 0; e < EQA; ++e) {
-      const int flat = astage ? e * NT + tid : 0;
-      amm[e] = flat % TM;
-      akq[e] = flat / TM;
-      const uint32_t om_ = tlook(tab + TAB_AM * kTabSize, m0 + amm[e]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) aoff[e][q] = om_ + tab[TAB_AK * kTabSize + 4 * akq[e] + q];
-    }
     uint64_t pbe[EQB];  // B instance of each quad (fan tiles: its slot's)
     float cbe[EQB];     // and its factor (FP16 B)
 #pragma unroll
     for (int e = 0; e < EQB; ++e) {
-      const int flat = bstage ? e * NT + tid : 0;
-      bnn[e] = flat % TN;
-      bkq[e] = flat / TN;
-      uint32_t on_;
-      if (FAN) {
-        pbe[e] = ws + s_bb[bnn[e] >> d.nbits];
-        cbe[e] = HB ? s_fb[bnn[e] >> d.nbits] : 1.f;
-        on_ = tlook(tab + TAB_BN * kTabSize, bnn[e] & nmask);
-      } else {
-        pbe[e] = pb;
-        cbe[e] = cb;
-        on_ = tlook(tab + TAB_BN * kTabSize, n0 + bnn[e]);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) boff[e][q] = on_ + tab[TAB_BK * kTabSize + 4 * bkq[e] + q];
+      pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] : pb;
+      cbe[e] = FAN ? (HB ? s_fb[bnn[e] >> d.nbits] : 1.f) : cb;
     }
     typename FStage<HA>::type ra[EQA][4];
     typename FStage<HB>::type rb[EQB][4];
@@ -259,34 +302,22 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][q][r] = 0.f;
 
-    const int half = lane >> 5;  // this lane's k quad
-    const int l32 = lane & 31;
-    const int dsel = l32 & 1;    // row of the real embedding: 0 real part, 1 imaginary part
-    const int ncol = l32 >> 1;
-
-    // output offsets of this lane's m values, fetched before the k loop
-    uint32_t om[RM];
-#pragma unroll
-    for (int i = 0; i < RM; ++i) om[i] = tlook(tab + TAB_CM * kTabSize, m0 + (wm * RM + i) * 32 + l32);
-
-    // k offsets run one step ahead of the loads that use them, so that their
-    // table reads are in flight during a whole step of MFMA work
-    uint32_t kba = tlook(ctab + TAB_AK * kTabSize, 0u), kbb = tlook(ctab + TAB_BK * kTabSize, 0u);
-    gload(kba, kbb);
-    if (ksteps > 1) {
-      kba = tlook(ctab + TAB_AK * kTabSize, (uint32_t)TK);
-      kbb = tlook(ctab + TAB_BK * kTabSize, (uint32_t)TK);
+    uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded
+    const uint32_t k0 = part * ((uint32_t)ksteps * TK);
+    if (d.ksplit) {
+      kba = dep<TAB_AK>(d, d.kbits, k0);
+      kbb = dep<TAB_BK>(d, d.kbits, k0);
     }
+    gload(kba, kbb);
     lstore(0);
     __syncthreads();
     for (int ks = 0; ks < ksteps; ++ks) {
       const int buf = ks & 1;
       if (ks + 1 < ksteps) {
+        const int t = 3 + __builtin_ctz(ks + 1);
+        kba ^= __builtin_amdgcn_readfirstlane(s_kx[0][t]);
+        kbb ^= __builtin_amdgcn_readfirstlane(s_kx[1][t]);
         gload(kba, kbb);
-        if (ks + 2 < ksteps) {
-          kba = tlook(ctab + TAB_AK * kTabSize, (uint32_t)(ks + 2) * TK);
-          kbb = tlook(ctab + TAB_BK * kTabSize, (uint32_t)(ks + 2) * TK);
-        }
       }
       auto afrag = [&](int p, int i) {
         return *reinterpret_cast<const bf16x8*>(&As[buf][p][half * AQ + 4 * ((wm * RM + i) * 32 + l32)]);
@@ -353,22 +384,22 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 #pragma unroll
         for (int r = 0; r < 16; ++r) fin = fmaf(acc[i][q][r], 0.f, fin);
     if (__any(fin != 0.f)) {
-      const uint32_t kcount = 1u << d.kbits;
+      const uint32_t k1 = k0 + (uint32_t)ksteps * TK;
       for (int e = lane; e < 32 * RM * 16 * RN; e += 64) {
         const int nl = wn * RN * 16 + e / (32 * RM);
-        const uint32_t m = m0 + wm * RM * 32 + e % (32 * RM);
+        const uint32_t m = wm * RM * 32 + e % (32 * RM);
         const int g = FAN ? nl >> d.nbits : 0;
         if (FAN && s_cb[g] == 0) continue;
         const uint64_t pbg = FAN ? ws + s_bb[g] : pb;
         const float cbg = FAN ? (HB ? s_fb[g] : 1.f) : cb;
-        const uint32_t oa = tlook(tab + TAB_AM * kTabSize, m);
-        const uint32_t ob = tlook(tab + TAB_BN * kTabSize, FAN ? (nl & nmask) : n0 + nl);
+        const uint32_t oa = dep<TAB_AM>(d, 8, m);
+        const uint32_t ob = dep<TAB_BN>(d, 8, FAN ? (nl & nmask) : nl);
         float2 c = make_float2(0.f, 0.f);
-        for (uint32_t k = 0; k < kcount; ++k)
-          cmac(c, FStage<HA>::val(FStage<HA>::load(pa, oa + tlook(tab + TAB_AK * kTabSize, k)), ca),
-               FStage<HB>::val(FStage<HB>::load(pbg, ob + tlook(tab + TAB_BK * kTabSize, k)), cbg));
+        for (uint32_t k = k0; k < k1; ++k)
+          cmac(c, FStage<HA>::val(FStage<HA>::load(pa, oa + dep<TAB_AK>(d, d.kbits, k)), ca),
+               FStage<HB>::val(FStage<HB>::load(pbg, ob + dep<TAB_BK>(d, d.kbits, k)), cbg));
         const gptr<f32x2> dst = FAN ? gmem<f32x2>(ws + s_cb[g]) : pc;
-        dst[tlook(tab + TAB_CM * kTabSize, m) + s_cn[nl]] = f32x2{c.x, c.y};
+        dst[dep<TAB_CM>(d, 8, m) + s_cn[nl]] = f32x2{c.x, c.y};
         if (REC) atomicMax(&s_mx[g], __float_as_uint(fmaxf(fmaxf(0.f, fabsf(c.x)), fabsf(c.y))));
       }
     } else {
@@ -411,7 +442,37 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
         if (jg >= 0 && s_mx[tid] > 0u) max_scale_mx(ws + d.c_scale_off, s * d.w + jg, s_mx[tid]);
       }
     }
-    __syncthreads();  // the next tile rewrites the column data
+    if (FAN) __syncthreads();  // the next tile rewrites the column data
+  }
+}
+
+// Adds the copies of a split sum in order; REC: and records each instance's
+// largest |component|.
+template <bool REC>
+__global__ __launch_bounds__(256) void k_split_add(NodeDesc d, uint64_t ws) {
+  const int eb = d.mbits + d.nbits;
+  const int64_t total = d.n_inst << eb;
+  const int parts = 1 << d.ksplit;
+  const uint64_t src = ws + d.part_off, dst = ws + d.c_off;
+  const int seg = eb >= 6 ? 64 : 1 << eb;
+  for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
+    const int64_t g = base + threadIdx.x;
+    float mx = 0.f;
+    if (g < total) {
+      float2 c = ldg_f2(src, g);
+      for (int p = 1; p < parts; p += 1) {
+        const float2 v = ldg_f2(src, (uint64_t)p * total + g);
+        c.x += v.x;
+        c.y += v.y;
+      }
+      stg_f2(dst, g, c);
+      mx = fmaxf(fabsf(c.x), fabsf(c.y));
+    }
+    if (REC) {
+      for (int o = seg >> 1; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+      if (g < total && (threadIdx.x & (seg - 1)) == 0 && mx > 0.f)
+        max_scale_mx(ws + d.c_scale_off, g >> eb, __float_as_uint(mx));
+    }
   }
 }
 
@@ -444,14 +505,43 @@ static hipError_t launch_split_t(const NodeDesc& d, int cfg, uint64_t ws, const 
   if (!fits || (FAN && (d.w <= 0 || d.n_fan <= 0))) return hipErrorInvalidValue;
   const int64_t units = FAN ? (d.n_inst / d.w) * d.n_fan : d.n_inst;
   const int tbits = d.mbits - mfma_config_tm_bits(cfg) + (FAN ? 0 : d.nbits - mfma_config_tn_bits(cfg));
-  const unsigned grid = grid_for(units << tbits);
+  // persistent: see the in-tile offsets; 2048 workgroups as for the FP16 tiles
+  const unsigned grid = (unsigned)std::min<int64_t>((units << tbits) << d.ksplit, 2048);
   // FP16-stored operands occur only in complex-half plans
+  hipError_t e;
+  const bool ks = d.ksplit > 0;  // the copies' sum records the maxima then
   if (d.A.half) {
-    if (d.B.half) return launch_split_s<FAN, REC, true, true>(d, cfg, grid, ws, sig, st);
-    return launch_split_s<FAN, REC, true, false>(d, cfg, grid, ws, sig, st);
+    if (d.B.half)
+      e = REC && !ks ? launch_split_s<FAN, REC, true, true>(d, cfg, grid, ws, sig, st)
+                     : launch_split_s<FAN, false, true, true>(d, cfg, grid, ws, sig, st);
+    else
+      e = REC && !ks ? launch_split_s<FAN, REC, true, false>(d, cfg, grid, ws, sig, st)
+                     : launch_split_s<FAN, false, true, false>(d, cfg, grid, ws, sig, st);
+  } else if (d.B.half) {
+    e = REC && !ks ? launch_split_s<FAN, REC, false, true>(d, cfg, grid, ws, sig, st)
+                   : launch_split_s<FAN, false, false, true>(d, cfg, grid, ws, sig, st);
+  } else {
+    e = REC && !ks ? launch_split_s<FAN, REC, false, false>(d, cfg, grid, ws, sig, st)
+                   : launch_split_s<FAN, false, false, false>(d, cfg, grid, ws, sig, st);
   }
-  if (d.B.half) return launch_split_s<FAN, REC, false, true>(d, cfg, grid, ws, sig, st);
-  return launch_split_s<FAN, REC, false, false>(d, cfg, grid, ws, sig, st);
+  if (e != hipSuccess || !ks) return e;
+  const unsigned g2 = grid_for(((d.n_inst << (d.mbits + d.nbits)) + 255) / 256);
+  if (REC)
+    hipLaunchKernelGGL((k_split_add<true>), dim3(g2), dim3(256), 0, st, d, ws);
+  else
+    hipLaunchKernelGGL((k_split_add<false>), dim3(g2), dim3(256), 0, st, d, ws);
+  return hipGetLastError();
+}
+
+int split_bits(int cfg, bool fan, int mbits, int nbits, int kbits, int64_t units) {
+  const int tbits = mbits - mfma_config_tm_bits(cfg) + (fan ? 0 : nbits - mfma_config_tn_bits(cfg));
+  const int64_t tiles = units << tbits;
+  // two workgroups per CU need no split; below that, four per CU as long as a
+  // part keeps 16 k steps
+  int sb = 0;
+  if (tiles < 512)
+    while ((tiles << sb) < 1024 && kbits - sb > 7) ++sb;
+  return sb;
 }
 
 hipError_t launch_split(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st) {

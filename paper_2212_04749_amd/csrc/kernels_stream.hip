@@ -3,16 +3,18 @@
 // compute (a big tensor times a gate-sized one, or a batched matrix-vector
 // product), so the kernels are built for HBM bandwidth:
 //
-//  * k_wide<FL, KB, R>     small K (<= 16) and N (<= 16): every lane owns R
-//    values of m spaced 256 apart (R x KB loads in flight), B is staged once
-//    per block in LDS, all offset tables that do not depend on m are hoisted.
-//    A block covers 256*R consecutive m of one instance, so instance
-//    decoding and B are block-uniform.
+//  * k_wide<FL, KB, R>     small K (<= 16): every lane owns R values of m
+//    spaced 256 apart (R x KB loads in flight) and up to 16 columns, whose B
+//    is staged once per block in LDS.  A block covers 256*R consecutive m of
+//    one instance, so instance decoding and B are block-uniform.
 //  * k_narrow<FL, KB>      the same for instances smaller than 256 elements:
-//    one lane per (instance, m).
+//    one lane per (instance, column group, m).
 //  * k_kred<FL, NB>        large K: lanes own m (coalesced reads of A along
 //    its low bits), groups of lanes split K, partial sums meet in LDS.
-//  * k_generic<FL>         anything else (one lane per output element).
+//
+// Offsets come from the bit positions in the descriptor (dep): no table is
+// read, so that a first touch of one does not delay the operand loads, and a
+// single contraction needs no table built before it.
 //
 // Precision policy P: C64 plans store float2 everywhere.  MIX (complex-half
 // plans) stores each tensor as __half2 with a per-instance exponent e
@@ -27,6 +29,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "desc.h"
 #include "device_common.h"
 #include "kernels.h"
@@ -36,6 +40,16 @@ namespace matnc {
 // Storage flags FL (compile-time): bit 3 = complex-half plan (scales
 // tracked); bit 0 / 1 / 2 = A / B / C stored as FP16 (else FP32).
 constexpr int kMixBit = 8;
+
+// lanes that fill the chip: 256 CUs x 1024
+constexpr int64_t kNarrowLanes = 256 * 1024;
+// blocks that keep HBM busy in a long sum
+constexpr int64_t kKredBlocks = 1024;
+// persistent blocks of the long-sum kernels: 8 per CU, so that the offsets in
+// LDS are set up once for several instances
+constexpr int64_t kBlocks = 2048;
+// one wave per instance fills the chip from four waves per CU up
+constexpr int64_t kDotInstances = 1024;
 
 template <int FL, int WHICH>
 __device__ __forceinline__ float2 ldop(uint64_t base, uint32_t i) {
@@ -122,7 +136,7 @@ __device__ __forceinline__ float segment_max(float v, int seg) {
 // first wave of the block that covers the instance's first elements
 template <int FL>
 __device__ __forceinline__ void block_record(const NodeDesc& d, uint64_t ws, int64_t inst, const OutScale& s, float mx,
-                                             float* /*red*/, bool first_block) {
+                                             bool first_block) {
   if constexpr ((FL & kMixBit) != 0) {
     mx = wave_max(mx);
     if ((threadIdx.x & 63) == 0) record_scale<FL>(d, ws, inst, s, mx, first_block && threadIdx.x == 0);
@@ -134,15 +148,21 @@ struct InstPtrs {
   uint64_t pa, pb, pc;
 };
 
-__device__ __forceinline__ InstPtrs instance_ptrs(const NodeDesc& d, uint64_t ws, int64_t inst, int64_t sigma0) {
+__device__ __forceinline__ InstPtrs instance_ptrs(const NodeDesc& d, uint64_t ws, int64_t inst,
+                                                  const int64_t* __restrict__ sig) {
   InstPtrs r;
   r.inst = inst;
-  const int64_t s = d.dep ? inst / d.w : 0;
-  const int64_t j = d.dep ? inst - s * d.w : inst;
-  const gptr<const int32_t> glA = gmem<const int32_t>(ws + d.A.gmap_off);
-  const gptr<const int32_t> glB = gmem<const int32_t>(ws + d.B.gmap_off);
-  r.ai = operand_instance(d.A, glA, j, s, sigma0 + s);
-  r.bi = operand_instance(d.B, glB, j, s, sigma0 + s);
+  if (d.flat) {
+    r.ai = r.bi = inst;
+  } else {
+    const int64_t s = d.dep ? inst / d.w : 0;
+    const int64_t j = d.dep ? inst - s * d.w : inst;
+    const int64_t sigma = sig[0] + s;
+    const gptr<const int32_t> glA = gmem<const int32_t>(ws + d.A.gmap_off);
+    const gptr<const int32_t> glB = gmem<const int32_t>(ws + d.B.gmap_off);
+    r.ai = operand_instance(d.A, glA, j, s, sigma);
+    r.bi = operand_instance(d.B, glB, j, s, sigma);
+  }
   r.pa = ws + d.A.off + (uint64_t)r.ai * d.A.inst_bytes;
   r.pb = ws + d.B.off + (uint64_t)r.bi * d.B.inst_bytes;
   r.pc = ws + d.c_off + (uint64_t)inst * d.c_inst_bytes;
@@ -151,38 +171,36 @@ __device__ __forceinline__ InstPtrs instance_ptrs(const NodeDesc& d, uint64_t ws
 
 // ---------------------------------------------------------------------------
 
-// N (<= 16) is a runtime bound: outputs are produced one n at a time
+// Columns are taken 16 at a time (a runtime bound below that); the blocks of
+// one m range's column groups are neighbours, so A is read from HBM once.
 template <int FL, int KB, int R>
 __global__ __launch_bounds__(256) void k_wide(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   constexpr int LR = (R == 1) ? 0 : (R == 2) ? 1 : (R == 4) ? 2 : 3;
   __shared__ float2 Bs[KB * 16];
-  __shared__ float red[4];
-  const gptr<const uint32_t> tab = gmem<const uint32_t>(ws + d.tab_off);
-  const gptr<const uint32_t> TA = tab + TAB_AM * kTabSize;
-  const gptr<const uint32_t> TC = tab + TAB_CM * kTabSize;
+  __shared__ uint32_t cns[16];
   const int tid = threadIdx.x;
-  const int NB = 1 << d.nbits;
-  const uint32_t oa_lo = TA[tid], oc_lo = TC[tid];
+  const int nb = d.nbits < 4 ? d.nbits : 4;
+  const int NB = 1 << nb;
+  const int ng = d.nbits - nb;  // column groups = 2^ng
+  const uint32_t oa_lo = dep<TAB_AM>(d, 8, tid), oc_lo = dep<TAB_CM>(d, 8, tid);
   uint32_t tak[KB];
 #pragma unroll
-  for (int k = 0; k < KB; ++k) tak[k] = tab[TAB_AK * kTabSize + k];
+  for (int k = 0; k < KB; ++k) tak[k] = dep<TAB_AK>(d, 4, k);
   // this lane's B element when staging (KB * NB <= 256)
-  uint32_t ob_mine = 0;
-  if (tid < KB * NB) ob_mine = tab[TAB_BK * kTabSize + tid / NB] + tab[TAB_BN * kTabSize + tid % NB];
+  const uint32_t bk_mine = dep<TAB_BK>(d, 4, tid >> nb);
   const int sh = d.mbits - 8 - LR;
-  const int64_t bpi = (int64_t)1 << sh;
-  const int64_t nblk = d.n_inst << sh;
-  const int64_t sigma0 = sig[0];
+  const int64_t nblk = d.n_inst << (sh + ng);
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const InstPtrs ip = instance_ptrs(d, ws, blk >> sh, sigma0);
-    const uint32_t hi0 = (uint32_t)(blk & (bpi - 1)) << LR;
-    if (tid < KB * NB) Bs[tid] = ldop<FL, 2>(ip.pb, ob_mine);
+    const InstPtrs ip = instance_ptrs(d, ws, blk >> (sh + ng), sig);
+    const uint32_t n0 = ((uint32_t)blk & ((1u << ng) - 1u)) << nb;
+    const uint32_t hi0 = ((uint32_t)(blk >> ng) & ((1u << sh) - 1u)) << LR;
+    if (tid < KB * NB) Bs[tid] = ldop<FL, 2>(ip.pb, bk_mine + dep<TAB_BN>(d, d.nbits, n0 + (tid & (NB - 1))));
+    if (tid < NB) cns[tid] = dep<TAB_CN>(d, d.nbits, n0 + tid);
     uint32_t oa[R], oc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const uint32_t hi = hi0 + r;
-      oa[r] = oa_lo + TA[256 + (hi & 255u)] + TA[512 + ((hi >> 8) & 255u)] + TA[768 + (hi >> 16)];
-      oc[r] = oc_lo + TC[256 + (hi & 255u)] + TC[512 + ((hi >> 8) & 255u)] + TC[768 + (hi >> 16)];
+      oa[r] = oa_lo + dep<TAB_AM>(d, d.mbits, (hi0 + r) << 8);
+      oc[r] = oc_lo + dep<TAB_CM>(d, d.mbits, (hi0 + r) << 8);
     }
     float2 a[R][KB];
 #pragma unroll
@@ -193,7 +211,7 @@ __global__ __launch_bounds__(256) void k_wide(NodeDesc d, uint64_t ws, const int
     __syncthreads();
     float mx = 0.f;
     for (int n = 0; n < NB; ++n) {
-      const uint32_t cn = tab[TAB_CN * kTabSize + n];
+      const uint32_t cn = cns[n];
       float2 b[KB];
 #pragma unroll
       for (int k = 0; k < KB; ++k) b[k] = Bs[k * NB + n];
@@ -205,25 +223,27 @@ __global__ __launch_bounds__(256) void k_wide(NodeDesc d, uint64_t ws, const int
         mx = fmaxf(mx, put<FL>(ip.pc, oc[r] + cn, c, s));
       }
     }
-    block_record<FL>(d, ws, ip.inst, s, mx, red, hi0 == 0);
+    block_record<FL>(d, ws, ip.inst, s, mx, hi0 == 0 && n0 == 0);
     __syncthreads();  // Bs is rewritten next iteration
   }
 }
 
+// npl: columns per lane (a power of two).  One where the step is so small
+// that lanes are idle otherwise, all of them where that fills the chip (A is
+// then read once per lane).
 template <int FL, int KB>
-__global__ __launch_bounds__(256) void k_narrow(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
-  const gptr<const uint32_t> tab = gmem<const uint32_t>(ws + d.tab_off);
-  const int NB = 1 << d.nbits;
+__global__ __launch_bounds__(256) void k_narrow(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig, int nplbits) {
+  const int NPL = 1 << nplbits;
   uint32_t tak[KB], tbk[KB];
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    tak[k] = tab[TAB_AK * kTabSize + k];
-    tbk[k] = tab[TAB_BK * kTabSize + k];
+    tak[k] = dep<TAB_AK>(d, 4, k);
+    tbk[k] = dep<TAB_BK>(d, 4, k);
   }
-  const int64_t total = d.n_inst << d.mbits;
-  const uint32_t mmask = (1u << d.mbits) - 1u;
-  const int64_t sigma0 = sig[0];
-  const int seg = d.mbits >= 6 ? 64 : (1 << d.mbits);
+  const int gb = d.mbits + d.nbits - nplbits;  // lanes per instance = 2^gb
+  const int64_t total = d.n_inst << gb;
+  const uint32_t mmask = (1u << d.mbits) - 1u, gmask = (1u << gb) - 1u;
+  const int seg = gb >= 6 ? 64 : (1 << gb);
   for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
     const int64_t g = base + threadIdx.x;
     const bool live = g < total;
@@ -231,76 +251,97 @@ __global__ __launch_bounds__(256) void k_narrow(NodeDesc d, uint64_t ws, const i
     OutScale s{1.f, 0};
     int64_t inst = 0;
     if (live) {
-      inst = g >> d.mbits;
+      inst = g >> gb;
       const uint32_t m = (uint32_t)g & mmask;
-      const InstPtrs ip = instance_ptrs(d, ws, inst, sigma0);
-      const uint32_t oa = tab[TAB_AM * kTabSize + m];
-      const uint32_t oc = tab[TAB_CM * kTabSize + m];
+      const uint32_t n0 = (((uint32_t)g & gmask) >> d.mbits) << nplbits;
+      const InstPtrs ip = instance_ptrs(d, ws, inst, sig);
+      const uint32_t oa = dep<TAB_AM>(d, d.mbits, m);
+      const uint32_t oc = dep<TAB_CM>(d, d.mbits, m);
       float2 a[KB];
 #pragma unroll
       for (int k = 0; k < KB; ++k) a[k] = ldop<FL, 1>(ip.pa, oa + tak[k]);
       s = out_scale<FL>(d, ws, ip.ai, ip.bi);
-      for (int n = 0; n < NB; ++n) {
-        const uint32_t bn = tab[TAB_BN * kTabSize + n];
+      for (int n = 0; n < NPL; ++n) {
+        const uint32_t bn = dep<TAB_BN>(d, d.nbits, n0 + n);
         float2 c = make_float2(0.f, 0.f);
 #pragma unroll
         for (int k = 0; k < KB; ++k) cmac(c, a[k], ldop<FL, 2>(ip.pb, bn + tbk[k]));
-        mx = fmaxf(mx, put<FL>(ip.pc, oc + tab[TAB_CN * kTabSize + n], c, s));
+        mx = fmaxf(mx, put<FL>(ip.pc, oc + dep<TAB_CN>(d, d.nbits, n0 + n), c, s));
       }
     }
     if constexpr ((FL & kMixBit) != 0) {
       // lanes of one instance are contiguous; reduce within segments of a wave
       mx = segment_max(mx, seg);
       const int lane = threadIdx.x & 63;
-      if (live && (lane & (seg - 1)) == 0) record_scale<FL>(d, ws, inst, s, mx, ((uint32_t)g & mmask) == 0);
+      if (live && (lane & (seg - 1)) == 0) record_scale<FL>(d, ws, inst, s, mx, ((uint32_t)g & gmask) == 0);
     }
   }
 }
 
-// large K: block = (instance, 256-wide chunk of m) or, for M < 256, one
-// instance with 256 / M groups splitting K
-// KS1: M >= 256, every lane of a block walks the same k, so B's offsets are
-// made wave-uniform and its loads go through the scalar path
-template <int FL, int NB, bool KS1>
+// sum of part[g * stride + o] over g < groups, in that order; sixteen reads are
+// in flight together (one at a time, 255 of them took 7 us)
+__device__ __forceinline__ float2 add_groups(const float2* part, int o, int stride, int groups) {
+  float2 c = part[o];
+  int g = 1;
+  for (; g + 15 < groups; g += 16) {
+    float2 v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = part[(g + u) * stride + o];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      c.x += v[u].x;
+      c.y += v[u].y;
+    }
+  }
+  for (; g < groups; ++g) {
+    c.x += part[g * stride + o].x;
+    c.y += part[g * stride + o].y;
+  }
+  return c;
+}
+
+// Large K: a block takes 2^mb values of m of one instance and NB of its
+// columns; 2^ks_bits groups of lanes take every 2^ks_bits-th k each, and their
+// partial sums are added in group order.  B goes through LDS, 256 k at a time.
+template <int FL, int NB>
 __global__ __launch_bounds__(256) void k_kred(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   __shared__ uint32_t kofa[256], kofb[256];
-  __shared__ float2 part[256 * NB];
-  __shared__ float red[4];
-  const gptr<const uint32_t> tab = gmem<const uint32_t>(ws + d.tab_off);
+  __shared__ float2 sb[256 * NB];  // B's chunk, then the partial sums
   const int tid = threadIdx.x;
-  kofa[tid] = tab[TAB_AK * kTabSize + tid];
-  kofb[tid] = tab[TAB_BK * kTabSize + tid];
-  uint32_t tbn[NB], tcn[NB];
-#pragma unroll
-  for (int n = 0; n < NB; ++n) {
-    tbn[n] = tab[TAB_BN * kTabSize + n];
-    tcn[n] = tab[TAB_CN * kTabSize + n];
-  }
-  __syncthreads();
-  const int mb = d.mbits < 8 ? d.mbits : 8;
+  const int ksb = d.ks_bits;
+  const int mb = d.mbits < 8 - ksb ? d.mbits : 8 - ksb;
   const int M = 1 << mb;
-  const int KS = 256 >> mb;            // groups splitting K
+  const int KS = 1 << ksb;
   const int mloc = tid & (M - 1);
-  const int grp = tid >> mb;
-  const int chunks_sh = d.mbits - mb;  // 256-wide m chunks per instance
-  const int64_t nblk = d.n_inst << chunks_sh;
+  const int grp = tid >> mb;           // >= KS: an idle lane
+  const bool live = grp < KS;
+  const int mch = d.mbits - mb;        // m chunks per instance = 2^mch
+  const int nch = d.nbits - __builtin_ctz(NB);
+  const int64_t nblk = d.n_inst << (mch + nch);
   const uint32_t kcount = 1u << d.kbits;
-  const uint32_t klo_n = kcount < 256u ? kcount : 256u;
-  const int64_t sigma0 = sig[0];
+  const int klb = d.kbits < 8 ? d.kbits : 8;
+  const uint32_t klo_n = 1u << klb;
+  kofa[tid] = dep<TAB_AK>(d, klb, tid & (klo_n - 1));
+  kofb[tid] = dep<TAB_BK>(d, klb, tid & (klo_n - 1));
+  __syncthreads();
   for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
-    const InstPtrs ip = instance_ptrs(d, ws, blk >> chunks_sh, sigma0);
-    const uint32_t chunk = (uint32_t)(blk & (((int64_t)1 << chunks_sh) - 1));
+    const InstPtrs ip = instance_ptrs(d, ws, blk >> (mch + nch), sig);
+    const uint32_t n0 = ((uint32_t)blk & ((1u << nch) - 1u)) * NB;
+    const uint32_t chunk = (uint32_t)(blk >> nch) & ((1u << mch) - 1u);
     const uint32_t m = (chunk << mb) + mloc;
     const uint64_t pa = ip.pa, pb = ip.pb;
-    const uint32_t om = tlook(tab + TAB_AM * kTabSize, m);
+    const uint32_t om = dep<TAB_AM>(d, d.mbits, m);
     float2 acc[NB];
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[n] = make_float2(0.f, 0.f);
-    for (uint32_t kh = 0; kh < (kcount >> 8) + (kcount < 256u ? 1u : 0u); ++kh) {
-      const uint32_t ba = om + tab[TAB_AK * kTabSize + 256 + (kh & 255u)] +
-                          tab[TAB_AK * kTabSize + 512 + ((kh >> 8) & 255u)] + tab[TAB_AK * kTabSize + 768 + (kh >> 16)];
-      const uint32_t bb = tab[TAB_BK * kTabSize + 256 + (kh & 255u)] +
-                          tab[TAB_BK * kTabSize + 512 + ((kh >> 8) & 255u)] + tab[TAB_BK * kTabSize + 768 + (kh >> 16)];
+    for (uint32_t kh = 0; kh < kcount; kh += klo_n) {
+      const uint32_t bb = dep<TAB_BK>(d, d.kbits, kh);
+      __syncthreads();  // the last chunk (or the partial sums) has been read
+      const uint32_t on = dep<TAB_BN>(d, d.nbits, n0 + tid % NB);
+      for (uint32_t e = tid; e < klo_n * NB; e += 256) sb[e] = ldop<FL, 2>(pb, bb + kofb[e / NB] + on);
+      __syncthreads();
+      if (!live) continue;
+      const uint32_t ba = om + dep<TAB_AK>(d, d.kbits, kh);
       uint32_t kl = grp;
       for (; kl + 7 * KS < klo_n; kl += 8 * KS) {
         float2 a[8];
@@ -308,83 +349,151 @@ __global__ __launch_bounds__(256) void k_kred(NodeDesc d, uint64_t ws, const int
         for (int u = 0; u < 8; ++u) a[u] = ldop<FL, 1>(pa, ba + kofa[kl + u * KS]);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          uint32_t ob = bb + kofb[kl + u * KS];
-          if constexpr (KS1) ob = __builtin_amdgcn_readfirstlane(ob);
 #pragma unroll
-          for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(pb, ob + tbn[n]));
+          for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], sb[(kl + u * KS) * NB + n]);
         }
       }
       for (; kl < klo_n; kl += KS) {
         const float2 a = ldop<FL, 1>(pa, ba + kofa[kl]);
-        const uint32_t ob = bb + kofb[kl];
 #pragma unroll
-        for (int n = 0; n < NB; ++n) cmac(acc[n], a, ldop<FL, 2>(pb, ob + tbn[n]));
+        for (int n = 0; n < NB; ++n) cmac(acc[n], a, sb[kl * NB + n]);
       }
     }
     const OutScale s = out_scale<FL>(d, ws, ip.ai, ip.bi);
     float mx = 0.f;
     if (KS > 1) {
-#pragma unroll
-      for (int n = 0; n < NB; ++n) part[tid * NB + n] = acc[n];
       __syncthreads();
-      if (grp == 0) {
-        for (int g = 1; g < KS; ++g)
+      if (live) {
 #pragma unroll
-          for (int n = 0; n < NB; ++n) {
-            const float2 v = part[(g * M + mloc) * NB + n];
-            acc[n].x += v.x;
-            acc[n].y += v.y;
-          }
+        for (int n = 0; n < NB; ++n) sb[tid * NB + n] = acc[n];
       }
-    }
-    if (grp == 0) {
-      const uint32_t oc = tlook(tab + TAB_CM * kTabSize, m);
+      __syncthreads();
+      const int out = M * NB;
+      for (int o = tid; o < out; o += 256) {
+        const float2 c = add_groups(sb, o, out, KS);
+        const uint32_t mo = (chunk << mb) + o / NB, no = n0 + o % NB;
+        mx = fmaxf(mx, put<FL>(ip.pc, dep<TAB_CM>(d, d.mbits, mo) + dep<TAB_CN>(d, d.nbits, no), c, s));
+      }
+    } else if (live) {
+      const uint32_t oc = dep<TAB_CM>(d, d.mbits, m);
 #pragma unroll
-      for (int n = 0; n < NB; ++n) mx = fmaxf(mx, put<FL>(ip.pc, oc + tcn[n], acc[n], s));
+      for (int n = 0; n < NB; ++n) mx = fmaxf(mx, put<FL>(ip.pc, oc + dep<TAB_CN>(d, d.nbits, n0 + n), acc[n], s));
     }
-    block_record<FL>(d, ws, ip.inst, s, mx, red, chunk == 0);
-    if (KS > 1) __syncthreads();  // part[] is rewritten next iteration
+    block_record<FL>(d, ws, ip.inst, s, mx, chunk == 0 && n0 == 0);
   }
 }
 
-template <int FL>
-__global__ __launch_bounds__(256) void k_generic(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
-  const gptr<const uint32_t> tab = gmem<const uint32_t>(ws + d.tab_off);
-  const int cb = d.mbits + d.nbits;
-  const int64_t total = d.n_inst << cb;
-  const int64_t sigma0 = sig[0];
-  const uint64_t kcount = (uint64_t)1 << d.kbits;
-  // lanes of one instance are contiguous: the output maximum is reduced
-  // within segments of a wave before its one atomic
-  const int seg = cb >= 6 ? 64 : (1 << cb);
-  for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
-    const int64_t g = base + threadIdx.x;
-    const bool live = g < total;
-    float mx = 0.f;
-    OutScale s{1.f, 0};
-    int64_t inst = 0;
-    if (live) {
-      inst = g >> cb;
-      const uint64_t mn = (uint64_t)g & (((uint64_t)1 << cb) - 1);
-      const uint32_t m = (uint32_t)(mn & (((uint64_t)1 << d.mbits) - 1));
-      const uint32_t n = (uint32_t)(mn >> d.mbits);
-      const InstPtrs ip = instance_ptrs(d, ws, inst, sigma0);
-      const uint32_t oa = tlook(tab + TAB_AM * kTabSize, m);
-      const uint32_t ob = tlook(tab + TAB_BN * kTabSize, n);
-      float2 c = make_float2(0.f, 0.f);
-      for (uint64_t k = 0; k < kcount; ++k) {
-        const uint32_t kk = (uint32_t)k;
-        cmac(c, ldop<FL, 1>(ip.pa, oa + tlook(tab + TAB_AK * kTabSize, kk)),
-             ldop<FL, 2>(ip.pb, ob + tlook(tab + TAB_BK * kTabSize, kk)));
+// The same sums (groups and order) for at most 8 values of m: too few share B
+// for LDS, and a lane's loads are spaced so far apart that the 256-wide steps
+// of k_kred would leave one in flight; here it is eight.  NT lanes: 256, or 512
+// where there are fewer instances than CUs can hold blocks.
+template <int FL, int NB, int NT>
+__global__ __launch_bounds__(NT) void k_kfew(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
+  __shared__ float2 sb[NT * NB];
+  const int tid = threadIdx.x;
+  const int M = 1 << d.mbits, KS = 1 << d.ks_bits;
+  const uint32_t m = tid & (M - 1), grp = tid >> d.mbits;  // grp >= KS: an idle lane
+  const uint32_t kcount = 1u << d.kbits;
+  const uint32_t oa = dep<TAB_AM>(d, 3, m) + dep<TAB_AK>(d, 12, grp & (KS - 1));
+  const uint32_t ob = dep<TAB_BK>(d, 12, grp & (KS - 1));
+  uint32_t tbn[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) tbn[n] = dep<TAB_BN>(d, 3, n);
+  const uint32_t oc = dep<TAB_CM>(d, 3, (uint32_t)tid / NB) + dep<TAB_CN>(d, 3, (uint32_t)tid % NB);
+  for (int64_t inst = blockIdx.x; inst < d.n_inst; inst += gridDim.x) {
+    const InstPtrs ip = instance_ptrs(d, ws, inst, sig);
+    if (grp < (uint32_t)KS) {
+      float2 acc[NB];
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acc[n] = make_float2(0.f, 0.f);
+      uint32_t k = 0;
+      for (; k + 8 * KS <= kcount; k += 8 * KS) {
+        float2 a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k + u * KS));
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k + u * KS);
+#pragma unroll
+          for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, obk + tbn[n]));
+        }
       }
-      s = out_scale<FL>(d, ws, ip.ai, ip.bi);
-      mx = put<FL>(ip.pc, tlook(tab + TAB_CM * kTabSize, m) + tlook(tab + TAB_CN * kTabSize, n), c, s);
+      for (; k < kcount; k += KS) {
+        const float2 a = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k));
+        const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) cmac(acc[n], a, ldop<FL, 2>(ip.pb, obk + tbn[n]));
+      }
+#pragma unroll
+      for (int n = 0; n < NB; ++n) sb[tid * NB + n] = acc[n];
+    }
+    __syncthreads();
+    const OutScale s = out_scale<FL>(d, ws, ip.ai, ip.bi);
+    float mx = 0.f;
+    if (tid < M * NB) mx = put<FL>(ip.pc, oc, add_groups(sb, tid, M * NB, KS), s);
+    if (tid < 64) block_record<FL>(d, ws, inst, s, mx, true);
+    __syncthreads();  // the partial sums are rewritten next iteration
+  }
+}
+
+// Large K, few outputs (at most 8 m and 8 columns per instance): one wave per
+// instance, whose lanes are 2^mbits values of m times 64 / 2^mbits groups that
+// take every such k each; the groups' sums meet in a tree of lane exchanges.
+// No LDS, no barrier, and four instances per block: a block per instance
+// spent its time on its set-up and on adding 256 partial sums one by one.
+template <int FL, int NB>
+__global__ __launch_bounds__(256) void k_kdot(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
+  const int lane = threadIdx.x & 63;
+  const int gb = 6 - d.mbits;
+  const uint32_t m = lane & ((1 << d.mbits) - 1);
+  const uint32_t grp = lane >> d.mbits;
+  const uint32_t KS = 1u << gb, kcount = 1u << d.kbits;
+  const uint32_t oa = dep<TAB_AM>(d, 3, m) + dep<TAB_AK>(d, 6, grp);
+  const uint32_t ob = dep<TAB_BK>(d, 6, grp);
+  uint32_t tbn[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) tbn[n] = dep<TAB_BN>(d, 3, n);
+  const uint32_t oc = dep<TAB_CM>(d, 3, m);
+  const int64_t stride = (int64_t)gridDim.x * 4;
+  for (int64_t inst = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); inst < d.n_inst; inst += stride) {
+    const InstPtrs ip = instance_ptrs(d, ws, inst, sig);
+    float2 acc[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) acc[n] = make_float2(0.f, 0.f);
+    uint32_t k = 0;
+    for (; k + 8 * KS <= kcount; k += 8 * KS) {
+      float2 a[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k + u * KS));
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k + u * KS);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, obk + tbn[n]));
+      }
+    }
+    for (; k + grp < kcount; k += KS) {
+      const float2 a = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k));
+      const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) cmac(acc[n], a, ldop<FL, 2>(ip.pb, obk + tbn[n]));
+    }
+    for (int o = 1 << d.mbits; o < 64; o <<= 1) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        acc[n].x += __shfl_xor(acc[n].x, o);
+        acc[n].y += __shfl_xor(acc[n].y, o);
+      }
+    }
+    const OutScale s = out_scale<FL>(d, ws, ip.ai, ip.bi);
+    float mx = 0.f;
+    if (grp == 0) {
+#pragma unroll
+      for (int n = 0; n < NB; ++n) mx = fmaxf(mx, put<FL>(ip.pc, oc + dep<TAB_CN>(d, 3, n), acc[n], s));
     }
     if constexpr ((FL & kMixBit) != 0) {
-      mx = segment_max(mx, seg);
-      const int lane = threadIdx.x & 63;
-      if (live && (lane & (seg - 1)) == 0)
-        record_scale<FL>(d, ws, inst, s, mx, ((uint64_t)g & (((uint64_t)1 << cb) - 1)) == 0);
+      mx = wave_max(mx);
+      if (lane == 0) record_scale<FL>(d, ws, inst, s, mx, true);
     }
   }
 }
@@ -399,44 +508,82 @@ static hipError_t launch_small(const NodeDesc& d, uint64_t ws, const int64_t* si
     // K is 16, to bound registers)
     constexpr int RMAX = KB >= 16 ? 2 : 4;
     const int extra = d.mbits - 8;
+    const int ng = d.nbits < 4 ? 0 : d.nbits - 4;  // column groups of 16
     if (RMAX >= 4 && extra >= 2) {
-      const int64_t blocks = d.n_inst << (d.mbits - 10);
+      const int64_t blocks = d.n_inst << (d.mbits - 10 + ng);
       hipLaunchKernelGGL((k_wide<FL, KB, 4>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
     } else if (extra >= 1) {
-      const int64_t blocks = d.n_inst << (d.mbits - 9);
+      const int64_t blocks = d.n_inst << (d.mbits - 9 + ng);
       hipLaunchKernelGGL((k_wide<FL, KB, 2>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
     } else {
-      const int64_t blocks = d.n_inst;
+      const int64_t blocks = d.n_inst << ng;
       hipLaunchKernelGGL((k_wide<FL, KB, 1>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
     }
   } else {
-    const int64_t blocks = ((d.n_inst << d.mbits) + 255) / 256;
-    hipLaunchKernelGGL((k_narrow<FL, KB>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
+    // as many columns per lane as still leave kNarrowLanes lanes
+    int npl = d.nbits;
+    while (npl > 0 && (d.n_inst << (d.mbits + d.nbits - npl)) < kNarrowLanes) --npl;
+    const int64_t blocks = ((d.n_inst << (d.mbits + d.nbits - npl)) + 255) / 256;
+    hipLaunchKernelGGL((k_narrow<FL, KB>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig, npl);
   }
   return hipGetLastError();
 }
 
 template <int FL>
-static hipError_t launch_kred(const NodeDesc& d, uint64_t ws, const int64_t* sig, hipStream_t st) {
+static hipError_t launch_kred(const NodeDesc& d0, uint64_t ws, const int64_t* sig, hipStream_t st) {
+  if (!d0.keep_order && d0.mbits <= 3 && d0.nbits <= 3 && d0.n_ref >= kDotInstances) {
+    const dim3 g((unsigned)std::min<int64_t>((d0.n_inst + 3) / 4, kBlocks)), b(256);
+    switch (d0.nbits) {
+      case 0: hipLaunchKernelGGL((k_kdot<FL, 1>), g, b, 0, st, d0, ws, sig); break;
+      case 1: hipLaunchKernelGGL((k_kdot<FL, 2>), g, b, 0, st, d0, ws, sig); break;
+      case 2: hipLaunchKernelGGL((k_kdot<FL, 4>), g, b, 0, st, d0, ws, sig); break;
+      default: hipLaunchKernelGGL((k_kdot<FL, 8>), g, b, 0, st, d0, ws, sig); break;
+    }
+    return hipGetLastError();
+  }
+  NodeDesc d = d0;
+  const int nb = d.nbits < 4 ? d.nbits : 4;
   const int mb = d.mbits < 8 ? d.mbits : 8;
-  const int64_t blocks = d.n_inst << (d.mbits - mb);
-  const dim3 g(grid_for(blocks)), b(256);
-  if (d.mbits >= 8) {
-    switch (d.nbits) {
-      case 0: hipLaunchKernelGGL((k_kred<FL, 1, true>), g, b, 0, st, d, ws, sig); break;
-      case 1: hipLaunchKernelGGL((k_kred<FL, 2, true>), g, b, 0, st, d, ws, sig); break;
-      case 2: hipLaunchKernelGGL((k_kred<FL, 4, true>), g, b, 0, st, d, ws, sig); break;
-      case 3: hipLaunchKernelGGL((k_kred<FL, 8, true>), g, b, 0, st, d, ws, sig); break;
-      default: return hipErrorInvalidValue;
+  // The lanes of a block that m does not fill split the sum (where the order
+  // of additions has to stay, sums of 16 columns run on one lane each).
+  d.ks_bits = d.keep_order && nb == 4 ? 0 : 8 - mb;
+  if (!d.keep_order) {
+    // fewer m per block, down to one wave of them, until there are
+    // kKredBlocks blocks: each lane's chain of loads gets shorter and more
+    // of them are in flight
+    while (8 - d.ks_bits > 6 && mb > 6 && (d.n_ref << (d.mbits - (8 - d.ks_bits) + d.nbits - nb)) < kKredBlocks)
+      ++d.ks_bits;
+  }
+  if (d.ks_bits > d.kbits) d.ks_bits = d.kbits;
+  const int m2 = d.mbits < 8 - d.ks_bits ? d.mbits : 8 - d.ks_bits;
+  const int64_t blocks = d.n_inst << (d.mbits - m2 + d.nbits - nb);
+  const dim3 g((unsigned)std::min<int64_t>(blocks, kBlocks)), b(256);
+  if (d.mbits <= 3 && d.nbits <= 3) {
+    if (!d.keep_order && d.n_ref < 512 && d.kbits > d.ks_bits && d.ks_bits + d.mbits == 8) {
+      ++d.ks_bits;
+      const dim3 b2(512);
+      switch (nb) {
+        case 0: hipLaunchKernelGGL((k_kfew<FL, 1, 512>), g, b2, 0, st, d, ws, sig); break;
+        case 1: hipLaunchKernelGGL((k_kfew<FL, 2, 512>), g, b2, 0, st, d, ws, sig); break;
+        case 2: hipLaunchKernelGGL((k_kfew<FL, 4, 512>), g, b2, 0, st, d, ws, sig); break;
+        default: hipLaunchKernelGGL((k_kfew<FL, 8, 512>), g, b2, 0, st, d, ws, sig); break;
+      }
+      return hipGetLastError();
     }
-  } else {
-    switch (d.nbits) {
-      case 0: hipLaunchKernelGGL((k_kred<FL, 1, false>), g, b, 0, st, d, ws, sig); break;
-      case 1: hipLaunchKernelGGL((k_kred<FL, 2, false>), g, b, 0, st, d, ws, sig); break;
-      case 2: hipLaunchKernelGGL((k_kred<FL, 4, false>), g, b, 0, st, d, ws, sig); break;
-      case 3: hipLaunchKernelGGL((k_kred<FL, 8, false>), g, b, 0, st, d, ws, sig); break;
-      default: return hipErrorInvalidValue;
+    switch (nb) {
+      case 0: hipLaunchKernelGGL((k_kfew<FL, 1, 256>), g, b, 0, st, d, ws, sig); break;
+      case 1: hipLaunchKernelGGL((k_kfew<FL, 2, 256>), g, b, 0, st, d, ws, sig); break;
+      case 2: hipLaunchKernelGGL((k_kfew<FL, 4, 256>), g, b, 0, st, d, ws, sig); break;
+      default: hipLaunchKernelGGL((k_kfew<FL, 8, 256>), g, b, 0, st, d, ws, sig); break;
     }
+    return hipGetLastError();
+  }
+  switch (nb) {
+    case 0: hipLaunchKernelGGL((k_kred<FL, 1>), g, b, 0, st, d, ws, sig); break;
+    case 1: hipLaunchKernelGGL((k_kred<FL, 2>), g, b, 0, st, d, ws, sig); break;
+    case 2: hipLaunchKernelGGL((k_kred<FL, 4>), g, b, 0, st, d, ws, sig); break;
+    case 3: hipLaunchKernelGGL((k_kred<FL, 8>), g, b, 0, st, d, ws, sig); break;
+    default: hipLaunchKernelGGL((k_kred<FL, 16>), g, b, 0, st, d, ws, sig); break;
   }
   return hipGetLastError();
 }
@@ -444,19 +591,14 @@ static hipError_t launch_kred(const NodeDesc& d, uint64_t ws, const int64_t* sig
 template <int FL>
 static hipError_t launch_stream_fl(const NodeDesc& d, uint64_t ws, const int64_t* sig, hipStream_t st) {
   if (d.n_inst == 0) return hipSuccess;
-  if (d.kbits <= 4 && d.nbits <= 4) {
-    switch (d.kbits) {
-      case 0: return launch_small<FL, 1>(d, ws, sig, st);
-      case 1: return launch_small<FL, 2>(d, ws, sig, st);
-      case 2: return launch_small<FL, 4>(d, ws, sig, st);
-      case 3: return launch_small<FL, 8>(d, ws, sig, st);
-      case 4: return launch_small<FL, 16>(d, ws, sig, st);
-    }
+  switch (d.kbits) {
+    case 0: return launch_small<FL, 1>(d, ws, sig, st);
+    case 1: return launch_small<FL, 2>(d, ws, sig, st);
+    case 2: return launch_small<FL, 4>(d, ws, sig, st);
+    case 3: return launch_small<FL, 8>(d, ws, sig, st);
+    case 4: return launch_small<FL, 16>(d, ws, sig, st);
   }
-  if (d.nbits <= 3) return launch_kred<FL>(d, ws, sig, st);
-  const int64_t blocks = ((d.n_inst << (d.mbits + d.nbits)) + 255) / 256;
-  hipLaunchKernelGGL((k_generic<FL>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
-  return hipGetLastError();
+  return launch_kred<FL>(d, ws, sig, st);
 }
 
 hipError_t launch_stream(const NodeDesc& d, uint64_t ws, const int64_t* sig, hipStream_t st) {

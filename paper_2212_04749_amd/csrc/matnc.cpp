@@ -114,6 +114,10 @@ constexpr int kMaxHalfNodes = 16;
 // instruction, so that their results stay the same bit for bit.
 constexpr int kMaxHalfSplit = 2;
 
+// largest region, per slice, for the parts of split sums: 1024 tiles' worth of
+// parts of the 64 KiB tiles
+constexpr uint64_t kMaxPartBytes = 64ull << 20;
+
 // bytes per stored element of node v: complex64 (8) unless the plan is
 // complex-half and v is an FP16-stored branch tensor (4)
 inline uint64_t eb_of(const Plan& P, int v) { return P.nodes[v].half_store ? 4 : 8; }
@@ -410,28 +414,31 @@ void build_steps(Plan& P) {
       const double reuse = (double)V.ga.size() / std::max(1.0, distinct);
       if (reuse >= 2.0 || (nb == 4 && kb >= 6)) {
         // 64-column tiles when the groups are large enough to fill them
-        // (the A tile is then read once for twice as many instances)
-        const int tn = (nb <= 4 && reuse >= 1.5 * (double)(32 >> nb)) ? 64 : 32;
+        // (the A tile is then read once for twice as many instances), else,
+        // or where no 64-column tile is small enough for m, 32
+        const bool wide = nb <= 4 && reuse >= 1.5 * (double)(32 >> nb);
         const int order_f32[] = {0, 3, 2, -1};
         const int order_f64[] = {4, 1, -1, -1};
         const int order_h32[] = {1, 3, 2, 4};
         const int order_h64[] = {5, 0, 6, -1};
-        const int* order = hm ? (tn == 64 ? order_h64 : order_h32) : (tn == 64 ? order_f64 : order_f32);
-        for (int t = 0; t < 4; ++t) {
-          const int c = order[t];
-          const bool fits = hm ? mfma_h_fan_config_fits(c, mb, nb, kb, tn) : mfma_fan_config_fits(c, mb, nb, kb, tn);
-          if (fits) {
-            V.kernel = 1;
-            V.fan = true;
-            V.fan_tn = tn;
-            V.cfg = c;
-            // both tile widths' tables, so that the tuner may pick either
-            make_fan(V.ga, 32 >> nb, V.fanv[0], V.n_fan[0]);
-            make_fan(V.ga, 64 >> nb, V.fanv[1], V.n_fan[1]);
-            const uint64_t ab = (1ull << A.idx.size()) * eb_of(P, V.swap ? V.b : V.a);
-            V.fan_rows[0] = fan_block_rows(V.fanv[0], 32 >> nb, V.ga, ab);
-            V.fan_rows[1] = fan_block_rows(V.fanv[1], 64 >> nb, V.ga, ab);
-            break;
+        for (int tn = wide ? 64 : 32; tn >= 32 && !V.fan; tn = P.split ? tn - 32 : 0) {
+          const int* order = hm ? (tn == 64 ? order_h64 : order_h32) : (tn == 64 ? order_f64 : order_f32);
+          for (int t = 0; t < 4; ++t) {
+            const int c = order[t];
+            const bool fits = hm ? mfma_h_fan_config_fits(c, mb, nb, kb, tn) : mfma_fan_config_fits(c, mb, nb, kb, tn);
+            if (fits) {
+              V.kernel = 1;
+              V.fan = true;
+              V.fan_tn = tn;
+              V.cfg = c;
+              // both tile widths' tables, so that the tuner may pick either
+              make_fan(V.ga, 32 >> nb, V.fanv[0], V.n_fan[0]);
+              make_fan(V.ga, 64 >> nb, V.fanv[1], V.n_fan[1]);
+              const uint64_t ab = (1ull << A.idx.size()) * eb_of(P, V.swap ? V.b : V.a);
+              V.fan_rows[0] = fan_block_rows(V.fanv[0], 32 >> nb, V.ga, ab);
+              V.fan_rows[1] = fan_block_rows(V.fanv[1], 64 >> nb, V.ga, ab);
+              break;
+            }
           }
         }
       }
@@ -455,6 +462,33 @@ void build_steps(Plan& P) {
       P.bytes_inv += by;
     }
   }
+  // Split sums.  The number of parts goes by the node's keys alone, not by
+  // slice batch, key chunk or tuned tile, so that none of these changes an
+  // amplitude's bits.
+  for (int v = nt; v < P.n_nodes; ++v) {
+    PNode& V = P.nodes[v];
+    V.ksplit = 0;
+    if (!P.split || V.kernel != 1 || V.half_store) continue;
+    const int64_t units = V.fan ? V.n_fan[V.fan_tn == 64 ? 1 : 0] : (int64_t)V.keys.size();
+    V.ksplit = split_bits(V.cfg, V.fan, (int)V.M.size(), (int)V.N.size(), (int)V.K.size(), units);
+    while (V.ksplit > 0 && (((uint64_t)V.keys.size() << V.idx.size()) * 8) << V.ksplit > kMaxPartBytes) --V.ksplit;
+  }
+  // storage bit of every coordinate bit
+  for (int v = nt; v < P.n_nodes; ++v) {
+    PNode& V = P.nodes[v];
+    const std::vector<int>&A = P.nodes[V.swap ? V.b : V.a].idx, &B = P.nodes[V.swap ? V.a : V.b].idx;
+    auto fill = [&](int cls, const std::vector<int>& order, const std::vector<int>& storage) {
+      for (size_t t = 0; t < order.size(); ++t)
+        V.pos[cls][t] = (int8_t)(std::find(storage.begin(), storage.end(), order[t]) - storage.begin());
+    };
+    std::memset(V.pos, 0, sizeof(V.pos));
+    fill(TAB_AM, V.M, A);
+    fill(TAB_CM, V.M, V.idx);
+    fill(TAB_BN, V.N, B);
+    fill(TAB_CN, V.N, V.idx);
+    fill(TAB_AK, V.K, A);
+    fill(TAB_BK, V.K, B);
+  }
   // FP32 tensors whose maximum an FP16 consumer needs for its exponent (and
   // for the scaling of its FP16 products)
   for (int v = nt; v < P.n_nodes; ++v) {
@@ -463,20 +497,15 @@ void build_steps(Plan& P) {
   }
 }
 
-// offset tables of one class: entry e of level L = sum over bits t of e of
-// 2^pos(index 8L+t)
-void fill_table(uint32_t* T, const std::vector<int>& order, const std::vector<int>& storage) {
-  std::vector<int> pos(order.size());
-  for (size_t t = 0; t < order.size(); ++t) {
-    auto it = std::find(storage.begin(), storage.end(), order[t]);
-    pos[t] = (int)(it - storage.begin());
-  }
+// offset table of one class: entry e of level L = sum over bits t of e of
+// 2^(storage position of coordinate bit 8L+t)
+void fill_table(uint32_t* T, const int8_t* pos, size_t nbits) {
   for (int L = 0; L < kTabLevels; ++L)
     for (int e = 0; e < kTabEntries; ++e) {
       uint32_t off = 0;
       for (int t = 0; t < 8; ++t) {
         const size_t bit = (size_t)(8 * L + t);
-        if (((e >> t) & 1) && bit < pos.size()) off += 1u << pos[bit];
+        if (((e >> t) & 1) && bit < nbits) off += 1u << pos[bit];
       }
       T[L * kTabEntries + e] = off;
     }
@@ -725,18 +754,33 @@ void build_memory_for(Plan& P, int n_chunks) {
     if (b.t1 == t_end && b.node != root) P.cache_bytes += b.size;
   }
   P.workspace_bytes = align_up(P.static_bytes + arena);
+  // room behind the arena for the parts of split sums (used within a launch
+  // only, so one region serves every node)
+  P.part_off = P.workspace_bytes;
+  uint64_t part = 0;
+  for (int v = nt; v < P.n_nodes; ++v) {
+    const PNode& V = P.nodes[v];
+    if (V.ksplit) part = std::max(part, (uint64_t)cap_inst[v] * (V.dep ? P.batch : 1) * V.inst_elems * 8 << V.ksplit);
+  }
+  P.workspace_bytes += align_up(part);
 }
 
 // smallest power-of-two chunk count whose workspace fits the budget
 void build_memory(Plan& P) {
-  int c = 1;
-  build_memory_for(P, c);
   const int64_t nr = (int64_t)P.nodes[P.n_nodes - 1].keys.size();
-  while (P.memory_budget && P.workspace_bytes > P.memory_budget && c < nr) {
-    c *= 2;
+  auto fit = [&] {
+    int c = 1;
     build_memory_for(P, c);
-  }
-  if (P.memory_budget && P.workspace_bytes > P.memory_budget)
+    while (P.memory_budget && P.workspace_bytes > P.memory_budget && c < nr) {
+      c *= 2;
+      build_memory_for(P, c);
+    }
+    return !P.memory_budget || P.workspace_bytes <= P.memory_budget;
+  };
+  if (fit()) return;
+  // no room even for single keys: sums in one piece need less
+  for (PNode& V : P.nodes) V.ksplit = 0;
+  if (!fit())
     fail(MATNC_E_NOMEM, "plan needs " + std::to_string(P.workspace_bytes) + " bytes of workspace even with " +
                             std::to_string(P.n_chunks) + " key chunks; budget " + std::to_string(P.memory_budget));
 }
@@ -849,6 +893,11 @@ NodeDesc node_desc(const Plan& P, int v, int nb, int c = 0) {
   d.mbits = (int32_t)V.M.size();
   d.nbits = (int32_t)V.N.size();
   d.kbits = (int32_t)V.K.size();
+  std::memcpy(d.pos, V.pos, sizeof(d.pos));
+  d.keep_order = P.split ? 0 : 1;
+  d.n_ref = (int64_t)V.keys.size();
+  d.part_off = P.part_off + P.arena_delta;
+  d.ksplit = V.ksplit;
   if (V.fan) {
     const int t = V.fan_tn == 64 ? 1 : 0;
     d.fan_off = pos >= 0 ? P.chunks[c].nodes[pos].fan_off[t] : V.fan_off[t];
@@ -1062,21 +1111,30 @@ void write_tune_cache(const char* path, const std::map<std::string, int>& m) {
 // ---------------------------------------------------------------------------
 // single pairwise contractions (matnc_contract, matnc_contract_noalloc)
 
-// scratch of one call: a zero head (int64 sigma slot at byte 0, a zero
-// int32 gather entry at byte 8), then the six offset tables
+// The size callers' scratch buffers have (it once held offset tables; the
+// kernels now take bit positions by value and use no scratch).
 constexpr size_t kContractScratchBytes = kAlign + (size_t)TAB_COUNT * kTabSize * 4;
-
-struct TabPos {
-  int8_t pos[TAB_COUNT][32];  // storage bit of coordinate bit i, per table class
-  int32_t nbits[TAB_COUNT];
-};
 
 struct ContractCall {
   int64_t batch;
   int nm, nn, nk;
-  int kind, cfg;  // 0 streaming, 1 MFMA configuration cfg
-  TabPos pos;
+  int kind, cfg;               // 0 streaming, 1 MFMA configuration cfg
+  bool swap;                   // the caller's B is the kernel's A
+  int8_t pos[TAB_COUNT][32];   // storage bit of coordinate bit i
 };
+
+// Tile configuration of one contraction, -1 if none fits: the largest tile
+// (most products per staged byte) that still gives every CU two workgroups,
+// else the smallest.
+int contract_config(int64_t batch, int nm, int nn, int nk) {
+  int last = -1;
+  for (int k : {5, 4, 1, 0, 2}) {
+    if (!mfma_config_fits(k, nm, nn, nk)) continue;
+    last = k;
+    if ((batch << (nm - mfma_config_tm_bits(k) + nn - mfma_config_tn_bits(k))) >= 512) break;
+  }
+  return last;
+}
 
 // validates the arguments of one contraction and picks its kernel
 ContractCall contract_call(int64_t batch, int nm, int nn, int nk, const int* posA_m, const int* posA_k,
@@ -1104,24 +1162,11 @@ ContractCall contract_call(int64_t batch, int nm, int nn, int nk, const int* pos
   ContractCall c;
   std::memset(&c, 0, sizeof(c));
   c.batch = batch;
-  c.nm = nm;
-  c.nn = nn;
-  c.nk = nk;
-  c.kind = 0;
   c.cfg = -1;
-  if (kernel == -1) {
-    if (nn + nk > 8) {
-      const int order[] = {1, 0, 3, 2};
-      for (int k : order)
-        if (mfma_config_fits(k, nm, nn, nk)) {
-          c.kind = 1;
-          c.cfg = k;
-          break;
-        }
-    }
-  } else if (kernel == 0) {
-    c.kind = 0;
-  } else if (kernel == 1) {
+  // Explicit tile configurations are checked against the shape as given; the
+  // other selectors take the operand with more free bits as A (the kernels'
+  // lanes run along m).
+  if (kernel == 1) {
     for (int k = 0; k < mfma_config_count() && c.cfg < 0; ++k)
       if (mfma_config_fits(k, nm, nn, nk)) c.cfg = k;
     if (c.cfg < 0) fail(MATNC_E_INVALID, "no MFMA tile fits this shape");
@@ -1130,26 +1175,46 @@ ContractCall contract_call(int64_t batch, int nm, int nn, int nk, const int* pos
     c.cfg = kernel - 100;
     if (!mfma_config_fits(c.cfg, nm, nn, nk)) fail(MATNC_E_INVALID, "MFMA tile does not fit this shape");
     c.kind = 1;
+  } else if (kernel == -1 || kernel == 0) {
+    c.swap = nn > nm;
+    if (c.swap) {
+      std::swap(nm, nn);
+      std::swap(posA_m, posB_n);
+      std::swap(posA_k, posB_k);
+      std::swap(posC_m, posC_n);
+    }
+    if (kernel == -1 && nn + nk > 8) {
+      c.cfg = contract_config(batch, nm, nn, nk);
+      c.kind = c.cfg >= 0 ? 1 : 0;
+    }
   } else {
     fail(MATNC_E_INVALID, "unknown kernel selector");
   }
-  const int* src[TAB_COUNT];
-  src[TAB_AM] = posA_m;
-  src[TAB_CM] = posC_m;
-  src[TAB_BN] = posB_n;
-  src[TAB_CN] = posC_n;
-  src[TAB_AK] = posA_k;
-  src[TAB_BK] = posB_k;
-  const int nb[TAB_COUNT] = {nm, nm, nn, nn, nk, nk};
-  for (int t = 0; t < TAB_COUNT; ++t) {
-    c.pos.nbits[t] = nb[t];
-    for (int i = 0; i < nb[t]; ++i) c.pos.pos[t][i] = (int8_t)src[t][i];
-  }
+  c.nm = nm;
+  c.nn = nn;
+  c.nk = nk;
+  // The order of a class's bits is free as long as both tensors share it:
+  // lowest storage bits first, so that a tile or a wave covers whole runs of
+  // both (the k bits by the larger operand's order).
+  auto order = [&](int cx, const int* x, int cy, const int* y, int n, bool both) {
+    std::vector<int> t(n);
+    std::iota(t.begin(), t.end(), 0);
+    std::stable_sort(t.begin(), t.end(), [&](int a, int b) {
+      return (both ? std::min(x[a], y[a]) : x[a]) < (both ? std::min(x[b], y[b]) : x[b]);
+    });
+    for (int i = 0; i < n; ++i) {
+      c.pos[cx][i] = (int8_t)x[t[i]];
+      c.pos[cy][i] = (int8_t)y[t[i]];
+    }
+  };
+  order(TAB_AM, posA_m, TAB_CM, posC_m, nm, true);
+  order(TAB_BN, posB_n, TAB_CN, posC_n, nn, true);
+  order(TAB_AK, posA_k, TAB_BK, posB_k, nk, false);
   return c;
 }
 
-// the contraction of one call; base = device address of its scratch
-void launch_contract(const ContractCall& c, const void* A, const void* B, void* C, uint64_t base, hipStream_t st) {
+// the contraction of one call: one launch, operands in order
+void launch_contract(const ContractCall& c, const void* A, const void* B, void* C, hipStream_t st) {
   NodeDesc d;
   std::memset(&d, 0, sizeof(d));
   auto op = [&](const void* p, int rank) {
@@ -1157,66 +1222,22 @@ void launch_contract(const ContractCall& c, const void* A, const void* B, void* 
     std::memset(&o, 0, sizeof(o));
     o.off = reinterpret_cast<uint64_t>(p);
     o.inst_bytes = 8ull << rank;
-    o.gmap_off = base + 8;  // a single zero entry
-    o.w_child = 1;
-    o.dep = 1;
-    o.nsv = 1;
     return o;
   };
-  d.A = op(A, c.nm + c.nk);
-  d.B = op(B, c.nn + c.nk);
+  d.A = op(c.swap ? B : A, c.nm + c.nk);
+  d.B = op(c.swap ? A : B, c.nn + c.nk);
   d.c_off = reinterpret_cast<uint64_t>(C);
   d.c_inst_bytes = 8ull << (c.nm + c.nn);
-  d.tab_off = base + kAlign;
   d.w = 1;
   d.dep = 1;
-  d.n_inst = c.batch;
+  d.flat = 1;
+  d.n_inst = d.n_ref = c.batch;
   d.mbits = c.nm;
   d.nbits = c.nn;
   d.kbits = c.nk;
-  const int64_t* sig = reinterpret_cast<const int64_t*>(base);
-  hipError_t e = c.kind == 1 ? launch_split(d, c.cfg, 0, sig, st) : launch_stream(d, 0, sig, st);
+  std::memcpy(d.pos, c.pos, sizeof(d.pos));
+  hipError_t e = c.kind == 1 ? launch_split(d, c.cfg, 0, nullptr, st) : launch_stream(d, 0, nullptr, st);
   hip_check(e, "contract launch");
-}
-
-// The scratch of matnc_contract_noalloc: one copy per GPU, held until the
-// process ends, shared by every call on that GPU (calls that overlap on one
-// GPU race on it).  Host code never uses the symbol's name as an address:
-// the device address of each GPU's copy comes from hipGetSymbolAddress,
-// taken once per device with that device current.
-static __device__ __align__(256) unsigned char scratch[32768];
-
-__global__ void k_contract_tables(TabPos pos, uint32_t* base) {
-  // block t writes table class t; block 0 also clears the head (sigma slot
-  // and the zero gather entry)
-  const int t = blockIdx.x, e = threadIdx.x;
-  if (t == 0 && e < (int)(kAlign / 4)) base[e] = 0u;
-  uint32_t* T = base + kAlign / 4 + t * kTabSize;
-  for (int L = 0; L < kTabLevels; ++L) {
-    uint32_t off = 0;
-    for (int b = 0; b < 8; ++b) {
-      const int bit = 8 * L + b;
-      if (((e >> b) & 1) && bit < pos.nbits[t]) off += 1u << pos.pos[t][bit];
-    }
-    T[L * kTabEntries + e] = off;
-  }
-}
-
-std::mutex g_scratch_mu;
-std::vector<void*> g_scratch_dev;  // device address of `scratch` per device id
-
-void* static_scratch_ptr() {
-  int dev = 0;
-  hip_check(hipGetDevice(&dev), "get device");
-  std::lock_guard<std::mutex> lk(g_scratch_mu);
-  if ((size_t)dev >= g_scratch_dev.size()) g_scratch_dev.resize((size_t)dev + 1, nullptr);
-  if (!g_scratch_dev[dev]) {
-    void* p = nullptr;
-    hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)), "scratch symbol address");
-    if (!p) fail(MATNC_E_HIP, "scratch symbol has no device address");
-    g_scratch_dev[dev] = p;
-  }
-  return g_scratch_dev[dev];
 }
 
 // attaches plan P to its static region at dev_workspace (and its arena at
@@ -1240,14 +1261,8 @@ void bind_plan(Plan& P, void* dev_workspace, size_t bytes, void* hip_stream, uin
   for (int v = nt; v < P.n_nodes; ++v) {
     const PNode& V = P.nodes[v];
     uint32_t* T = reinterpret_cast<uint32_t*>(P.staging.data() + V.tab_off);
-    const PNode& A = P.nodes[V.swap ? V.b : V.a];
-    const PNode& B = P.nodes[V.swap ? V.a : V.b];
-    fill_table(T + TAB_AM * kTabSize, V.M, A.idx);
-    fill_table(T + TAB_CM * kTabSize, V.M, V.idx);
-    fill_table(T + TAB_BN * kTabSize, V.N, B.idx);
-    fill_table(T + TAB_CN * kTabSize, V.N, V.idx);
-    fill_table(T + TAB_AK * kTabSize, V.K, A.idx);
-    fill_table(T + TAB_BK * kTabSize, V.K, B.idx);
+    const size_t nbits[TAB_COUNT] = {V.M.size(), V.M.size(), V.N.size(), V.N.size(), V.K.size(), V.K.size()};
+    for (int t = 0; t < TAB_COUNT; ++t) fill_table(T + t * kTabSize, V.pos[t], nbits[t]);
     if (P.chunk_pos[v] < 0) {
       std::memcpy(P.staging.data() + V.ga_off, V.ga.data(), V.ga.size() * 4);
       std::memcpy(P.staging.data() + V.gb_off, V.gb.data(), V.gb.size() * 4);
@@ -1895,23 +1910,7 @@ int matnc_contract(const void* A, const void* B, void* C, int64_t batch, int nm,
     if (scratch_bytes < matnc_contract_scratch_bytes()) fail(MATNC_E_NOMEM, "scratch too small");
     const ContractCall c = contract_call(batch, nm, nn, nk, posA_m, posA_k, posB_k, posB_n, posC_m, posC_n, kernel);
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-    // host image of the scratch: zero head (sigma slot, one zero gather
-    // entry), then the six offset tables
-    std::vector<unsigned char> img(matnc_contract_scratch_bytes(), 0);
-    uint32_t* T = reinterpret_cast<uint32_t*>(img.data() + kAlign);
-    for (int t = 0; t < TAB_COUNT; ++t)
-      for (int L = 0; L < kTabLevels; ++L)
-        for (int e = 0; e < kTabEntries; ++e) {
-          uint32_t off = 0;
-          for (int b = 0; b < 8; ++b) {
-            const int bit = 8 * L + b;
-            if (((e >> b) & 1) && bit < c.pos.nbits[t]) off += 1u << c.pos.pos[t][bit];
-          }
-          T[t * kTabSize + L * kTabEntries + e] = off;
-        }
-    hip_check(hipMemcpyAsync(dev_scratch, img.data(), img.size(), hipMemcpyHostToDevice, st), "upload tables");
-    hip_check(hipStreamSynchronize(st), "upload tables");
-    launch_contract(c, A, B, C, reinterpret_cast<uint64_t>(dev_scratch), st);
+    launch_contract(c, A, B, C, st);
   });
 }
 
@@ -1921,15 +1920,7 @@ int matnc_contract_noalloc(const void* A, const void* B, void* C, int64_t batch,
   return guarded([&] {
     if (!A || !B || !C) fail(MATNC_E_INVALID, "null argument");
     const ContractCall c = contract_call(batch, nm, nn, nk, posA_m, posA_k, posB_k, posB_n, posC_m, posC_n, kernel);
-    static_assert(kContractScratchBytes <= sizeof(scratch), "static scratch smaller than one call's tables");
-    const uint64_t base = reinterpret_cast<uint64_t>(static_scratch_ptr());
-    hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-    // the same scratch image as matnc_contract uploads, written by a kernel
-    // on the caller's stream: no copy, no wait, nothing allocated
-    hipLaunchKernelGGL(k_contract_tables, dim3(TAB_COUNT), dim3(kTabEntries), 0, st, c.pos,
-                       reinterpret_cast<uint32_t*>(base));
-    hip_check(hipGetLastError(), "table kernel launch");
-    launch_contract(c, A, B, C, base, st);
+    launch_contract(c, A, B, C, reinterpret_cast<hipStream_t>(hip_stream));
   });
 }
 

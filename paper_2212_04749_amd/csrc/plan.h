@@ -60,6 +60,8 @@ struct PNode {
   int32_t fan_rows[2] = {2, 2};  // tile-order blocks of the two tables (NodeDesc::fan_rows)
   int32_t unit_rows = 1;         // ... of the output instances of a plain MFMA step
   std::vector<int> M, N, K;      // virtual orders of the three index classes
+  int ksplit = 0;                // MFMA step: log2 of the parts of its sum
+  int8_t pos[TAB_COUNT][32] = {};  // storage bit of each coordinate bit, per table class
   // memory
   uint64_t inst_elems = 0;
   uint64_t buf_bytes = 0;        // whole buffer (all instances of a launch)
@@ -126,6 +128,7 @@ struct Plan {
   uint64_t static_bytes = 0;
   uint64_t workspace_bytes = 0;
   uint64_t cache_bytes = 0;
+  uint64_t part_off = 0;         // parts of split sums (behind the arena)
   // node ids in schedule order: computed once per cache fill (prologue),
   // once per chunk (cpro), per slice batch and chunk (loop); chunked =
   // cpro followed by loop
