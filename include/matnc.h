@@ -229,10 +229,11 @@ int matnc_plan_bind(matnc_plan plan, void *dev_workspace, size_t bytes, void *hi
 int matnc_execute(matnc_plan plan, int64_t slice_begin, int64_t slice_end, double *amps_dev);
 
 /* matnc_execute_timed: the same work as matnc_execute over the same range
- * (same launches, same results, bit for bit), launched one by one rather
- * than replayed from captured graphs, with a pair of HIP events on the
- * bound stream around every launch of contraction step `step` (0 ..
- * n_tensors - 2, the order of the plan's pairs).  It blocks until the
+ * (same kernels, same results, bit for bit), launched one by one and slice
+ * batch by slice batch rather than replayed from captured graphs, with a pair
+ * of HIP events on the bound stream around every launch of contraction step
+ * `step` (0 .. n_tensors - 2, the order of the plan's pairs; for a step fused
+ * with others, around the launch that holds it).  It blocks until the
  * stream is idle, then stores in *ms_total the summed event time of those
  * launches (milliseconds) and in *launches their number (once per slice
  * batch and key chunk for a slice-dependent step, once for an invariant
@@ -281,7 +282,8 @@ int matnc_plan_reset_cache(matnc_plan plan);
  * starting at slice_begin, with a HIP event pair around every node's launch
  * on the bound stream; waits for the stream.  For step j (0 <= j <
  * n_tensors - 1) it writes
- *   time_ms[j]  elapsed time of that launch (-1 if the node has no work),
+ *   time_ms[j]  elapsed time of that launch (-1 if the node has no work;
+ *               steps fused into one launch get equal shares of it),
  *   kernel[j]   0 = streaming kernel, 100 + c = FP32 MFMA tile
  *               configuration c, 200 + c = FP32 MFMA configuration c as
  *               fan-out tiles (the output instances that share an A

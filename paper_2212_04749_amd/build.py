@@ -16,7 +16,7 @@ OUT = os.path.join(HERE, "libmatnc.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["matnc.cpp", "kernels_stream.hip", "kernels_c64.hip", "kernels_split.hip",
-           "kernels_chalf.hip"]
+           "kernels_chalf.hip", "kernels_tree.hip"]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950",

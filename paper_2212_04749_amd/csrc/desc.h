@@ -93,6 +93,38 @@ struct HalfScale {
   uint32_t mx;
 };
 
+// Fused subtrees of small steps (kernels_tree.hip): a table of n_comp + 1
+// word offsets, then each component's words: TreeHeader, the inputs, the
+// steps, level starts (n_levels + 1 positions in the item list), the items
+// (step << 16 | 64-output chunk) and the gather maps.  Offsets in the header
+// and in TreeStep::gmap count words from the component's first.
+constexpr int kTreeThreads = 1024;
+constexpr int kTreeWords = 6 * 1024;    // 24 KiB of description
+constexpr int kTreeElems = 16 * 1024;   // 128 KiB of tensors
+constexpr int kTreeMaxBits = 12;        // output bits of one instance
+
+struct TreeHeader {
+  uint32_t n_levels, n_inputs, inputs, steps, levels, items;
+};
+
+struct TreeInput {
+  uint32_t off_lo, off_hi;  // byte offset of instance 0 in the workspace
+  uint32_t lds;             // first element in LDS
+  uint32_t ebits, keys;     // instances of 2^ebits elements
+  uint32_t nsb;             // leaf: sliced indices; instance = key * 2^nsb + their bits of sigma
+  uint32_t sbit[4];         // sigma bit of each, one byte per index
+};
+
+struct TreeStep {
+  uint32_t bits;            // m | n << 8 | k << 16 | (result to the arena) << 24
+  uint32_t outputs;         // w << (m + n)
+  uint32_t a, b;            // operands' first elements in LDS: (k, m) and (k, n), k highest
+  uint32_t c_lo, c_hi;      // LDS element, or byte offset in the workspace
+  uint32_t w;               // instances per slice
+  uint32_t gmap;            // B instance << 16 | A instance, per output instance; 0: instance 0 of both
+  uint32_t pos[3];          // storage bit of output coordinate bit t (m bits, then n bits), one byte each
+};
+
 __host__ __device__ inline int64_t sub_index(const OpDesc& o, int64_t sigma) {
   int64_t v = 0;
   for (int t = 0; t < o.nsb; ++t) v |= ((sigma >> o.sbit[t]) & 1) << t;

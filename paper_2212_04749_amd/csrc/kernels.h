@@ -53,6 +53,10 @@ hipError_t launch_absmax(const NodeDesc& d, uint64_t ws, hipStream_t st);
 
 // shared
 hipError_t launch_xeb(const double* amps, int64_t count, int n_qubits, double* out, hipStream_t st);
+// nb slices of n_comp fused subtrees (see TreeStep), from slice sig[0], or
+// sigma0 where sig is null
+hipError_t launch_tree(uint64_t ws, uint64_t table_off, int n_comp, int nb, const int64_t* sig, int64_t sigma0,
+                       hipStream_t st);
 hipError_t launch_set_i64(int64_t* p, int64_t v, hipStream_t st);
 
 }  // namespace matnc

@@ -541,15 +541,10 @@ __global__ __launch_bounds__(256) void k_slice_sum_h(OpDesc root, uint64_t ws, c
     for (int s = 0; s < nb; ++s) {
       const int64_t inst = operand_instance(root, gmap, rp, s, sigma0 + s);
       const uint64_t base = ws + root.off + inst * root.inst_bytes;
-      float2 v;
-      if (root.half) {
-        const uint32_t u = ldg_u32(base, o);
-        __half2 h;
-        __builtin_memcpy(&h, &u, 4);
-        v = __half22float2(h);
-      } else {
-        v = ldg_f2(base, o);
-      }
+      const uint32_t u = ldg_u32(base, o);
+      __half2 h;
+      __builtin_memcpy(&h, &u, 4);
+      const float2 v = __half22float2(h);
       const int e = ldg_scale(sc, inst).e;
       acc.x += ldexp((double)v.x, e);
       acc.y += ldexp((double)v.y, e);

@@ -114,6 +114,18 @@ constexpr int kMaxHalfNodes = 16;
 // instruction, so that their results stay the same bit for bit.
 constexpr int kMaxHalfSplit = 2;
 
+// Steps fused into one workgroup's subtree: up to 2^16 complex multiply-adds
+// (about 3 us there; a launch of its own costs 5 us and more), tensors of up
+// to 32 KiB.
+constexpr uint64_t kFuseMacs = 1ull << 16;
+constexpr uint64_t kFuseElems = 4096;
+constexpr uint64_t kFuseKeys = 1024;
+
+// slices per launch where a whole slice is one fused subtree: four workgroups
+// per CU one after another, and at most this much for their results
+constexpr int64_t kTreeBatch = 1024;
+constexpr uint64_t kTreeBatchBytes = 16ull << 20;
+
 // largest region, per slice, for the parts of split sums: 1024 tiles' worth of
 // parts of the 64 KiB tiles
 constexpr uint64_t kMaxPartBytes = 64ull << 20;
@@ -497,6 +509,53 @@ void build_steps(Plan& P) {
   }
 }
 
+// Marks the steps that run inside fused subtrees (kernels_tree.hip): small
+// steps all of whose operands are leaves, slice-invariant tensors read by a
+// slice-dependent step, or fused steps themselves, as long as everything the
+// subtree holds fits LDS.  The rule looks at a node's own subtree and at all
+// of its keys only, so that slice batches and key chunks do not change it.
+void mark_fused(Plan& P) {
+  const int nt = P.net.n_tensors;
+  auto elems = [&](int v) { return (uint64_t)P.nodes[v].keys.size() << P.nodes[v].idx.size(); };
+  std::vector<uint64_t> held(P.n_nodes, 0), words(P.n_nodes, 0);  // LDS elements and description words below v
+  for (int v = nt; v < P.n_nodes; ++v) {
+    PNode& V = P.nodes[v];
+    const int mb = (int)V.M.size(), nb = (int)V.N.size(), kb = (int)V.K.size();
+    const uint64_t w = V.keys.size();
+    V.fused = false;
+    if (V.half_store || V.rec_max || w > kFuseKeys || mb + nb > kTreeMaxBits) continue;
+    if (elems(v) > kFuseElems || elems(V.a) > kFuseElems || elems(V.b) > kFuseElems) continue;
+    if ((w << (mb + nb + kb)) > kFuseMacs) continue;
+    // A step that would else run on the matrix cores or as a long sum adds in
+    // another order here; it is fused only where it always is: not where key
+    // chunks may move it out of the prologue, nor where that order must stay.
+    if ((V.kernel == 1 || kb > 4) && (!P.split || !(V.dep || w == 1))) continue;
+    // operands lie (k highest, m or n in order) by construction
+    bool ok = true;
+    for (int t = 0; t < mb; ++t) ok = ok && V.pos[TAB_AM][t] == t;
+    for (int t = 0; t < nb; ++t) ok = ok && V.pos[TAB_BN][t] == t;
+    for (int t = 0; t < kb; ++t) ok = ok && V.pos[TAB_AK][t] == mb + t && V.pos[TAB_BK][t] == nb + t;
+    if (!ok) continue;
+    uint64_t h = elems(v), wd = sizeof(TreeStep) / 4 + w + (((w << (mb + nb)) + 63) / 64) + 1;
+    for (int c : {V.a, V.b}) {
+      const PNode& C = P.nodes[c];
+      if (c >= nt && C.half_store) ok = false;
+      if (c < nt || C.dep != V.dep) {  // an input
+        h += elems(c);
+        wd += sizeof(TreeInput) / 4;
+      } else {
+        ok = ok && C.fused;
+        h += held[c];
+        wd += words[c];
+      }
+    }
+    if (!ok || h > (uint64_t)kTreeElems || wd + 16 > (uint64_t)kTreeWords) continue;
+    V.fused = true;
+    held[v] = h;
+    words[v] = wd;
+  }
+}
+
 // offset table of one class: entry e of level L = sum over bits t of e of
 // 2^(storage position of coordinate bit 8L+t)
 void fill_table(uint32_t* T, const int8_t* pos, size_t nbits) {
@@ -591,6 +650,139 @@ void build_chunks(Plan& P, int n_chunks) {
   }
 }
 
+// how a node of chunk c reads child `child` (gmap_off: the gather map)
+OpDesc operand_desc(const Plan& P, int child, uint64_t gmap_off, int c) {
+  const PNode& C = P.nodes[child];
+  OpDesc o;
+  std::memset(&o, 0, sizeof(o));
+  o.off = C.off + (child >= P.net.n_tensors ? P.arena_delta : 0);
+  o.inst_bytes = C.inst_elems * eb_of(P, child);
+  o.half = C.half_store ? 1 : 0;
+  o.gmap_off = gmap_off;
+  o.scale_off = C.scale_off;
+  const int pos = P.chunk_pos.empty() ? -1 : P.chunk_pos[child];
+  o.w_child = pos >= 0 ? P.chunks[c].nodes[pos].w : (int32_t)C.keys.size();
+  const bool leaf = child < P.net.n_tensors;
+  o.dep = (!leaf && C.dep) ? 1 : 0;
+  o.nsb = leaf ? (int32_t)C.sl_bits.size() : 0;
+  o.nsv = 1 << o.nsb;
+  for (int t = 0; t < o.nsb; ++t) o.sbit[t] = (int8_t)C.sl_bits[t];
+  return o;
+}
+
+// description of the fused subtrees of one list for chunk c (desc.h, TreeStep)
+std::vector<uint32_t> tree_words(const Plan& P, const Tree& T, int c) {
+  const int nt = P.net.n_tensors;
+  std::vector<uint32_t> out(T.roots.size() + 1);
+  auto width = [&](int v) {
+    return (uint32_t)(P.chunk_pos[v] >= 0 ? P.chunks[c].nodes[P.chunk_pos[v]].w : (int32_t)P.nodes[v].keys.size());
+  };
+  for (size_t r = 0; r < T.roots.size(); ++r) {
+    // the root's fused steps, deepest first
+    std::vector<int> steps, todo{T.roots[r]};
+    while (!todo.empty()) {
+      const int v = todo.back();
+      todo.pop_back();
+      steps.push_back(v);
+      for (int ch : {P.nodes[v].a, P.nodes[v].b})
+        if (ch >= nt && P.nodes[ch].in_lds && P.nodes[ch].dep == P.nodes[v].dep) todo.push_back(ch);
+    }
+    std::sort(steps.begin(), steps.end());
+    std::vector<TreeInput> inputs;
+    std::vector<TreeStep> desc;
+    std::vector<std::vector<uint32_t>> levels;
+    std::vector<uint32_t> gmaps;  // word positions are fixed up below
+    std::map<int, uint32_t> lds;
+    std::map<int, int> level;
+    uint32_t used = 0;
+    auto place = [&](int v) {
+      lds[v] = used;
+      used += width(v) << P.nodes[v].idx.size();
+    };
+    auto input = [&](int v) {
+      const OpDesc o = operand_desc(P, v, 0, c);
+      TreeInput in;
+      std::memset(&in, 0, sizeof(in));
+      in.off_lo = (uint32_t)o.off;
+      in.off_hi = (uint32_t)(o.off >> 32);
+      in.ebits = (uint32_t)P.nodes[v].idx.size();
+      in.keys = width(v);
+      in.nsb = (uint32_t)o.nsb;
+      for (int t = 0; t < o.nsb; ++t) in.sbit[t >> 2] |= (uint32_t)(uint8_t)o.sbit[t] << (8 * (t & 3));
+      place(v);
+      in.lds = lds[v];
+      inputs.push_back(in);
+      level[v] = -1;
+    };
+    for (int v : steps) {
+      const PNode& V = P.nodes[v];
+      const int ca = V.swap ? V.b : V.a, cb = V.swap ? V.a : V.b;
+      for (int ch : {ca, cb})
+        if (!lds.count(ch)) input(ch);
+      TreeStep t;
+      std::memset(&t, 0, sizeof(t));
+      const uint32_t mb = (uint32_t)V.M.size(), nb = (uint32_t)V.N.size(), kb = (uint32_t)V.K.size();
+      t.w = width(v);
+      t.bits = mb | nb << 8 | kb << 16 | (V.in_lds ? 0u : 1u << 24);
+      t.outputs = t.w << (mb + nb);
+      t.a = lds[ca];
+      t.b = lds[cb];
+      if (V.in_lds) {
+        place(v);
+        t.c_lo = lds[v];
+      } else {
+        const uint64_t off = V.off + P.arena_delta;
+        t.c_lo = (uint32_t)off;
+        t.c_hi = (uint32_t)(off >> 32);
+      }
+      if (t.w > 1) {
+        t.gmap = (uint32_t)gmaps.size() + 1;
+        const int pos = P.chunk_pos[v];
+        const std::vector<int32_t>&ga = pos >= 0 ? P.chunks[c].nodes[pos].ga : V.ga,
+                        &gb = pos >= 0 ? P.chunks[c].nodes[pos].gb : V.gb;
+        for (uint32_t j = 0; j < t.w; ++j) gmaps.push_back((uint32_t)ga[j] | (uint32_t)gb[j] << 16);
+      }
+      for (uint32_t q = 0; q < mb + nb; ++q)
+        t.pos[q >> 2] |= (uint32_t)(uint8_t)(q < mb ? V.pos[TAB_CM][q] : V.pos[TAB_CN][q - mb]) << (8 * (q & 3));
+      level[v] = std::max(level[ca], level[cb]) + 1;
+      if ((int)levels.size() <= level[v]) levels.resize(level[v] + 1);
+      for (uint32_t o = 0; o < (t.outputs + 63) / 64; ++o)
+        levels[level[v]].push_back((uint32_t)desc.size() << 16 | o);
+      desc.push_back(t);
+    }
+    TreeHeader h;
+    h.n_levels = (uint32_t)levels.size();
+    h.n_inputs = (uint32_t)inputs.size();
+    h.inputs = sizeof(TreeHeader) / 4;
+    h.steps = h.inputs + (uint32_t)(inputs.size() * sizeof(TreeInput) / 4);
+    h.levels = h.steps + (uint32_t)(desc.size() * sizeof(TreeStep) / 4);
+    h.items = h.levels + h.n_levels + 1;
+    std::vector<uint32_t> starts{0}, items;
+    for (const auto& l : levels) {
+      items.insert(items.end(), l.begin(), l.end());
+      starts.push_back((uint32_t)items.size());
+    }
+    const uint32_t gm = h.items + (uint32_t)items.size();
+    for (TreeStep& t : desc)
+      if (t.gmap) t.gmap += gm - 1;
+    if (used > (uint32_t)kTreeElems || gm + gmaps.size() > (size_t)kTreeWords)
+      fail(MATNC_E_INVALID, "fused subtree exceeds its LDS");
+    out[r] = (uint32_t)out.size();
+    auto append = [&](const void* p, size_t bytes) {
+      const uint32_t* w = static_cast<const uint32_t*>(p);
+      out.insert(out.end(), w, w + bytes / 4);
+    };
+    append(&h, sizeof(h));
+    append(inputs.data(), inputs.size() * sizeof(TreeInput));
+    append(desc.data(), desc.size() * sizeof(TreeStep));
+    append(starts.data(), starts.size() * 4);
+    append(items.data(), items.size() * 4);
+    append(gmaps.data(), gmaps.size() * 4);
+  }
+  out[T.roots.size()] = (uint32_t)out.size();
+  return out;
+}
+
 struct ArenaBuf {
   int node;
   uint64_t size;
@@ -608,23 +800,44 @@ void build_memory_for(Plan& P, int n_chunks) {
   P.prologue.clear();
   P.cpro.clear();
   P.loop.clear();
+  P.pro_tree = Tree();
+  P.loop_tree = Tree();
   for (int v = nt; v < P.n_nodes; ++v) {
-    const PNode& V = P.nodes[v];
-    if (V.dep)
+    PNode& V = P.nodes[v];
+    V.in_lds = false;
+    const bool per_chunk = !V.dep && n_chunks > 1 && V.keys.size() > 1;
+    Tree& T = V.dep ? P.loop_tree : P.pro_tree;
+    if (V.fused && !per_chunk) {
+      T.nodes.push_back(v);
+      // a root unless the parent is fused in the same list
+      const bool root_v = v == root || !P.nodes[V.parent].fused || P.nodes[V.parent].dep != V.dep ||
+                          (!V.dep && n_chunks > 1 && P.nodes[V.parent].keys.size() > 1);
+      if (root_v)
+        T.roots.push_back(v);
+      else
+        V.in_lds = true;
+    } else if (V.dep) {
       P.loop.push_back(v);
-    else if (n_chunks > 1 && V.keys.size() > 1)
+    } else if (per_chunk) {
       P.cpro.push_back(v);
-    else
+    } else {
       P.prologue.push_back(v);
+    }
   }
   P.chunked = P.cpro;
+  P.chunked.insert(P.chunked.end(), P.loop_tree.nodes.begin(), P.loop_tree.nodes.end());
   P.chunked.insert(P.chunked.end(), P.loop.begin(), P.loop.end());
   P.chunk_pos.assign(P.n_nodes, -1);
   for (size_t i = 0; i < P.chunked.size(); ++i) P.chunk_pos[P.chunked[i]] = (int)i;
   build_chunks(P, n_chunks);
   int t = 0;
+  for (int v : P.pro_tree.nodes) P.nodes[v].time = t;  // one launch
+  ++t;
   for (int v : P.prologue) P.nodes[v].time = t++;
-  for (int v : P.chunked) P.nodes[v].time = t++;
+  for (int v : P.cpro) P.nodes[v].time = t++;
+  for (int v : P.loop_tree.nodes) P.nodes[v].time = t;
+  ++t;
+  for (int v : P.loop) P.nodes[v].time = t++;
   const int t_end = t + 1;
   // instance capacity of every node: the largest chunk
   std::vector<int64_t> cap_inst(P.n_nodes, 0);
@@ -636,6 +849,7 @@ void build_memory_for(Plan& P, int n_chunks) {
   }
 
   // static region
+  for (int v = 0; v < P.n_nodes; ++v) P.nodes[v].inst_elems = 1ull << P.nodes[v].idx.size();
   uint64_t off = 0;
   P.sigma_off = off;
   off += kAlign;
@@ -672,6 +886,14 @@ void build_memory_for(Plan& P, int n_chunks) {
     off += C.rootloc.size() * 4;
   }
   off = align_up(off);
+  for (Tree* T : {&P.pro_tree, &P.loop_tree}) {
+    T->off.clear();
+    if (T->roots.empty()) continue;
+    for (int c = 0; c < (T == &P.loop_tree ? P.n_chunks : 1); ++c) {
+      T->off.push_back(off);
+      off = align_up(off + tree_words(P, *T, c).size() * 4);
+    }
+  }
   // leaf variants: keys x 2^nsb instances
   for (int l = 0; l < nt; ++l) {
     PNode& L = P.nodes[l];
@@ -688,10 +910,11 @@ void build_memory_for(Plan& P, int n_chunks) {
       off = align_up(off + (uint64_t)L.keys.size() * (1ull << L.sl_bits.size()) * hs);
     }
     P.inv_scale_lo = off;
-    for (int v : P.prologue) {
-      P.nodes[v].scale_off = off;
-      off += (uint64_t)P.nodes[v].keys.size() * hs;
-    }
+    for (const std::vector<int>* list : {&P.pro_tree.nodes, &P.prologue})
+      for (int v : *list) {
+        P.nodes[v].scale_off = off;
+        off += (uint64_t)P.nodes[v].keys.size() * hs;
+      }
     off = align_up(off);
     P.inv_scale_hi = off;
     P.cpro_scale_lo = off;
@@ -702,22 +925,35 @@ void build_memory_for(Plan& P, int n_chunks) {
     off = align_up(off);
     P.cpro_scale_hi = off;
     P.dep_scale_lo = off;
-    for (int v : P.loop) {
-      P.nodes[v].scale_off = off;
-      off += (uint64_t)cap_inst[v] * P.batch * hs;
-    }
+    for (const std::vector<int>* list : {&P.loop_tree.nodes, &P.loop})
+      for (int v : *list) {
+        P.nodes[v].scale_off = off;
+        off += (uint64_t)cap_inst[v] * P.batch * hs;
+      }
     off = align_up(off);
     P.dep_scale_hi = off;
   }
   P.static_bytes = off;
+
+  // A slice that is one fused subtree: as many slices per launch as kTreeBatch
+  // and the root's instances allow (the caller's slice batch is sized for
+  // intermediates, which such slices keep in LDS).
+  P.tree_batch = 0;
+  if (P.loop.empty() && !P.loop_tree.roots.empty() && n_chunks == 1) {
+    const uint64_t bytes = (uint64_t)cap_inst[root] * 8 << P.nodes[root].idx.size();
+    const int64_t n = std::min<int64_t>((int64_t)1 << P.sliced.size(), kTreeBatch);
+    P.tree_batch = (int)std::max<int64_t>(P.batch, std::min<int64_t>(n, (int64_t)(kTreeBatchBytes / bytes)));
+  }
 
   // intermediates
   std::vector<ArenaBuf> bufs;
   for (int v = nt; v < P.n_nodes; ++v) {
     PNode& V = P.nodes[v];
     V.inst_elems = 1ull << V.idx.size();
-    const uint64_t ninst = (uint64_t)cap_inst[v] * (V.dep ? (uint64_t)P.batch : 1ull);
+    uint64_t ninst = (uint64_t)cap_inst[v] * (V.dep ? (uint64_t)P.batch : 1ull);
+    if (v == root && P.tree_batch > P.batch) ninst = (uint64_t)cap_inst[v] * (uint64_t)P.tree_batch;
     V.buf_bytes = align_up(ninst * V.inst_elems * eb_of(P, v));
+    if (V.in_lds) continue;
     const PNode& Par = P.nodes[v == root ? root : V.parent];
     int t1;
     if (v == root)
@@ -851,26 +1087,6 @@ void fill_leaf_data(Plan& P, int l, unsigned char* dst) {
   }
 }
 
-// how a node of chunk c reads child `child` (gmap_off: the gather map)
-OpDesc operand_desc(const Plan& P, int child, uint64_t gmap_off, int c) {
-  const PNode& C = P.nodes[child];
-  OpDesc o;
-  std::memset(&o, 0, sizeof(o));
-  o.off = C.off + (child >= P.net.n_tensors ? P.arena_delta : 0);
-  o.inst_bytes = C.inst_elems * eb_of(P, child);
-  o.half = C.half_store ? 1 : 0;
-  o.gmap_off = gmap_off;
-  o.scale_off = C.scale_off;
-  const int pos = P.chunk_pos.empty() ? -1 : P.chunk_pos[child];
-  o.w_child = pos >= 0 ? P.chunks[c].nodes[pos].w : (int32_t)C.keys.size();
-  const bool leaf = child < P.net.n_tensors;
-  o.dep = (!leaf && C.dep) ? 1 : 0;
-  o.nsb = leaf ? (int32_t)C.sl_bits.size() : 0;
-  o.nsv = 1 << o.nsb;
-  for (int t = 0; t < o.nsb; ++t) o.sbit[t] = (int8_t)C.sl_bits[t];
-  return o;
-}
-
 NodeDesc node_desc(const Plan& P, int v, int nb, int c = 0) {
   const PNode& V = P.nodes[v];
   NodeDesc d;
@@ -961,6 +1177,14 @@ void launch_node(const Plan& P, const PNode& V, const NodeDesc& d, hipStream_t s
 struct StepTimer {
   int v = -1;
   std::vector<hipEvent_t> ev;  // (begin, end) pairs, one per launch
+  void begin(hipStream_t st) {
+    for (int i = 0; i < 2; ++i) {
+      ev.push_back(nullptr);
+      hip_check(hipEventCreate(&ev.back()), "event create");
+    }
+    hip_check(hipEventRecord(ev[ev.size() - 2], st), "event record");
+  }
+  void end(hipStream_t st) { hip_check(hipEventRecord(ev.back(), st), "event record"); }
   ~StepTimer() {
     for (auto e : ev)
       if (e) (void)hipEventDestroy(e);
@@ -972,14 +1196,20 @@ void launch_node_timed(const Plan& P, int v, const NodeDesc& d, hipStream_t st, 
     launch_node(P, P.nodes[v], d, st);
     return;
   }
-  for (int i = 0; i < 2; ++i) {
-    t->ev.push_back(nullptr);
-    hip_check(hipEventCreate(&t->ev.back()), "event create");
-  }
-  const size_t n = t->ev.size();
-  hip_check(hipEventRecord(t->ev[n - 2], st), "event record");
+  t->begin(st);
   launch_node(P, P.nodes[v], d, st);
-  hip_check(hipEventRecord(t->ev[n - 1], st), "event record");
+  t->end(st);
+}
+
+// the fused subtrees of one list (nb slices of chunk c); timed if they hold the
+// timer's step
+void launch_fused(const Plan& P, const Tree& T, int c, int nb, hipStream_t st, StepTimer* t) {
+  if (T.roots.empty()) return;
+  const int64_t* sig = reinterpret_cast<const int64_t*>(P.ws + P.sigma_off);
+  const bool timed = t && std::binary_search(T.nodes.begin(), T.nodes.end(), t->v);
+  if (timed) t->begin(st);
+  hip_check(launch_tree(P.ws, T.off[T.off.size() > 1 ? c : 0], (int)T.roots.size(), nb, sig, 0, st), "fused steps");
+  if (timed) t->end(st);
 }
 
 void launch_batch(const Plan& P, int c, int nb, hipStream_t st, double* amps, StepTimer* t = nullptr) {
@@ -987,20 +1217,24 @@ void launch_batch(const Plan& P, int c, int nb, hipStream_t st, double* amps, St
   const int ob = (int)P.open_qubits.size();
   if (P.precision == MATNC_CHALF)
     hip_check(launch_zero(P.ws + P.dep_scale_lo, P.dep_scale_hi - P.dep_scale_lo, st), "clear scales");
+  launch_fused(P, P.loop_tree, c, nb, st, t);
   for (int v : P.loop) launch_node_timed(P, v, node_desc(P, v, nb, c), st, t);
   if (!amps) return;
   const Chunk& C = P.chunks[c];
   const OpDesc root = root_desc(P, c);
   const int64_t nrows = (int64_t)C.rows.size();
   const int32_t* rows = reinterpret_cast<const int32_t*>(P.ws + C.rows_off);
-  hipError_t er = P.precision == MATNC_C64 ? launch_slice_sum(root, P.ws, sig, nb, nrows, rows, ob, amps, st)
-                                           : launch_slice_sum_h(root, P.ws, sig, nb, nrows, rows, ob, amps, st);
+  // (an FP32 root's exponent is 0: no scale slot is read, which a fused slice's
+  // root does not have for every slice of its batch)
+  hipError_t er = !root.half ? launch_slice_sum(root, P.ws, sig, nb, nrows, rows, ob, amps, st)
+                             : launch_slice_sum_h(root, P.ws, sig, nb, nrows, rows, ob, amps, st);
   hip_check(er, "slice sum");
 }
 
 void launch_prologue(const Plan& P, hipStream_t st, StepTimer* t = nullptr) {
   if (P.precision == MATNC_CHALF)
     hip_check(launch_zero(P.ws + P.inv_scale_lo, P.inv_scale_hi - P.inv_scale_lo, st), "clear scales");
+  launch_fused(P, P.pro_tree, 0, 1, st, t);
   for (int v : P.prologue) launch_node_timed(P, v, node_desc(P, v, 1), st, t);
 }
 
@@ -1051,10 +1285,11 @@ void launch_pass(Plan& P, int64_t b, int64_t e, double* amps, hipStream_t st) {
   int64_t* sig = reinterpret_cast<int64_t*>(P.ws + P.sigma_off);
   hip_check(launch_set_i64(sig, 0, st), "set sigma");
   launch_prologue(P, st);
+  const int64_t batch = P.tree_batch ? P.tree_batch : P.batch;
   for (int c = 0; c < P.n_chunks; ++c) {
     launch_chunk_prologue(P, c, st);
-    for (int64_t s0 = b; s0 < e; s0 += P.batch) {
-      const int nb = (int)std::min<int64_t>(P.batch, e - s0);
+    for (int64_t s0 = b; s0 < e; s0 += batch) {
+      const int nb = (int)std::min<int64_t>(batch, e - s0);
       hip_check(launch_set_i64(sig, s0, st), "set sigma");
       launch_batch(P, c, nb, st, amps);
     }
@@ -1280,6 +1515,11 @@ void bind_plan(Plan& P, void* dev_workspace, size_t bytes, void* hip_stream, uin
     std::memcpy(P.staging.data() + C.rows_off, C.rows.data(), C.rows.size() * 4);
     std::memcpy(P.staging.data() + C.rootloc_off, C.rootloc.data(), C.rootloc.size() * 4);
   }
+  for (const Tree* T : {&P.pro_tree, &P.loop_tree})
+    for (size_t c = 0; c < T->off.size(); ++c) {
+      const std::vector<uint32_t> w = tree_words(P, *T, (int)c);
+      std::memcpy(P.staging.data() + T->off[c], w.data(), w.size() * 4);
+    }
   for (int l = 0; l < nt; ++l) fill_leaf_data(P, l, P.staging.data());
   hip_check(hipMemcpyAsync(dev_workspace, P.staging.data(), P.static_bytes, hipMemcpyHostToDevice, P.stream),
             "upload static region");
@@ -1438,6 +1678,7 @@ int matnc_plan_create_ex(matnc_network net, const int* pairs, int n_sliced, cons
     build_structure(P);
     build_reuse(P);
     build_steps(P);
+    mark_fused(P);
     build_memory(P);
     *out = guard.release();
   });
@@ -1461,7 +1702,7 @@ int matnc_plan_info(matnc_plan plan, matnc_plan_info_t* info) {
     I.max_rank = P.max_rank;
     I.n_nodes = P.net.n_tensors - 1;
     I.n_mfma_nodes = P.n_mfma;
-    I.n_launches_per_batch = ((int)P.loop.size() + 2) * P.n_chunks;
+    I.n_launches_per_batch = ((int)P.loop.size() + (P.loop_tree.roots.empty() ? 2 : 3)) * P.n_chunks;
     I.workspace_bytes = P.workspace_bytes;
     I.cache_bytes = P.cache_bytes;
     I.n_chunks = P.n_chunks;
@@ -1526,6 +1767,21 @@ int matnc_execute(matnc_plan plan, int64_t slice_begin, int64_t slice_end, doubl
       P.inv_valid = true;
     }
     if (slice_end == slice_begin) return;
+    if (P.tree_batch) {
+      // a launch for the slices and one for their sum: nothing to capture
+      const OpDesc root = root_desc(P, 0);
+      const Chunk& C = P.chunks[0];
+      const int64_t nrows = (int64_t)C.rows.size();
+      const int32_t* rows = reinterpret_cast<const int32_t*>(P.ws + C.rows_off);
+      const int ob = (int)P.open_qubits.size();
+      for (int64_t s0 = slice_begin; s0 < slice_end; s0 += P.tree_batch) {
+        const int nb = (int)std::min<int64_t>(P.tree_batch, slice_end - s0);
+        hip_check(launch_tree(P.ws, P.loop_tree.off[0], (int)P.loop_tree.roots.size(), nb, nullptr, s0, st),
+                  "fused slices");
+        hip_check(launch_slice_sum(root, P.ws, sig, nb, nrows, rows, ob, amps_dev, st), "slice sum");
+      }
+      return;
+    }
     // full batches replay graphs captured for this amplitude buffer
     const bool full = slice_end - slice_begin >= P.batch;
     if (full && st != nullptr && (P.graph_execs.empty() || P.graph_amps != amps_dev))
@@ -1631,7 +1887,7 @@ int matnc_plan_autotune(matnc_plan plan, int reps, const char* cache_path) {
     order.insert(order.end(), P.chunked.begin(), P.chunked.end());
     for (int v : order) {
       PNode& V = P.nodes[v];
-      if (V.kernel != 1) continue;
+      if (V.kernel != 1 || V.fused) continue;
       const std::string key = tune_key(P, V, node_desc(P, v, V.dep ? P.batch : 1).n_inst);
       auto it = cache.find(key);
       const bool half = V.half_store;  // FP16-product MFMA kernels
@@ -1714,7 +1970,8 @@ int matnc_plan_profile(matnc_plan plan, int64_t slice_begin, int nb, float* time
     const int steps = nt - 1;
     std::vector<int> order(P.prologue);
     order.insert(order.end(), P.chunked.begin(), P.chunked.end());
-    std::vector<hipEvent_t> ev(2 * order.size(), nullptr);
+    // a launch of each list's fused subtrees, then one per other node
+    std::vector<hipEvent_t> ev(2 * order.size() + 4, nullptr);
     struct EvGuard {
       std::vector<hipEvent_t>& e;
       ~EvGuard() {
@@ -1730,15 +1987,30 @@ int matnc_plan_profile(matnc_plan plan, int64_t slice_begin, int nb, float* time
     if (P.precision == MATNC_CHALF) {
       hip_check(launch_zero(P.ws + P.inv_scale_lo, P.dep_scale_hi - P.inv_scale_lo, st), "clear scales");
     }
+    const size_t e_fused = 2 * order.size();
+    auto fused = [&](const Tree& T, int n, size_t at) {
+      hip_check(hipEventRecord(ev[at], st), "event record");
+      launch_fused(P, T, 0, n, st, nullptr);
+      hip_check(hipEventRecord(ev[at + 1], st), "event record");
+    };
+    fused(P.pro_tree, 1, e_fused);
+    bool in_loop = false;
+    auto enter_loop = [&] {
+      hip_check(launch_set_i64(sig, slice_begin, st), "set sigma");
+      fused(P.loop_tree, nb, e_fused + 2);
+      in_loop = true;
+    };
     for (size_t i = 0; i < order.size(); ++i) {
       const int v = order[i];
       const PNode& V = P.nodes[v];
-      if (i == P.prologue.size() + P.cpro.size()) hip_check(launch_set_i64(sig, slice_begin, st), "set sigma");
+      if (V.dep && !in_loop) enter_loop();
+      if (V.dep && V.fused) continue;
       const NodeDesc d = node_desc(P, v, V.dep ? nb : 1);
       hip_check(hipEventRecord(ev[2 * i], st), "event record");
       launch_node(P, V, d, st);
       hip_check(hipEventRecord(ev[2 * i + 1], st), "event record");
     }
+    if (!in_loop) enter_loop();
     hip_check(hipStreamSynchronize(st), "profile sync");
     P.inv_valid = true;
     for (int j = 0; j < steps; ++j) {
@@ -1747,14 +2019,23 @@ int matnc_plan_profile(matnc_plan plan, int64_t slice_begin, int nb, float* time
       cmac[j] = 0;
       bytes[j] = 0;
     }
+    order.insert(order.end(), P.pro_tree.nodes.begin(), P.pro_tree.nodes.end());
     for (size_t i = 0; i < order.size(); ++i) {
       const int v = order[i];
       const PNode& V = P.nodes[v];
       const int j = v - nt;
+      const bool in_tree = V.fused && (V.dep || 2 * i >= e_fused);
       float ms = 0.f;
-      hip_check(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]), "event time");
+      if (in_tree) {
+        // an equal share of the launch that holds the step
+        const size_t at = e_fused + (V.dep ? 2 : 0);
+        hip_check(hipEventElapsedTime(&ms, ev[at], ev[at + 1]), "event time");
+        ms /= (float)(V.dep ? P.loop_tree : P.pro_tree).nodes.size();
+      } else {
+        hip_check(hipEventElapsedTime(&ms, ev[2 * i], ev[2 * i + 1]), "event time");
+      }
       time_ms[j] = ms;
-      kernel[j] = V.kernel == 1 ? (V.half_store ? 300 : 100) + (V.fan ? 100 : 0) + V.cfg : 0;
+      kernel[j] = V.kernel == 1 && !in_tree ? (V.half_store ? 300 : 100) + (V.fan ? 100 : 0) + V.cfg : 0;
       const NodeDesc d = node_desc(P, v, V.dep ? nb : 1);
       const double inst = (double)d.n_inst;
       cmac[j] = inst * std::ldexp(1.0, (int)(V.M.size() + V.N.size() + V.K.size()));

@@ -68,6 +68,8 @@ struct PNode {
   uint64_t off = 0;              // byte offset in workspace
   uint64_t tab_off = 0, ga_off = 0, gb_off = 0;
   int time = 0;                  // schedule position
+  bool fused = false;            // contracted inside a fused subtree (see Plan::tree)
+  bool in_lds = false;           // ... and not its root: the tensor never leaves LDS
   uint64_t scale_off = 0;        // complex-half: byte offset of the HalfScale array
 };
 
@@ -102,6 +104,14 @@ struct ArenaShare {
   uint64_t owner = 0;
 };
 
+// The fused subtrees of one schedule list: their steps (ascending ids) and
+// the description's place in the static region, per chunk for the slice loop.
+struct Tree {
+  std::vector<int> nodes;
+  std::vector<int> roots;
+  std::vector<uint64_t> off;
+};
+
 struct Plan {
   Network net;
   int n_nodes = 0;               // n_tensors + steps
@@ -130,8 +140,11 @@ struct Plan {
   uint64_t cache_bytes = 0;
   uint64_t part_off = 0;         // parts of split sums (behind the arena)
   // node ids in schedule order: computed once per cache fill (prologue),
-  // once per chunk (cpro), per slice batch and chunk (loop); chunked =
-  // cpro followed by loop
+  // once per chunk (cpro), per slice batch and chunk (loop).  The fused
+  // subtrees of prologue and loop run first, in one launch each (pro_tree,
+  // loop_tree); chunked = cpro, loop_tree's nodes, loop
+  Tree pro_tree, loop_tree;
+  int tree_batch = 0;  // slices per launch if a slice is one fused subtree, else 0
   std::vector<int> prologue, cpro, loop, chunked;
   // costs
   double cmac_single = 0, cmac_multi = 0, cmac_inv = 0, cmac_total = 0;

@@ -11,7 +11,7 @@ for the operands' own products).
 import numpy as np
 import pytest
 
-from gpu_util import bit_positions_to_index, rel_err, require_gpu, say
+from gpu_util import assert_close, bit_positions_to_index, rel_err, require_gpu, say
 from test_gpu_contract import make_case, reference, run
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +137,53 @@ def test_split_sums_with_and_without_room(precision):
         assert np.array_equal(a, full)
     a, less, chunks = contract(need - 1)  # not even one key's parts fit: the sum in one piece
     assert less < need and not np.array_equal(a, full)
+
+
+@pytest.mark.parametrize("precision,opens,cap,batch", [("c64", (), 4, 3), ("c64", (2, 9), 6, 2), ("chalf", (), 5, 4)])
+def test_fused_slices(precision, opens, cap, batch):
+    """Small circuits whose slices are fused subtrees, whole or in part: more slices than one launch takes, ranges that cut
+    it anywhere, the one-by-one pass and the queue give the same bits; against the state vector."""
+    torch = require_gpu()
+    from oracle import statevector
+    from paper_2212_04749_amd import api, planner
+    from paper_2212_04749_amd.circuit_tn import build_network
+    from workload import GridSpec, random_circuit, uniform_bitstrings
+    circ = random_circuit(GridSpec(3, 4), 8, 51)
+    words = uniform_bitstrings(12, 37, 52)
+    net = build_network(circ)
+    pl = planner.find_plan(net, words, opens, cap, trials=4, refine_top=0)
+    spec = api.PlanSpec(pl.pairs, pl.sliced, opens, cap)
+    run = api.Contraction(net, spec, words, precision=precision, slice_batch=batch)
+    n = run.n_slices
+    say(f"fused slices {precision}: {n} slices, {run.info.n_launches_per_batch} launches per batch")
+    if not opens:  # one subtree per slice (with open legs the last steps are launches of their own)
+        assert run.info.n_launches_per_batch == 3
+    if not opens and precision == "c64":
+        assert n > 1024
+    full = run.execute()
+    run.synchronize()
+    full = full.cpu().numpy()
+    parts = run.new_amplitudes()
+    for lo, hi in ((0, 1), (1, n // 3), (n // 3, n // 3), (n // 3, n - 1), (n - 1, n)):
+        run.execute(parts, lo, hi)
+    run.synchronize()
+    assert np.array_equal(full, parts.cpu().numpy())
+    timed = run.new_amplitudes()
+    run.execute_timed(timed, len(net.tensors) - 2)
+    assert np.array_equal(full, timed.cpu().numpy())
+    queue = api.Queue([run])
+    for _ in range(2):
+        amps, _ = queue.execute()
+        torch.cuda.synchronize()
+        assert np.array_equal(full, amps[0].cpu().numpy())
+    queue.close()
+    psi = statevector.final_state(circ)
+    rows = []
+    for w0 in words:
+        for j in range(1 << len(opens)):
+            word = int(w0)
+            for t, q in enumerate(opens):
+                word = (word & ~(1 << q)) | (((j >> t) & 1) << q)
+            rows.append(word)
+    assert_close(full[..., 0] + 1j * full[..., 1], statevector.amplitudes_from_state(psi, rows), 1e-5)
+    run.close()
