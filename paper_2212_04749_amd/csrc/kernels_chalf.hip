@@ -48,19 +48,31 @@ __device__ __forceinline__ uint32_t f32pair_to_h2bits(u32x2 raw, float c) {
 }
 
 // an operand's staged elements: one half2 word (FP16 storage) or two FP32
-// words
+// words; load2: two neighbouring elements at once
 template <bool H>
 struct AStage;
 template <>
 struct AStage<true> {
   typedef uint32_t type;
-  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return ldg_u32(base, i); }
+  static constexpr int kBytes = 4;
+  static __device__ __forceinline__ type load(uint64_t a) { return gmem<const uint32_t>(a)[0]; }
+  static __device__ __forceinline__ void load2(uint64_t base, uint32_t off, type (&r)[2]) {
+    const u32x2 v = *(gptr<const u32x2>)((gptr<const char>)base + off);
+    r[0] = v.x;
+    r[1] = v.y;
+  }
   static __device__ __forceinline__ uint32_t bits(type r, float) { return r; }
 };
 template <>
 struct AStage<false> {
   typedef u32x2 type;
-  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return gmem<const u32x2>(base)[i]; }
+  static constexpr int kBytes = 8;
+  static __device__ __forceinline__ type load(uint64_t a) { return gmem<const u32x2>(a)[0]; }
+  static __device__ __forceinline__ void load2(uint64_t base, uint32_t off, type (&r)[2]) {
+    const u32x4 v = *(gptr<const u32x4>)((gptr<const char>)base + off);
+    r[0] = u32x2{v.x, v.y};
+    r[1] = u32x2{v.z, v.w};
+  }
   static __device__ __forceinline__ uint32_t bits(type r, float c) { return f32pair_to_h2bits(r, c); }
 };
 
@@ -73,21 +85,25 @@ struct AStage<false> {
 // Per-column data (C column offsets; for fan tiles each slot's output base,
 // factors and exponent) is kept in LDS, shared by the waves, rather than in
 // per-lane registers.
-// Operand staging works on quads: a thread loads four consecutive k of one m
-// (of A) or of one n (of B) and writes them to LDS as one 16-byte store.
+// Operands lie with the contracted bits highest (A[m + (k << mbits)], B likewise;
+// the launcher checks), so addresses are sums and no table is read in the
+// loops: a thread loads four consecutive k of two neighbouring m of A (8 or 16
+// bytes each) or of one n of B, and writes each m's or n's four k to LDS as one
+// 16-byte store.
 template <int RM, int RN, int WM, int WN, int TK, bool FAN, bool HA, bool HB>
 __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = 32 * RM * WM;
   constexpr int TN = 16 * RN * WN;
   static_assert(TK % 8 == 0, "eight complex k per instruction");
-  constexpr int QA = (TK / 4) * TM;  // k quads of the A tile
-  constexpr int QB = (TK / 4) * TN;  // ... and of the B tile
-  static_assert(QA % NT == 0, "A quads must split evenly over threads");
-  static_assert(QB % NT == 0 || NT % QB == 0, "B quads must split evenly over threads, or fit in fewer");
-  constexpr int EQA = QA / NT;
+  constexpr int QA = (TK / 4) * (TM / 2);  // blocks of four k of two m of the A tile
+  constexpr int QB = (TK / 4) * TN;        // blocks of four k of the B tile
+  static_assert(QA % NT == 0 || NT % QA == 0, "A blocks must split evenly over threads, or fit in fewer");
+  static_assert(QB % NT == 0 || NT % QB == 0, "B blocks must split evenly over threads, or fit in fewer");
+  constexpr int EQA = QA >= NT ? QA / NT : 1;
   constexpr int EQB = QB >= NT ? QB / NT : 1;
-  constexpr bool BPART = QB < NT;  // only threads tid < QB stage B
+  // a wave's A blocks share their k (its row bases are then scalars)
+  constexpr bool AUNI = (TM / 2) % 64 == 0;
   // LDS tiles in the register layout of the MFMA operands: As[k/4][m][k%4]
   // holds A's half2 (re, im); Bs[k/4][n][d][k%4] holds B's column pair of
   // the real embedding, (re, -im) for d = 0 and (im, re) for d = 1
@@ -103,9 +119,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
   __shared__ int s_e[FAN ? TN : 1];
   __shared__ float s_fb[FAN ? TN : 1];
   __shared__ uint32_t s_mx[FAN ? TN : 1];
+  // output offsets of a tile's first row and column: [CM, CN][nibble][value]
+  __shared__ uint32_t s_nib[2][8][16];
 
-  const gptr<const uint32_t> tab = gmem<const uint32_t>(ws + d.tab_off);
-  const cptr<const uint32_t> ctab = cmem<const uint32_t>(ws + d.tab_off);  // k-step lookups
   const gptr<const int32_t> glA = gmem<const int32_t>(ws + d.A.gmap_off);
   const gptr<const int32_t> glB = gmem<const int32_t>(ws + d.B.gmap_off);
   const int tid = threadIdx.x;
@@ -127,7 +143,43 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
   const uint32_t nmask = (1u << d.nbits) - 1u;
   const int slots = FAN ? (TN >> d.nbits) : 1;
   const uint64_t scB = ws + d.B.scale_off;
-  const bool bstage = !BPART || tid < QB;
+  const bool astage = QA >= NT || tid < QA;
+  const bool bstage = QB >= NT || tid < QB;
+
+  // offsets inside a tile, the same for all tiles of this persistent workgroup
+  if (lane < 16) {
+    if (wave == 0) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s_nib[0][q][lane] = dep_nibble<TAB_CM>(d, q, lane);
+    } else if (wave == 1) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s_nib[1][q][lane] = dep_nibble<TAB_CN>(d, q, lane);
+    }
+  }
+  if (tid < TN) s_cn[tid] = dep<TAB_CN>(d, 8, FAN ? (tid & nmask) : tid);
+  uint32_t om[RM];  // output offsets of this lane's m values
+#pragma unroll
+  for (int i = 0; i < RM; ++i) om[i] = dep<TAB_CM>(d, 8, (wm * RM + i) * 32 + l32);
+  const bool m0_lowest = (d.pos[TAB_CM][0] & 31) == 0;
+  // A block e covers m = amm[e], amm[e] + 1 and k = 4 akq[e] .. 4 akq[e] + 3 of
+  // the k step; B block e n = bnn[e] and likewise k
+  int akq[EQA], amm[EQA], bkq[EQB], bnn[EQB];
+#pragma unroll
+  for (int e = 0; e < EQA; ++e) {
+    const int flat = astage ? e * NT + tid : 0;
+    amm[e] = 2 * (flat % (TM / 2));
+    akq[e] = flat / (TM / 2);
+    if (AUNI) akq[e] = __builtin_amdgcn_readfirstlane(akq[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < EQB; ++e) {
+    const int flat = bstage ? e * NT + tid : 0;
+    bnn[e] = flat % TN;
+    bkq[e] = flat / TN;
+  }
+  const uint64_t a_k = (uint64_t)AStage<HA>::kBytes << d.mbits;  // bytes from one k to the next
+  const uint64_t b_k = (uint64_t)AStage<HB>::kBytes << d.nbits;
+  __syncthreads();
 
   for (uint32_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
     // logical tile order: n tiles innermost (they share the A tile), then m
@@ -152,9 +204,14 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
     const int64_t sigma = sigma0 + s;
     const int64_t ai = operand_instance(d.A, glA, j, s, sigma);
     const int64_t bi = operand_instance(d.B, glB, j, s, sigma);
-    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes;
-    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes;
-    const uint64_t pc = ws + d.c_off + inst * d.c_inst_bytes;
+    // output offset of (m0, n0): lane 8c + q looks up nibble q of class c
+    uint32_t first = s_nib[(lane >> 3) & 1][lane & 7][((lane & 8 ? n0 : m0) >> (4 * (lane & 7))) & 15u];
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) first |= __shfl_xor(first, o);
+    const uint64_t oc0 = (uint64_t)__builtin_amdgcn_readlane(first, 0) + (uint64_t)__builtin_amdgcn_readlane(first, 8);
+    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes + (uint64_t)m0 * AStage<HA>::kBytes;
+    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes + (uint64_t)n0 * AStage<HB>::kBytes;
+    const uint64_t pc = ws + d.c_off + inst * d.c_inst_bytes + oc0 * 4;
     // operand scales; an FP32 operand is converted on load with a power of two
     // that puts its largest component in [2^13, 2^14)
     const HalfScale sa = ldg_scale(ws + d.A.scale_off, ai);
@@ -176,7 +233,6 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
       cb = ldexpf(1.f, -eb);
       mxb *= cb;
     }
-    if (tid < TN) s_cn[tid] = tlook(tab + TAB_CN * kTabSize, FAN ? (tid & nmask) : n0 + tid);
     if (FAN) {
       // per-slot scales: B's exponent and load factor, the output exponent
       if (tid < slots) {
@@ -200,50 +256,33 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
           f = ldexpf(1.f, 15 - ex);
           e = ea + ebg + ex - 15;
         }
-        s_cbase[tid] = jg < 0 ? 0 : d.c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes;
+        s_cbase[tid] = jg < 0 ? 0 : d.c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes + oc0 * 4;
         s_f[tid] = f;
         s_e[tid] = e;
         s_fb[tid] = cbg;
         s_mx[tid] = 0u;
       }
     }
-    __syncthreads();  // the column data above is read by every wave
+    if (FAN) __syncthreads();  // the slot data above is read by every wave
 
-    // quad coordinates: A quad e of this thread covers m = amm[e], k =
-    // 4 akq[e] .. 4 akq[e] + 3 of the k step; likewise B quads over n
-    uint32_t aoff[EQA][4], boff[EQB][4];
-    int akq[EQA], amm[EQA], bkq[EQB], bnn[EQB];
-#pragma unroll
-    for (int e = 0; e < EQA; ++e) {
-      const int flat = e * NT + tid;
-      amm[e] = flat % TM;
-      akq[e] = flat / TM;
-      const uint32_t om_ = tlook(tab + TAB_AM * kTabSize, m0 + amm[e]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) aoff[e][q] = om_ + tab[TAB_AK * kTabSize + 4 * akq[e] + q];
-    }
-    uint64_t pbe[EQB];  // B instance of each quad (fan tiles: its slot's)
+    uint64_t pak[EQA], pbk[EQB];  // first k row of each block of the k step being loaded
     float cbe[EQB];
 #pragma unroll
+    for (int e = 0; e < EQA; ++e) pak[e] = pa + (uint64_t)(4 * akq[e]) * a_k;
+#pragma unroll
     for (int e = 0; e < EQB; ++e) {
-      const int flat = bstage ? e * NT + tid : 0;
-      bnn[e] = flat % TN;
-      bkq[e] = flat / TN;
-      uint32_t on_;
       if (FAN) {
         const int g = bnn[e] >> d.nbits;
         const int jg = fj[g];
         // an empty slot reads slot 0's B into columns that are never stored
-        pbe[e] = ws + d.B.off + operand_instance(d.B, glB, jg < 0 ? j : jg, s, sigma) * d.B.inst_bytes;
+        pbk[e] = ws + d.B.off + operand_instance(d.B, glB, jg < 0 ? j : jg, s, sigma) * d.B.inst_bytes +
+                 (uint64_t)(bnn[e] & nmask) * AStage<HB>::kBytes;
         cbe[e] = s_fb[g];
-        on_ = tlook(tab + TAB_BN * kTabSize, bnn[e] & nmask);
       } else {
-        pbe[e] = pb;
+        pbk[e] = pb + (uint64_t)bnn[e] * AStage<HB>::kBytes;
         cbe[e] = cb;
-        on_ = tlook(tab + TAB_BN * kTabSize, n0 + bnn[e]);
       }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) boff[e][q] = on_ + tab[TAB_BK * kTabSize + 4 * bkq[e] + q];
+      pbk[e] += (uint64_t)(4 * bkq[e]) * b_k;
     }
     // raw operand words in flight (an FP32 element, or a half2 in .x); the
     // FP32 -> FP16 conversion happens when the tile is written to LDS, after
@@ -253,31 +292,39 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
     // steps of MFMA work cover their latency.  Two only for the 8-wave tiles
     // whose second stage still fits two waves per SIMD (FP16 operands); the
     // 4-wave tiles would lose half their occupancy to it.
-    constexpr int SW = EQA * 4 * (HA ? 1 : 2) + EQB * 4 * (HB ? 1 : 2);  // words per stage
-    constexpr int S = (NT == 512 && SW <= 12) ? 2 : 1;
-    typename AStage<HA>::type ra[S][EQA][4];
+    constexpr int SW = EQA * 8 * (HA ? 1 : 2) + EQB * 4 * (HB ? 1 : 2);  // words per stage
+    constexpr int S = (NT == 512 && SW <= 16) ? 2 : 1;
+    typename AStage<HA>::type ra[S][EQA][4][2];
     typename AStage<HB>::type rb[S][EQB][4];
-    auto gload = [&](int st, uint32_t kba, uint32_t kbb) {
+    // loads the next k step into stage st
+    auto gload = [&](int st) {
+      if (astage) {
 #pragma unroll
-      for (int e = 0; e < EQA; ++e)
+        for (int e = 0; e < EQA; ++e)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ra[st][e][q] = AStage<HA>::load(pa, aoff[e][q] + kba);
+          for (int q = 0; q < 4; ++q)
+            AStage<HA>::load2(pak[e] + q * a_k, (uint32_t)amm[e] * AStage<HA>::kBytes, ra[st][e][q]);
+      }
       if (bstage) {
 #pragma unroll
         for (int e = 0; e < EQB; ++e)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) rb[st][e][q] = AStage<HB>::load(pbe[e], boff[e][q] + kbb);
+          for (int q = 0; q < 4; ++q) rb[st][e][q] = AStage<HB>::load(pbk[e] + q * b_k);
       }
+#pragma unroll
+      for (int e = 0; e < EQA; ++e) pak[e] += TK * a_k;
+#pragma unroll
+      for (int e = 0; e < EQB; ++e) pbk[e] += TK * b_k;
     };
     auto lstore = [&](int buf, int st) {
+      if (astage) {
 #pragma unroll
-      for (int e = 0; e < EQA; ++e) {
-        uint4 v;
-        v.x = AStage<HA>::bits(ra[st][e][0], ca);
-        v.y = AStage<HA>::bits(ra[st][e][1], ca);
-        v.z = AStage<HA>::bits(ra[st][e][2], ca);
-        v.w = AStage<HA>::bits(ra[st][e][3], ca);
-        *reinterpret_cast<uint4*>(&As[buf][akq[e] * AQ + 4 * amm[e]]) = v;
+        for (int e = 0; e < EQA; ++e)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            *reinterpret_cast<uint4*>(&As[buf][akq[e] * AQ + 4 * (amm[e] + i)]) =
+                make_uint4(AStage<HA>::bits(ra[st][e][0][i], ca), AStage<HA>::bits(ra[st][e][1][i], ca),
+                           AStage<HA>::bits(ra[st][e][2][i], ca), AStage<HA>::bits(ra[st][e][3][i], ca));
       }
       if (bstage) {
 #pragma unroll
@@ -328,44 +375,34 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
       }
     };
 
-    // output offsets of this lane's m values, fetched before the k loop
-    uint32_t om[RM];
-#pragma unroll
-    for (int i = 0; i < RM; ++i) om[i] = tlook(tab + TAB_CM * kTabSize, m0 + (wm * RM + i) * 32 + l32);
-
-    // stages 0 .. S-1 hold k steps 0 .. S-1; kna, knb: k offsets of the next
-    // step to load (S), fetched one load ahead of their use
-    gload(0, tlook(ctab + TAB_AK * kTabSize, 0u), tlook(ctab + TAB_BK * kTabSize, 0u));
+    // stages 0 .. S-1 hold k steps 0 .. S-1
+    gload(0);
 #pragma unroll
     for (int u = 1; u < S; ++u)
-      if (u < ksteps)
-        gload(u, tlook(ctab + TAB_AK * kTabSize, (uint32_t)(u * TK)),
-              tlook(ctab + TAB_BK * kTabSize, (uint32_t)(u * TK)));
-    uint32_t kna = 0, knb = 0;
-    if (S < ksteps) {
-      kna = tlook(ctab + TAB_AK * kTabSize, (uint32_t)(S * TK));
-      knb = tlook(ctab + TAB_BK * kTabSize, (uint32_t)(S * TK));
-    }
+      if (u < ksteps) gload(u);
     lstore(0, 0);
     __syncthreads();
-    for (int ks = 0; ks < ksteps; ks += S) {
+    // Stage u held step k and was written to LDS at the end of step k - 1: it
+    // now takes step k + S.  The last S steps, which load nothing, have a copy of
+    // their own: a load under a condition makes the compiler wait for every
+    // outstanding one before the LDS store, the second stage's too.
+    int ks = 0;
+    for (; ks + S < ksteps; ks += S) {
 #pragma unroll
       for (int u = 0; u < S; ++u) {
-        const int k = ks + u;
-        if (k < ksteps) {
-          // stage u held step k and was written to LDS at the end of step
-          // k - 1: it now takes step k + S
-          if (k + S < ksteps) {
-            gload(u, kna, knb);
-            if (k + S + 1 < ksteps) {
-              kna = tlook(ctab + TAB_AK * kTabSize, (uint32_t)(k + S + 1) * TK);
-              knb = tlook(ctab + TAB_BK * kTabSize, (uint32_t)(k + S + 1) * TK);
-            }
-          }
-          kstep(k & 1);
-          if (k + 1 < ksteps) lstore((k + 1) & 1, (u + 1) % S);
-          __syncthreads();
-        }
+        gload(u);
+        kstep((ks + u) & 1);
+        lstore((ks + u + 1) & 1, (u + 1) % S);
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int k = ks + u;
+      if (k < ksteps) {
+        kstep(k & 1);
+        if (k + 1 < ksteps) lstore((k + 1) & 1, (u + 1) % S);
+        __syncthreads();
       }
     }
 
@@ -429,7 +466,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
           }
         }
       }
-    } else if (!FAN && s_cn[1] - s_cn[0] == 2u && tlook(tab + TAB_CM * kTabSize, 1u) == 1u) {
+    } else if (!FAN && s_cn[1] - s_cn[0] == 2u && m0_lowest) {
       // m bit 0 lowest, n bit 0 next: lanes 2j and 2j + 1 (m bit 0 = 0, 1)
       // exchange column pairs (DPP) so that each holds the 2 x 2 block of one
       // pair -- four consecutive words, one 16-byte store -- the even lane
@@ -521,7 +558,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_mfma_h(NodeDesc d, uint64_t ws
         if (mx > 0.f) max_scale_mx(ws + d.c_scale_off, inst, __float_as_uint(mx));
       }
     }
-    __syncthreads();  // the column and slot arrays are rewritten by the next tile
+    if (FAN) __syncthreads();  // the slot arrays are rewritten by the next tile
   }
 }
 
@@ -649,7 +686,7 @@ static hipError_t launch_mfma_h_t(const NodeDesc& d, int cfg, uint64_t ws, const
   if (d.n_inst == 0) return hipSuccess;
   const bool fits = FAN ? mfma_h_fan_config_fits(cfg, d.mbits, d.nbits, d.kbits, d.fan_tn)
                         : mfma_h_config_fits(cfg, d.mbits, d.nbits, d.kbits);
-  if (!fits || (FAN && (d.w <= 0 || d.n_fan <= 0))) return hipErrorInvalidValue;
+  if (!fits || (FAN && (d.w <= 0 || d.n_fan <= 0)) || !d.linear) return hipErrorInvalidValue;
   const MfmaCfgH& c = kMfmaCfgsH[cfg];
   const int64_t units = FAN ? (d.n_inst / d.w) * d.n_fan : d.n_inst;
   const int64_t tiles = ((int64_t)1 << (d.mbits - c.tm_bits)) * (FAN ? 1 : ((int64_t)1 << (d.nbits - c.tn_bits)));

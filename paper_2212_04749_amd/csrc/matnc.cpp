@@ -203,7 +203,7 @@ void build_structure(Plan& P) {
   // first, in ascending qubit order
   auto key_of = [&](int i) {
     auto oq = out_qubit.find(i);
-    if (oq != out_qubit.end()) return std::make_pair(-1LL, (long long)oq->second);
+    if (oq != out_qubit.end()) return std::make_pair(-2LL * INT_MAX, (long long)oq->second);
     auto d = death.find(i);
     const long long dt = d == death.end() ? (long long)INT_MAX : (long long)d->second;
     return std::make_pair(-dt, (long long)i);
@@ -500,6 +500,13 @@ void build_steps(Plan& P) {
     fill(TAB_CN, V.N, V.idx);
     fill(TAB_AK, V.K, A);
     fill(TAB_BK, V.K, B);
+    // the storage order (latest death lowest) puts them there
+    V.linear = true;
+    const int mb = (int)V.M.size(), nb = (int)V.N.size(), kb = (int)V.K.size();
+    for (int t = 0; t < mb; ++t) V.linear = V.linear && V.pos[TAB_AM][t] == t;
+    for (int t = 0; t < nb; ++t) V.linear = V.linear && V.pos[TAB_BN][t] == t;
+    for (int t = 0; t < kb; ++t) V.linear = V.linear && V.pos[TAB_AK][t] == mb + t && V.pos[TAB_BK][t] == nb + t;
+    if (!V.linear) fail(MATNC_E_INVALID, "internal: storage order of step " + std::to_string(v - nt));
   }
   // FP32 tensors whose maximum an FP16 consumer needs for its exponent (and
   // for the scaling of its FP16 products)
@@ -530,12 +537,8 @@ void mark_fused(Plan& P) {
     // another order here; it is fused only where it always is: not where key
     // chunks may move it out of the prologue, nor where that order must stay.
     if ((V.kernel == 1 || kb > 4) && (!P.split || !(V.dep || w == 1))) continue;
-    // operands lie (k highest, m or n in order) by construction
+    if (!V.linear) continue;
     bool ok = true;
-    for (int t = 0; t < mb; ++t) ok = ok && V.pos[TAB_AM][t] == t;
-    for (int t = 0; t < nb; ++t) ok = ok && V.pos[TAB_BN][t] == t;
-    for (int t = 0; t < kb; ++t) ok = ok && V.pos[TAB_AK][t] == mb + t && V.pos[TAB_BK][t] == nb + t;
-    if (!ok) continue;
     uint64_t h = elems(v), wd = sizeof(TreeStep) / 4 + w + (((w << (mb + nb)) + 63) / 64) + 1;
     for (int c : {V.a, V.b}) {
       const PNode& C = P.nodes[c];
@@ -1112,6 +1115,7 @@ NodeDesc node_desc(const Plan& P, int v, int nb, int c = 0) {
   std::memcpy(d.pos, V.pos, sizeof(d.pos));
   d.keep_order = P.split ? 0 : 1;
   d.n_ref = (int64_t)V.keys.size();
+  d.linear = V.linear ? 1 : 0;
   d.part_off = P.part_off + P.arena_delta;
   d.ksplit = V.ksplit;
   if (V.fan) {

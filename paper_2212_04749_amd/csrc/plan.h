@@ -60,6 +60,7 @@ struct PNode {
   int32_t fan_rows[2] = {2, 2};  // tile-order blocks of the two tables (NodeDesc::fan_rows)
   int32_t unit_rows = 1;         // ... of the output instances of a plain MFMA step
   std::vector<int> M, N, K;      // virtual orders of the three index classes
+  bool linear = false;           // operands lie with the contracted bits highest, all classes in order
   int ksplit = 0;                // MFMA step: log2 of the parts of its sum
   int8_t pos[TAB_COUNT][32] = {};  // storage bit of each coordinate bit, per table class
   // memory
