@@ -44,6 +44,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));  // MFMA accumulato
 // element accessors (HIP's float2 / __half2 classes cannot be copied
 // through an address-space-qualified reference; plain vectors can)
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float2 ldg_f2(uint64_t base, uint64_t i) {
@@ -182,12 +183,23 @@ template <>
 struct FStage<false> {
   typedef f32x2 type;
   static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return gmem<const f32x2>(base)[i]; }
+  // elements i (even) and i + 1
+  static __device__ __forceinline__ void load2(uint64_t base, uint32_t i, type (&r)[2]) {
+    const f32x4 v = *(gptr<const f32x4>)((gptr<const char>)base + 8 * i);
+    r[0] = f32x2{v.x, v.y};
+    r[1] = f32x2{v.z, v.w};
+  }
   static __device__ __forceinline__ float2 val(type r, float) { return make_float2(r.x, r.y); }
 };
 template <>
 struct FStage<true> {
   typedef uint32_t type;
   static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return ldg_u32(base, i); }
+  static __device__ __forceinline__ void load2(uint64_t base, uint32_t i, type (&r)[2]) {
+    const u32x2 v = *(gptr<const u32x2>)((gptr<const char>)base + 4 * i);
+    r[0] = v.x;
+    r[1] = v.y;
+  }
   static __device__ __forceinline__ float2 val(type r, float c) {
     __half2 h;
     __builtin_memcpy(&h, &r, 4);

@@ -75,14 +75,22 @@ __device__ __forceinline__ Split3 split3(float2 v) {
 // slot column, one global atomic per slot and tile.
 // HA, HB (complex-half plans only): A, B stored in FP16 with a per-instance
 // exponent; the output is FP32 either way.
-template <int RM, int RN, int WM, int WN, bool FAN, bool REC = false, bool HA = false, bool HB = false>
+// LIN (every plan step): A[m + (k << mbits)], B[n + (k << nbits)] -- a thread
+// loads two neighbouring m at once and every k row's address is a scalar step
+// from the last; otherwise (a caller's own layout) an offset per element.
+template <int RM, int RN, int WM, int WN, bool FAN, bool LIN, bool REC = false, bool HA = false, bool HB = false>
 __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   static_assert(!REC || FAN, "maxima are recorded by fan-out tiles only");
+  static_assert(LIN || !FAN, "fan-out tiles are a plan's");
   constexpr int TK = 8;
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = 32 * RM * WM;
   constexpr int TN = 16 * RN * WN;
-  constexpr int QA = (TK / 4) * TM;  // quads of four consecutive k of the A tile
+  // m per block of A: two where every thread then still has a block, or where
+  // registers are short (128 x 128); with half of the threads idle the smaller
+  // tiles lose 10-15% to it
+  constexpr int MA = LIN && (TM == 256 || TN == 128) ? 2 : 1;
+  constexpr int QA = (TK / 4) * TM / MA;  // blocks of four consecutive k of the A tile
   constexpr int QB = (TK / 4) * TN;  // ... and of the B tile
   static_assert(QA % NT == 0 || NT % QA == 0, "A quads must split evenly over threads, or fit in fewer");
   static_assert(QB % NT == 0 || NT % QB == 0, "B quads must split evenly over threads, or fit in fewer");
@@ -157,28 +165,36 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   const bool astage = QA >= NT || tid < QA;
   const bool bstage = QB >= NT || tid < QB;
 
-  // A quad e of this thread covers m = amm[e], k = 4 akq[e] .. 4 akq[e] + 3 of
-  // the tile; likewise B quads over n
-  uint32_t aoff[EQA][4], boff[EQB][4];
+  // A block e of this thread covers m = amm[e] .. amm[e] + MA - 1, k = 4 akq[e]
+  // .. 4 akq[e] + 3 of the tile; likewise B blocks over n
+  uint32_t aoff[LIN ? 1 : EQA][4], boff[LIN ? 1 : EQB][4];
   int akq[EQA], bkq[EQB], amm[EQA], bnn[EQB];
 #pragma unroll
   for (int e = 0; e < EQA; ++e) {
     const int flat = astage ? e * NT + tid : 0;
-    amm[e] = flat % TM;
-    akq[e] = flat / TM;
-    const uint32_t om_ = dep<TAB_AM>(d, 8, amm[e]);
+    amm[e] = MA * (flat % (TM / MA));
+    akq[e] = flat / (TM / MA);
+    if constexpr (LIN) {
+      if ((TM / MA) % 64 == 0) akq[e] = __builtin_amdgcn_readfirstlane(akq[e]);
+    } else {
+      const uint32_t om_ = dep<TAB_AM>(d, 8, amm[e]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) aoff[e][q] = om_ + dep<TAB_AK>(d, 4, 4 * akq[e] + q);
+      for (int q = 0; q < 4; ++q) aoff[e][q] = om_ + dep<TAB_AK>(d, 4, 4 * akq[e] + q);
+    }
   }
 #pragma unroll
   for (int e = 0; e < EQB; ++e) {
     const int flat = bstage ? e * NT + tid : 0;
     bnn[e] = flat % TN;
     bkq[e] = flat / TN;
-    const uint32_t on_ = dep<TAB_BN>(d, 8, FAN ? bnn[e] & nmask : bnn[e]);
+    if constexpr (!LIN) {
+      const uint32_t on_ = dep<TAB_BN>(d, 8, bnn[e]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) boff[e][q] = on_ + dep<TAB_BK>(d, 4, 4 * bkq[e] + q);
+      for (int q = 0; q < 4; ++q) boff[e][q] = on_ + dep<TAB_BK>(d, 4, 4 * bkq[e] + q);
+    }
   }
+  const uint64_t a_k = (uint64_t)(HA ? 4 : 8) << d.mbits;  // LIN: bytes from one k to the next
+  const uint64_t b_k = (uint64_t)(HB ? 4 : 8) << d.nbits;
   uint32_t om[RM];  // output offsets of this lane's m values
 #pragma unroll
   for (int i = 0; i < RM; ++i) om[i] = dep<TAB_CM>(d, 8, (wm * RM + i) * 32 + l32);
@@ -236,40 +252,82 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
     }
     if (FAN) __syncthreads();  // the column data above is read by every wave
 
-    uint64_t pbe[EQB];  // B instance of each quad (fan tiles: its slot's)
-    float cbe[EQB];     // and its factor (FP16 B)
+    uint64_t pak[LIN ? EQA : 1], pbe[EQB];  // LIN: next k row of each block; else the instance's start
+    float cbe[EQB];                         // factor (FP16 B)
+    const uint32_t k0 = part * ((uint32_t)ksteps * TK);
 #pragma unroll
     for (int e = 0; e < EQB; ++e) {
-      pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] : pb;
+      pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] + (uint64_t)(bnn[e] & nmask) * (HB ? 4 : 8)
+                   : pb + (LIN ? (uint64_t)bnn[e] * (HB ? 4 : 8) : 0);
+      if (LIN) pbe[e] += (uint64_t)(k0 + 4 * bkq[e]) * b_k;
       cbe[e] = FAN ? (HB ? s_fb[bnn[e] >> d.nbits] : 1.f) : cb;
     }
-    typename FStage<HA>::type ra[EQA][4];
+    if constexpr (LIN) {
+#pragma unroll
+      for (int e = 0; e < EQA; ++e) pak[e] = pa + (uint64_t)(k0 + 4 * akq[e]) * a_k;
+    }
+    uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded (not LIN)
+    if (!LIN && d.ksplit) {
+      kba = dep<TAB_AK>(d, d.kbits, k0);
+      kbb = dep<TAB_BK>(d, d.kbits, k0);
+    }
+    // (a second register stage, as the FP16 tiles have, costs a workgroup per CU:
+    // 20/8/9 bits on the 128 x 64 tile 6.4 ms with one, 6.9 ms with two)
+    typename FStage<HA>::type ra[EQA][4][MA];
     typename FStage<HB>::type rb[EQB][4];
-    auto gload = [&](uint32_t kba, uint32_t kbb) {
+    auto gload = [&](int ks) {
+      if constexpr (!LIN) {
+        if (ks > 0) {
+          const int t = 3 + __builtin_ctz(ks);
+          kba ^= __builtin_amdgcn_readfirstlane(s_kx[0][t]);
+          kbb ^= __builtin_amdgcn_readfirstlane(s_kx[1][t]);
+        }
+      }
       if (astage) {
 #pragma unroll
         for (int e = 0; e < EQA; ++e)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) ra[e][q] = FStage<HA>::load(pa, aoff[e][q] + kba);
+          for (int q = 0; q < 4; ++q) {
+            if constexpr (LIN && MA == 2)
+              FStage<HA>::load2(pak[e] + q * a_k, (uint32_t)amm[e], ra[e][q]);
+            else if constexpr (LIN)
+              ra[e][q][0] = FStage<HA>::load(pak[e] + q * a_k, (uint32_t)amm[e]);
+            else
+              ra[e][q][0] = FStage<HA>::load(pa, aoff[e][q] + kba);
+          }
       }
       if (bstage) {
 #pragma unroll
         for (int e = 0; e < EQB; ++e)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) rb[e][q] = FStage<HB>::load(pbe[e], boff[e][q] + kbb);
+          for (int q = 0; q < 4; ++q) {
+            if constexpr (LIN)
+              rb[e][q] = FStage<HB>::load(pbe[e] + q * b_k, 0);
+            else
+              rb[e][q] = FStage<HB>::load(pbe[e], boff[e][q] + kbb);
+          }
+      }
+      if constexpr (LIN) {
+#pragma unroll
+        for (int e = 0; e < EQA; ++e) pak[e] += TK * a_k;
+#pragma unroll
+        for (int e = 0; e < EQB; ++e) pbe[e] += TK * b_k;
       }
     };
     auto lstore = [&](int buf) {
       if (astage) {
 #pragma unroll
         for (int e = 0; e < EQA; ++e) {
-          Split3 v[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = split3<PA>(scaled(FStage<HA>::val(ra[e][q], ca)));
+          for (int i = 0; i < MA; ++i) {
+            Split3 v[4];
 #pragma unroll
-          for (int p = 0; p < PA; ++p)
-            *reinterpret_cast<uint4*>(&As[buf][p][akq[e] * AQ + 4 * amm[e]]) =
-                make_uint4(v[0].p[p], v[1].p[p], v[2].p[p], v[3].p[p]);
+            for (int q = 0; q < 4; ++q) v[q] = split3<PA>(scaled(FStage<HA>::val(ra[e][q][i], ca)));
+#pragma unroll
+            for (int p = 0; p < PA; ++p)
+              *reinterpret_cast<uint4*>(&As[buf][p][akq[e] * AQ + 4 * (amm[e] + i)]) =
+                  make_uint4(v[0].p[p], v[1].p[p], v[2].p[p], v[3].p[p]);
+          }
         }
       }
       if (bstage) {
@@ -302,23 +360,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][q][r] = 0.f;
 
-    uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded
-    const uint32_t k0 = part * ((uint32_t)ksteps * TK);
-    if (d.ksplit) {
-      kba = dep<TAB_AK>(d, d.kbits, k0);
-      kbb = dep<TAB_BK>(d, d.kbits, k0);
-    }
-    gload(kba, kbb);
-    lstore(0);
-    __syncthreads();
-    for (int ks = 0; ks < ksteps; ++ks) {
-      const int buf = ks & 1;
-      if (ks + 1 < ksteps) {
-        const int t = 3 + __builtin_ctz(ks + 1);
-        kba ^= __builtin_amdgcn_readfirstlane(s_kx[0][t]);
-        kbb ^= __builtin_amdgcn_readfirstlane(s_kx[1][t]);
-        gload(kba, kbb);
-      }
+    auto kstep = [&](int buf) {
       auto afrag = [&](int p, int i) {
         return *reinterpret_cast<const bf16x8*>(&As[buf][p][half * AQ + 4 * ((wm * RM + i) * 32 + l32)]);
       };
@@ -368,9 +410,22 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
                   acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[g - ap][q], yv[ap], acc[i][q], 0, 0, 0);
         }
       }
-      if (ks + 1 < ksteps) lstore(buf ^ 1);
+    };
+
+    gload(0);
+    lstore(0);
+    __syncthreads();
+    // (the last step, which loads nothing, has a copy of its own: a load under a
+    // condition makes the compiler wait for more than it needs)
+    int ks = 0;
+    for (; ks + 1 < ksteps; ++ks) {
+      gload(ks + 1);
+      kstep(ks & 1);
+      lstore((ks + 1) & 1);
       __syncthreads();
     }
+    kstep(ks & 1);
+    __syncthreads();
 
     // A sum with an infinite or NaN input, or one whose scaled value leaves
     // FP32's range (an operand above 2^104, a sum above 2^80), is not what
@@ -479,18 +534,18 @@ __global__ __launch_bounds__(256) void k_split_add(NodeDesc d, uint64_t ws) {
 // ---------------------------------------------------------------------------
 // launchers (the tile configurations are those of kernels_c64.hip)
 
-template <bool FAN, bool REC, bool HA, bool HB>
+template <bool FAN, bool LIN, bool REC, bool HA, bool HB>
 static hipError_t launch_split_s(const NodeDesc& d, int cfg, unsigned grid, uint64_t ws, const int64_t* sig,
                                 hipStream_t st) {
   switch (cfg) {
-    case 0: hipLaunchKernelGGL((k_split<2, 1, 2, 2, FAN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 1: hipLaunchKernelGGL((k_split<2, 2, 2, 2, FAN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 2: hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 3: hipLaunchKernelGGL((k_split<4, 1, 2, 2, FAN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 4: hipLaunchKernelGGL((k_split<4, 2, 2, 2, FAN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 0: hipLaunchKernelGGL((k_split<2, 1, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 1: hipLaunchKernelGGL((k_split<2, 2, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 2: hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 3: hipLaunchKernelGGL((k_split<4, 1, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 4: hipLaunchKernelGGL((k_split<4, 2, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
     case 5:
       if (FAN) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_split<2, 4, 2, 2, false, false, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig);
+      hipLaunchKernelGGL((k_split<2, 4, 2, 2, false, LIN, false, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -510,19 +565,22 @@ static hipError_t launch_split_t(const NodeDesc& d, int cfg, uint64_t ws, const 
   // FP16-stored operands occur only in complex-half plans
   hipError_t e;
   const bool ks = d.ksplit > 0;  // the copies' sum records the maxima then
-  if (d.A.half) {
+  if (!d.linear) {  // a caller's own layout
+    if (FAN || REC || d.A.half || d.B.half) return hipErrorInvalidValue;
+    e = launch_split_s<false, false, false, false, false>(d, cfg, grid, ws, sig, st);
+  } else if (d.A.half) {
     if (d.B.half)
-      e = REC && !ks ? launch_split_s<FAN, REC, true, true>(d, cfg, grid, ws, sig, st)
-                     : launch_split_s<FAN, false, true, true>(d, cfg, grid, ws, sig, st);
+      e = REC && !ks ? launch_split_s<FAN, true, REC, true, true>(d, cfg, grid, ws, sig, st)
+                     : launch_split_s<FAN, true, false, true, true>(d, cfg, grid, ws, sig, st);
     else
-      e = REC && !ks ? launch_split_s<FAN, REC, true, false>(d, cfg, grid, ws, sig, st)
-                     : launch_split_s<FAN, false, true, false>(d, cfg, grid, ws, sig, st);
+      e = REC && !ks ? launch_split_s<FAN, true, REC, true, false>(d, cfg, grid, ws, sig, st)
+                     : launch_split_s<FAN, true, false, true, false>(d, cfg, grid, ws, sig, st);
   } else if (d.B.half) {
-    e = REC && !ks ? launch_split_s<FAN, REC, false, true>(d, cfg, grid, ws, sig, st)
-                   : launch_split_s<FAN, false, false, true>(d, cfg, grid, ws, sig, st);
+    e = REC && !ks ? launch_split_s<FAN, true, REC, false, true>(d, cfg, grid, ws, sig, st)
+                   : launch_split_s<FAN, true, false, false, true>(d, cfg, grid, ws, sig, st);
   } else {
-    e = REC && !ks ? launch_split_s<FAN, REC, false, false>(d, cfg, grid, ws, sig, st)
-                   : launch_split_s<FAN, false, false, false>(d, cfg, grid, ws, sig, st);
+    e = REC && !ks ? launch_split_s<FAN, true, REC, false, false>(d, cfg, grid, ws, sig, st)
+                   : launch_split_s<FAN, true, false, false, false>(d, cfg, grid, ws, sig, st);
   }
   if (e != hipSuccess || !ks) return e;
   const unsigned g2 = grid_for(((d.n_inst << (d.mbits + d.nbits)) + 255) / 256);

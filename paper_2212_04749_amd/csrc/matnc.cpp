@@ -1475,6 +1475,11 @@ void launch_contract(const ContractCall& c, const void* A, const void* B, void* 
   d.nbits = c.nn;
   d.kbits = c.nk;
   std::memcpy(d.pos, c.pos, sizeof(d.pos));
+  // contracted bits highest in both operands, and 16-byte loads aligned
+  d.linear = c.nm > 0 && (d.A.off | d.A.inst_bytes) % 16 == 0;
+  for (int t = 0; t < c.nm; ++t) d.linear &= c.pos[TAB_AM][t] == t;
+  for (int t = 0; t < c.nn; ++t) d.linear &= c.pos[TAB_BN][t] == t;
+  for (int t = 0; t < c.nk; ++t) d.linear &= c.pos[TAB_AK][t] == c.nm + t && c.pos[TAB_BK][t] == c.nn + t;
   hipError_t e = c.kind == 1 ? launch_split(d, c.cfg, 0, nullptr, st) : launch_stream(d, 0, nullptr, st);
   hip_check(e, "contract launch");
 }
