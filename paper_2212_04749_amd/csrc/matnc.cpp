@@ -1194,8 +1194,6 @@ void launch_node(const Plan& P, const PNode& V, const NodeDesc& d, hipStream_t s
   hip_check(e, "kernel launch");
 }
 
-// one slice batch of chunk c: the per-batch nodes, then the slice-sum of
-// the chunk's rows into amps (skipped when amps is null)
 // HIP events around every launch of one node (the rest run as usual)
 struct StepTimer {
   int v = -1;
@@ -1235,14 +1233,11 @@ void launch_fused(const Plan& P, const Tree& T, int c, int nb, hipStream_t st, S
   if (timed) t->end(st);
 }
 
-void launch_batch(const Plan& P, int c, int nb, hipStream_t st, double* amps, StepTimer* t = nullptr) {
+// the slice-sum of chunk c's rows into amps (the root holds no sliced index, so
+// it is read by position in the batch, not by slice id)
+void launch_sum(const Plan& P, int c, int nb, hipStream_t st, double* amps) {
   const int64_t* sig = reinterpret_cast<const int64_t*>(P.ws + P.sigma_off);
   const int ob = (int)P.open_qubits.size();
-  if (P.precision == MATNC_CHALF)
-    hip_check(launch_zero(P.ws + P.dep_scale_lo, P.dep_scale_hi - P.dep_scale_lo, st), "clear scales");
-  launch_fused(P, P.loop_tree, c, nb, st, t);
-  for (int v : P.loop) launch_node_timed(P, v, node_desc(P, v, nb, c), st, t);
-  if (!amps) return;
   const Chunk& C = P.chunks[c];
   const OpDesc root = root_desc(P, c);
   const int64_t nrows = (int64_t)C.rows.size();
@@ -1252,6 +1247,16 @@ void launch_batch(const Plan& P, int c, int nb, hipStream_t st, double* amps, St
   hipError_t er = !root.half ? launch_slice_sum(root, P.ws, sig, nb, nrows, rows, ob, amps, st)
                              : launch_slice_sum_h(root, P.ws, sig, nb, nrows, rows, ob, amps, st);
   hip_check(er, "slice sum");
+}
+
+// one slice batch of chunk c: the per-batch nodes, then the slice-sum of
+// the chunk's rows into amps (skipped when amps is null)
+void launch_batch(const Plan& P, int c, int nb, hipStream_t st, double* amps, StepTimer* t = nullptr) {
+  if (P.precision == MATNC_CHALF)
+    hip_check(launch_zero(P.ws + P.dep_scale_lo, P.dep_scale_hi - P.dep_scale_lo, st), "clear scales");
+  launch_fused(P, P.loop_tree, c, nb, st, t);
+  for (int v : P.loop) launch_node_timed(P, v, node_desc(P, v, nb, c), st, t);
+  if (amps) launch_sum(P, c, nb, st, amps);
 }
 
 void launch_prologue(const Plan& P, hipStream_t st, StepTimer* t = nullptr) {
@@ -1269,7 +1274,7 @@ void launch_chunk_prologue(const Plan& P, int c, hipStream_t st, StepTimer* t = 
   for (int v : P.cpro) launch_node_timed(P, v, node_desc(P, v, 1, c), st, t);
 }
 
-void release_graph(Plan& P) {
+void release_batch_graphs(Plan& P) {
   for (auto g : P.graph_execs)
     if (g) (void)hipGraphExecDestroy(g);
   for (auto g : P.graphs)
@@ -1279,10 +1284,63 @@ void release_graph(Plan& P) {
   P.graph_amps = nullptr;
 }
 
+void release_graph(Plan& P) {
+  release_batch_graphs(P);
+  if (P.pro_exec) (void)hipGraphExecDestroy(P.pro_exec);
+  if (P.pro_graph) (void)hipGraphDestroy(P.pro_graph);
+  P.pro_exec = nullptr;
+  P.pro_graph = nullptr;
+  P.pro_runs = 0;
+}
+
+// The prologue (slice-invariant tensors: no step reads the slice id).  An
+// unsliced plan is all prologue, 20 to 60 launches of 5 to 10 us each, which the
+// host cannot queue as fast as they run; a plan that runs it again (new tensors,
+// a dropped cache) captures it at the second run -- at the first the capture
+// would cost more than it gains -- and replays it from then on: 4x5 qubits, 11
+// cycles, 150 -> 110 us a pass (host 150 -> 106 us); 5x5 qubits complex-half,
+// 3.2 ms of kernels either way, host 825 -> 110 us.  Under the caller's own
+// capture it is recorded, not run, so the result says whether the cache holds
+// the tensors now.
+bool run_prologue(Plan& P) {
+  hipStream_t st = P.stream;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (st != nullptr) hip_check(hipStreamIsCapturing(st, &cap), "capture status");
+  if (cap != hipStreamCaptureStatusNone) {
+    launch_prologue(P, st);
+    return false;
+  }
+  if (st == nullptr || P.prologue.size() < 4 || (!P.pro_exec && P.pro_runs++ == 0)) {
+    launch_prologue(P, st);
+    return true;
+  }
+  if (!P.pro_exec) {
+    hip_check(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal), "begin prologue capture");
+    hipGraph_t g = nullptr;
+    try {
+      launch_prologue(P, st);
+    } catch (...) {
+      (void)hipStreamEndCapture(st, &g);
+      if (g) (void)hipGraphDestroy(g);
+      throw;
+    }
+    hip_check(hipStreamEndCapture(st, &g), "end prologue capture");
+    const hipError_t er = hipGraphInstantiate(&P.pro_exec, g, nullptr, nullptr, 0);
+    if (er != hipSuccess) {
+      P.pro_exec = nullptr;
+      (void)hipGraphDestroy(g);
+      hip_check(er, "prologue graph instantiate");
+    }
+    P.pro_graph = g;
+  }
+  hip_check(hipGraphLaunch(P.pro_exec, st), "prologue graph launch");
+  return true;
+}
+
 // capture one full slice batch of every chunk (adding into amps) as graphs;
 // not possible on the null stream
 void capture_batch_graphs(Plan& P, double* amps) {
-  release_graph(P);
+  release_batch_graphs(P);
   if (P.stream == nullptr || amps == nullptr) return;
   for (int c = 0; c < P.n_chunks; ++c) {
     hip_check(hipStreamBeginCapture(P.stream, hipStreamCaptureModeThreadLocal), "begin capture");
@@ -1306,7 +1364,6 @@ void capture_batch_graphs(Plan& P, double* amps) {
 // every launch of a complete pass over slices [b, e) into amps (no graphs)
 void launch_pass(Plan& P, int64_t b, int64_t e, double* amps, hipStream_t st) {
   int64_t* sig = reinterpret_cast<int64_t*>(P.ws + P.sigma_off);
-  hip_check(launch_set_i64(sig, 0, st), "set sigma");
   launch_prologue(P, st);
   const int64_t batch = P.tree_batch ? P.tree_batch : P.batch;
   for (int c = 0; c < P.n_chunks; ++c) {
@@ -1777,23 +1834,22 @@ int matnc_execute(matnc_plan plan, int64_t slice_begin, int64_t slice_end, doubl
     int64_t* sig = reinterpret_cast<int64_t*>(P.ws + P.sigma_off);
     claim_arena(P);
     if (!P.inv_valid) {
-      hip_check(launch_set_i64(sig, 0, st), "set sigma");
-      launch_prologue(P, st);
-      P.inv_valid = true;
+      P.inv_valid = run_prologue(P);
     }
     if (slice_end == slice_begin) return;
-    if (P.tree_batch) {
-      // a launch for the slices and one for their sum: nothing to capture
-      const OpDesc root = root_desc(P, 0);
-      const Chunk& C = P.chunks[0];
-      const int64_t nrows = (int64_t)C.rows.size();
-      const int32_t* rows = reinterpret_cast<const int32_t*>(P.ws + C.rows_off);
-      const int ob = (int)P.open_qubits.size();
-      for (int64_t s0 = slice_begin; s0 < slice_end; s0 += P.tree_batch) {
-        const int nb = (int)std::min<int64_t>(P.tree_batch, slice_end - s0);
-        hip_check(launch_tree(P.ws, P.loop_tree.off[0], (int)P.loop_tree.roots.size(), nb, nullptr, s0, st),
-                  "fused slices");
-        hip_check(launch_slice_sum(root, P.ws, sig, nb, nrows, rows, ob, amps_dev, st), "slice sum");
+    if (P.loop.empty()) {
+      // at most a launch for the fused slices and one for their sum: nothing to
+      // capture, and the slice id is an argument
+      const int64_t batch = P.tree_batch ? P.tree_batch : P.batch;
+      for (int c = 0; c < P.n_chunks; ++c) {
+        launch_chunk_prologue(P, c, st);
+        for (int64_t s0 = slice_begin; s0 < slice_end; s0 += batch) {
+          const int nb = (int)std::min<int64_t>(batch, slice_end - s0);
+          if (!P.loop_tree.roots.empty())
+            hip_check(launch_tree(P.ws, P.loop_tree.off[c], (int)P.loop_tree.roots.size(), nb, nullptr, s0, st),
+                      "fused slices");
+          launch_sum(P, c, nb, st, amps_dev);
+        }
       }
       return;
     }

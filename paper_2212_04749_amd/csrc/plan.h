@@ -164,6 +164,9 @@ struct Plan {
   hipStream_t stream = nullptr;
   std::vector<hipGraph_t> graphs;          // one full slice batch per chunk
   std::vector<hipGraphExec_t> graph_execs;
+  hipGraph_t pro_graph = nullptr;      // the prologue, from its second run on
+  hipGraphExec_t pro_exec = nullptr;
+  int pro_runs = 0;                    // eager runs of the prologue since the last binding
   double* graph_amps = nullptr;        // amplitude buffer the batch graphs add into
   uint64_t generation = 0;             // bumped whenever launch parameters change
   std::vector<unsigned char> staging;  // host image of the static region

@@ -187,3 +187,58 @@ def test_fused_slices(precision, opens, cap, batch):
             rows.append(word)
     assert_close(full[..., 0] + 1j * full[..., 1], statevector.amplitudes_from_state(psi, rows), 1e-5)
     run.close()
+
+
+@pytest.mark.parametrize("precision", ["c64", "chalf"])
+def test_invariant_steps_from_a_graph(precision):
+    """An unsliced plan run again and again (its steps are replayed from a graph from the second time on), with other
+    work between and new numbers in a tensor: the bits of a plan on the default stream, which never captures; and the
+    same under a capture of the caller's, which leaves nothing in the cache."""
+    torch = require_gpu()
+    from paper_2212_04749_amd import api, planner
+    from paper_2212_04749_amd.circuit_tn import build_network
+    from workload import GridSpec, random_circuit, uniform_bitstrings
+    net = build_network(random_circuit(GridSpec(4, 4), 10, 57))
+    words = uniform_bitstrings(16, 40, 58)
+    pl = planner.find_plan(net, words, (), 30, trials=4, refine_top=0)
+    spec = api.PlanSpec(pl.pairs, pl.sliced, (), 30)
+    eager = api.Contraction(net, spec, words, precision=precision, stream=torch.cuda.default_stream())
+    run = api.Contraction(net, spec, words, precision=precision)
+    assert run.n_slices == 1
+    t = max(range(len(run.net.tensors)), key=lambda i: run.net.tensors[i].size)
+    data = np.array(run.net.tensors[t])
+    noise, amps = torch.zeros(1 << 20, device="cuda"), run.new_amplitudes()
+    eager.amplitudes(), run.amplitudes()
+
+    def want(scale):
+        eager.set_tensor(t, data * scale)
+        return eager.amplitudes()
+
+    for scale in (1.0, 0.5, 0.75, -3.0, 1.0):
+        noise += 1.0
+        run.set_tensor(t, data * scale)
+        got = run.amplitudes()
+        run.reset_cache()
+        torch.cuda.synchronize()
+        noise += 1.0
+        ref = want(scale)
+        assert np.array_equal(got, ref) and np.array_equal(run.amplitudes(), ref)
+    ref = want(2.0)
+    run.set_tensor(t, data * 2.0)
+    run.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=run.stream):
+        amps.zero_()
+        run.execute(amps)
+    assert np.array_equal(run.amplitudes(), ref)  # the capture ran nothing, and the cache does not claim that it did
+    for _ in range(3):
+        noise += 1.0
+        amps.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        a = amps.cpu().numpy()
+        assert np.array_equal(a[..., 0] + 1j * a[..., 1], ref.reshape(a.shape[:-1]))
+        assert np.array_equal(run.amplitudes(), ref)
+    torch.cuda.synchronize()
+    run.close(), eager.close()
