@@ -40,7 +40,16 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"fp32": 157.3, "fp16": 2516.6}  # dense MFMA
+# dense MFMA; "split": FP32 operands in three bfloat16 parts, six products of parts
+PEAK_TFLOPS = {"fp32": 157.3, "fp16": 2516.6, "split": 2516.6 / 6}
+MAX_HALF_SPLIT = 2  # FP16 tensors up to which a plan's FP32 steps run on the split tiles
+
+
+def kernel_rate(kid, n_half):
+    """The matrix-core rate (a key of PEAK_TFLOPS) that kernel id `kid` of a plan with n_half FP16 tensors is priced at."""
+    return "fp16" if kid >= 300 else "split" if n_half <= MAX_HALF_SPLIT and kid >= 100 else "fp32"
+
+
 PEAK_HBM_GBS = 8000.0
 GOLDEN = os.path.join(ROOT, "tests", "golden")
 METRIC = "sustained complex TFLOP/s + amplitudes/sec per slice-batch at stated err vs FP64"
@@ -368,7 +377,7 @@ def run_leg(api, torch, name, w, net, spec, precision, batch, steps, warmup, arg
         "unit": "amplitudes/s",
         "complex_tflops": tflops,
         # whole-step rate over the MFMA peak of the precision's arithmetic
-        "mfma_peak_frac": tflops / PEAK_TFLOPS["fp32" if precision == "c64" else "fp16"],
+        "mfma_peak_frac": tflops / PEAK_TFLOPS["split" if precision == "c64" else "fp16"],
         # sum over the steps of each one's roofline time (the larger of its
         # flops over the MFMA peak of its kernel and its algorithmic bytes
         # over 8 TB/s), over the measured (or, for a slice subset, projected) time
@@ -499,9 +508,10 @@ def dominant_step(run, precision, n_batches):
         if ms < 0:
             continue
         reps = n_batches if dep else 1
-        # 100/200 + c: FP32 MFMA (complex64, and the FP32 steps of
-        # complex-half); 300/400 + c: FP16 MFMA; 0: streaming (vector ALU)
-        peak = PEAK_TFLOPS["fp16" if kid >= 300 else "fp32"]
+        # 100/200 + c: FP32-stored steps (split tiles, or the FP32 instruction);
+        # 300/400 + c: FP16 MFMA; 0: streaming (vector ALU) or fused
+        rate = kernel_rate(kid, run.info.n_half_nodes)
+        peak = PEAK_TFLOPS[rate]
         tf, tb = 8 * cmac / (peak * 1e12), by / (PEAK_HBM_GBS * 1e9)
         t_roof += reps * max(tf, tb) * 1e3
         e = per.setdefault(kid, {"ms": 0.0, "cmac": 0.0, "bytes": 0.0, "launches": 0})
@@ -509,11 +519,11 @@ def dominant_step(run, precision, n_batches):
         e["cmac"] += cmac * reps
         e["bytes"] += by * reps
         e["launches"] += reps
-        steps.append((ms * reps, j, ms, kid, cmac, by, reps, tf, tb, peak))
+        steps.append((ms * reps, j, ms, kid, cmac, by, reps, tf, tb, peak, rate))
     total = sum(x[0] for x in steps)
-    share, j, ms, kid, cmac, by, reps, tf, tb, peak = max(steps)
+    share, j, ms, kid, cmac, by, reps, tf, tb, peak, rate = max(steps)
     return {"step": j, "profile_ms": ms, "kid": kid, "cmac": cmac, "bytes": by, "tf": tf, "tb": tb, "peak": peak,
-            "share": share / total, "per": per, "t_roof_ms": t_roof}
+            "rate": rate, "share": share / total, "per": per, "t_roof_ms": t_roof}
 
 
 def roofline(dom, ms_total, launches, precision, workload):
@@ -533,7 +543,7 @@ def roofline(dom, ms_total, launches, precision, workload):
     r["algorithmic_bytes_per_launch"] = by
     r["algorithmic_flops_per_launch"] = 8 * cmac
     r["kernel"] = ("streaming" if kid < 100 else
-                   f"{'fp16' if kid >= 300 else 'fp32'} mfma{' fan-out' if (kid // 100) % 2 == 0 else ''} "
+                   f"{dom['rate']} mfma{' fan-out' if (kid // 100) % 2 == 0 else ''} "
                    f"cfg {kid % 100}") + f", step {j}"
     r["kernel_id"] = kid
     r["step"] = j

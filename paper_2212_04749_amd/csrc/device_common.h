@@ -36,9 +36,6 @@ __device__ __forceinline__ cptr<T> cmem(uint64_t a) {
   return (cptr<T>)a;
 }
 
-// unsigned atomic max on a workspace word (float bits of non-negative values)
-__device__ __forceinline__ void gmax_u32(uint64_t a, uint32_t v) { atomicMax((uint32_t*)a, v); }
-
 typedef float floatx16 __attribute__((ext_vector_type(16)));  // MFMA accumulator
 
 // element accessors (HIP's float2 / __half2 classes cannot be copied
@@ -118,12 +115,6 @@ __device__ __forceinline__ void unit_tile(uint32_t lt, uint32_t units, int tbits
 template <typename P>
 __device__ __forceinline__ uint32_t tlook(P T, uint32_t x) {
   return T[x & 255u] + T[256 + ((x >> 8) & 255u)] + T[512 + ((x >> 16) & 255u)] + T[768 + (x >> 24)];
-}
-
-// offset of coordinate hi * 256 + lo (lo < 256)
-template <typename P>
-__device__ __forceinline__ uint32_t tlook_split(P T, uint32_t hi, uint32_t lo) {
-  return T[lo] + T[256 + (hi & 255u)] + T[512 + ((hi >> 8) & 255u)] + T[768 + (hi >> 16)];
 }
 
 // offset of coordinate v (< 2^nbits) of class CLS, from the bit positions in

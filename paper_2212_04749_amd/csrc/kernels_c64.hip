@@ -1,7 +1,11 @@
 // complex64 kernels of the contraction path (gfx950).
 //
-//  * k_mfma: one pairwise step C[m, n] = sum_k A[m, k] B[k, n] with large N
-//    and K (the streaming kernels of kernels_stream.hip take the rest): a
+//  * k_mfma: one FP32-stored pairwise step C[m, n] = sum_k A[m, k] B[k, n]
+//    with large N and K of a complex-half plan that stores more than
+//    kMaxHalfSplit tensors in FP16 (the split tiles of kernels_split.hip are up
+//    to 1.7 times as fast and take the FP32 steps of every other plan, but each
+//    re-rounded input of an FP16 tensor may move that tensor by an FP16 rounding,
+//    4e-5 of the fidelity estimate): a
 //    complex GEMM on
 //    v_mfma_f32_32x32x2f32 through the real embedding
 //    [Ar Ai] x [[Br, Bi], [-Bi, Br]] = [Cr Ci] (8 real flops per complex

@@ -1,7 +1,7 @@
 // Matrix-core kernel of the FP32-stored steps (gfx950): C[m, n] = sum_k
 // A[m, k] B[k, n] as a complex GEMM whose FP32 operands are split exactly into
 // three bfloat16 parts each (8 + 8 + 8 of the 24 bits; bfloat16 has FP32's
-// exponent range, so no scaling is involved).  Of the nine products of parts
+// exponent range, so one constant factor serves every operand).  Of the nine products of parts
 // the six with index sum <= 2 are summed on v_mfma_f32_32x32x16_bf16 in FP32;
 // the three left out are below 2^-25 of the product.  The FP32 instruction
 // (v_mfma_f32_32x32x2f32, kernels_c64.hip) rounds the accumulator once per
@@ -12,9 +12,16 @@
 //
 // Bound: six bfloat16 products take 192 matrix-core cycles per 32 x 16 x 8
 // complex block, the FP32 instruction 512.  At 20/8/9 bits of m/n/k the step
-// runs 5.9 ms (186 TFLOP/s complex, 1118 TFLOP/s of bfloat16 -- what a large
-// bfloat16 library product reaches on this card under its power limit)
-// against 8.6 ms for the FP32 instruction's best tile.
+// runs 5.30 to 5.56 ms (198 to 208 TFLOP/s complex, 1190 to 1250 of bfloat16;
+// a large bfloat16 library product reaches 1107 on this card under its power
+// limit) against 9.1 ms for the FP32 instruction's tile.  At 22/6/6 bits the
+// step is bound by its 17 GB instead (4.4 TB/s of the 5.1 of a copy).
+//
+// Fan-out tiles whose groups do not fill them multiply empty columns: at
+// 10/3/11 bits (8 instances on average share an A) 0.70 of the 64-column
+// tiles' columns hold an instance, 129 TFLOP/s of those.  Leaving out the empty
+// 16-column blocks by a condition in the k loop gave 4% there and cost 11% on
+// 22/1/6 bits, whose tiles are full; with a loop of its own the kernel spills.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -12,6 +12,15 @@
 //  * k_kred<FL, NB>        large K: lanes own m (coalesced reads of A along
 //    its low bits), groups of lanes split K, partial sums meet in LDS.
 //
+//  * k_kfew, k_kdot  large K and at most 8 values of m: see there.
+//
+// Bound: bytes, of small steps the launch.  Whole calls of a single contraction
+// (m/n/k bits x instances) with an offset table read per access, uploaded for
+// each call, one block per 256 m, and now: 22/2/2, 268 MB, 73 -> 53 us (5.07
+// TB/s, a copy's rate); 10/1/11 x 33, 555 MB, 332 -> 108 us (it had 132 blocks, one
+// chain of loads per lane); 4/12/5 x 9, 14 MB, 76 -> 16 us (it ran a lane per output
+// with m, n as given; the wider side is M now); 5/3/2 x 7 40 -> 11 us.
+//
 // Offsets come from the bit positions in the descriptor (dep): no table is
 // read, so that a first touch of one does not delay the operand loads, and a
 // single contraction needs no table built before it.
