@@ -25,7 +25,6 @@
 #include <limits>
 #include <map>
 #include <memory>
-#include <mutex>
 #include <new>
 #include <numeric>
 #include <stdexcept>
@@ -811,6 +810,9 @@ struct ArenaBuf {
   int t0, t1;
 };
 
+// the one kernel that looks offsets up instead of depositing bits: k_mfma
+bool reads_tables(const Plan& P, const PNode& V) { return V.kernel == 1 && !V.half_store && !P.split; }
+
 // schedule, chunks and the static memory plan for a given chunk count
 void build_memory_for(Plan& P, int n_chunks) {
   const int nt = P.net.n_tensors;
@@ -878,7 +880,7 @@ void build_memory_for(Plan& P, int n_chunks) {
   for (int v = nt; v < P.n_nodes; ++v) {
     PNode& V = P.nodes[v];
     V.tab_off = off;
-    off = align_up(off + (uint64_t)TAB_COUNT * kTabSize * 4);
+    if (reads_tables(P, V)) off = align_up(off + (uint64_t)TAB_COUNT * kTabSize * 4);
     if (P.chunk_pos[v] < 0) {
       V.ga_off = off;
       off = align_up(off + V.ga.size() * 4);
@@ -961,7 +963,7 @@ void build_memory_for(Plan& P, int n_chunks) {
   // and the root's instances allow (the caller's slice batch is sized for
   // intermediates, which such slices keep in LDS).
   P.tree_batch = 0;
-  if (P.loop.empty() && !P.loop_tree.roots.empty() && n_chunks == 1) {
+  if (P.wide_batch && P.loop.empty() && !P.loop_tree.roots.empty() && n_chunks == 1) {
     const uint64_t bytes = (uint64_t)cap_inst[root] * 8 << P.nodes[root].idx.size();
     const int64_t n = std::min<int64_t>((int64_t)1 << P.sliced.size(), kTreeBatch);
     P.tree_batch = (int)std::max<int64_t>(P.batch, std::min<int64_t>(n, (int64_t)(kTreeBatchBytes / bytes)));
@@ -1036,8 +1038,10 @@ void build_memory(Plan& P) {
     return !P.memory_budget || P.workspace_bytes <= P.memory_budget;
   };
   if (fit()) return;
-  // no room even for single keys: sums in one piece need less
+  // no room even for single keys: sums in one piece and no more slices per
+  // launch than the slice batch need less
   for (PNode& V : P.nodes) V.ksplit = 0;
+  P.wide_batch = false;
   if (!fit())
     fail(MATNC_E_NOMEM, "plan needs " + std::to_string(P.workspace_bytes) + " bytes of workspace even with " +
                             std::to_string(P.n_chunks) + " key chunks; budget " + std::to_string(P.memory_budget));
@@ -1567,9 +1571,11 @@ void bind_plan(Plan& P, void* dev_workspace, size_t bytes, void* hip_stream, uin
   const int nt = P.net.n_tensors;
   for (int v = nt; v < P.n_nodes; ++v) {
     const PNode& V = P.nodes[v];
-    uint32_t* T = reinterpret_cast<uint32_t*>(P.staging.data() + V.tab_off);
-    const size_t nbits[TAB_COUNT] = {V.M.size(), V.M.size(), V.N.size(), V.N.size(), V.K.size(), V.K.size()};
-    for (int t = 0; t < TAB_COUNT; ++t) fill_table(T + t * kTabSize, V.pos[t], nbits[t]);
+    if (reads_tables(P, V)) {
+      uint32_t* T = reinterpret_cast<uint32_t*>(P.staging.data() + V.tab_off);
+      const size_t nbits[TAB_COUNT] = {V.M.size(), V.M.size(), V.N.size(), V.N.size(), V.K.size(), V.K.size()};
+      for (int t = 0; t < TAB_COUNT; ++t) fill_table(T + t * kTabSize, V.pos[t], nbits[t]);
+    }
     if (P.chunk_pos[v] < 0) {
       std::memcpy(P.staging.data() + V.ga_off, V.ga.data(), V.ga.size() * 4);
       std::memcpy(P.staging.data() + V.gb_off, V.gb.data(), V.gb.size() * 4);

@@ -146,6 +146,7 @@ struct Plan {
   // loop_tree); chunked = cpro, loop_tree's nodes, loop
   Tree pro_tree, loop_tree;
   int tree_batch = 0;  // slices per launch if a slice is one fused subtree, else 0
+  bool wide_batch = true;  // room for tree_batch to exceed the slice batch
   std::vector<int> prologue, cpro, loop, chunked;
   // costs
   double cmac_single = 0, cmac_multi = 0, cmac_inv = 0, cmac_total = 0;
