@@ -242,3 +242,26 @@ def test_invariant_steps_from_a_graph(precision):
         assert np.array_equal(run.amplitudes(), ref)
     torch.cuda.synchronize()
     run.close(), eager.close()
+
+
+@pytest.mark.parametrize("batch", [1, 3])
+def test_fused_slices_without_room(batch):
+    """One amplitude of a plan whose slice is one subtree: a budget without room for more slices per launch than the
+    slice batch is still enough, with the same bits."""
+    require_gpu()
+    from paper_2212_04749_amd import api, planner
+    from paper_2212_04749_amd.circuit_tn import build_network
+    from workload import GridSpec, random_circuit, uniform_bitstrings
+    net = build_network(random_circuit(GridSpec(3, 4), 8, 51))
+    words = uniform_bitstrings(12, 1, 52)
+    pl = planner.find_plan(net, words, (), 5, trials=4, refine_top=0)
+    spec = api.PlanSpec(pl.pairs, pl.sliced, (), 5)
+    run = api.Contraction(net, spec, words, slice_batch=batch)
+    need, n, full = int(run.info.workspace_bytes), run.n_slices, run.amplitudes()
+    run.close()
+    assert n > 32 * batch
+    run = api.Contraction(net, spec, words, slice_batch=batch, memory_budget=need - 1)
+    say(f"fused slices without room: {n} slices, {need} and {run.info.workspace_bytes} bytes")
+    assert int(run.info.workspace_bytes) < need
+    assert np.array_equal(run.amplitudes(), full) and np.array_equal(run.amplitudes(), full)
+    run.close()
