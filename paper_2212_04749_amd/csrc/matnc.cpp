@@ -756,11 +756,13 @@ std::vector<uint32_t> tree_words(const Plan& P, const Tree& T, int c) {
         t.c_lo = (uint32_t)off;
         t.c_hi = (uint32_t)(off >> 32);
       }
-      if (t.w > 1) {
+      const int pos = P.chunk_pos[v];
+      const std::vector<int32_t>&ga = pos >= 0 ? P.chunks[c].nodes[pos].ga : V.ga,
+                      &gb = pos >= 0 ? P.chunks[c].nodes[pos].gb : V.gb;
+      // (a chunk's single key may need any instance of a leaf: leaves keep all
+      // of their keys in every chunk)
+      if (t.w > 1 || ga[0] || gb[0]) {
         t.gmap = (uint32_t)gmaps.size() + 1;
-        const int pos = P.chunk_pos[v];
-        const std::vector<int32_t>&ga = pos >= 0 ? P.chunks[c].nodes[pos].ga : V.ga,
-                        &gb = pos >= 0 ? P.chunks[c].nodes[pos].gb : V.gb;
         for (uint32_t j = 0; j < t.w; ++j) gmaps.push_back((uint32_t)ga[j] | (uint32_t)gb[j] << 16);
       }
       for (uint32_t q = 0; q < mb + nb; ++q)
