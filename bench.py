@@ -42,12 +42,12 @@ sys.path.insert(0, ROOT)
 
 # dense MFMA; "split": FP32 operands in three bfloat16 parts, six products of parts
 PEAK_TFLOPS = {"fp32": 157.3, "fp16": 2516.6, "split": 2516.6 / 6}
-MAX_HALF_SPLIT = 2  # FP16 tensors up to which a plan's FP32 steps run on the split tiles
 
 
 def kernel_rate(kid, n_half):
-    """The matrix-core rate (a key of PEAK_TFLOPS) that kernel id `kid` of a plan with n_half FP16 tensors is priced at."""
-    return "fp16" if kid >= 300 else "split" if n_half <= MAX_HALF_SPLIT and kid >= 100 else "fp32"
+    """The matrix-core rate (a key of PEAK_TFLOPS) that kernel id `kid` of a plan with n_half FP16 tensors is priced at
+    (the FP32-stored steps of a plan without FP16 tensors run on the split tiles)."""
+    return "fp16" if kid >= 300 else "split" if n_half == 0 and kid >= 100 else "fp32"
 
 
 PEAK_HBM_GBS = 8000.0

@@ -71,7 +71,7 @@ struct NodeDesc {
   // of the node, whatever the slice batch or key chunk of this launch, so that
   // results do not depend on how slices and keys are grouped
   int64_t n_ref;
-  int32_t keep_order;    // 1: sums keep the order of additions fixed by the shape (see kMaxHalfSplit)
+  int32_t keep_order;    // 1: sums keep the order of additions fixed by the shape (plans with FP16 tensors)
   int32_t linear;        // 1: A[m + (k << mbits)] and B[n + (k << nbits)]
   int32_t ks_bits;       // long-sum kernel: 2^ks_bits lane groups share a sum
   // split sums (matrix-core steps with few tiles and a long sum): the sum is

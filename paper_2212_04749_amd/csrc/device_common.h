@@ -1,6 +1,5 @@
 // Device helpers shared by the complex64 and complex-half kernels.
 #pragma once
-#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -164,40 +163,6 @@ __device__ __forceinline__ void cmac(float2& c, float2 a, float2 b) {
   c.y = fmaf(a.y, b.x, c.y);
 }
 
-
-// An operand's staged element: an FP32 pair, or (complex-half plans, whose
-// FP32 steps may read an FP16-stored child) a half2 word converted exactly to
-// FP32 and multiplied by the instance's power of two 2^e.
-template <bool H>
-struct FStage;
-template <>
-struct FStage<false> {
-  typedef f32x2 type;
-  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return gmem<const f32x2>(base)[i]; }
-  // elements i (even) and i + 1
-  static __device__ __forceinline__ void load2(uint64_t base, uint32_t i, type (&r)[2]) {
-    const f32x4 v = *(gptr<const f32x4>)((gptr<const char>)base + 8 * i);
-    r[0] = f32x2{v.x, v.y};
-    r[1] = f32x2{v.z, v.w};
-  }
-  static __device__ __forceinline__ float2 val(type r, float) { return make_float2(r.x, r.y); }
-};
-template <>
-struct FStage<true> {
-  typedef uint32_t type;
-  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return ldg_u32(base, i); }
-  static __device__ __forceinline__ void load2(uint64_t base, uint32_t i, type (&r)[2]) {
-    const u32x2 v = *(gptr<const u32x2>)((gptr<const char>)base + 4 * i);
-    r[0] = v.x;
-    r[1] = v.y;
-  }
-  static __device__ __forceinline__ float2 val(type r, float c) {
-    __half2 h;
-    __builtin_memcpy(&h, &r, 4);
-    const float2 v = __half22float2(h);
-    return make_float2(v.x * c, v.y * c);
-  }
-};
 
 // grid size for grid-stride loops
 static inline unsigned grid_for(int64_t blocks) {

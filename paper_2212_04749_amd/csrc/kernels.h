@@ -25,7 +25,6 @@ hipError_t launch_mfma_fan_rec(const NodeDesc& d, int cfg, uint64_t ws, const in
 // configurations)
 hipError_t launch_split(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
 hipError_t launch_split_fan(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
-hipError_t launch_split_fan_rec(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st);
 // log2 of the parts that a step's sum should be cut into (units: output
 // instances or fan-table rows of the launch)
 int split_bits(int cfg, bool fan, int mbits, int nbits, int kbits, int64_t units);

@@ -1,12 +1,10 @@
 // complex64 kernels of the contraction path (gfx950).
 //
 //  * k_mfma: one FP32-stored pairwise step C[m, n] = sum_k A[m, k] B[k, n]
-//    with large N and K of a complex-half plan that stores more than
-//    kMaxHalfSplit tensors in FP16 (the split tiles of kernels_split.hip are up
-//    to 1.7 times as fast and take the FP32 steps of every other plan, but each
-//    re-rounded input of an FP16 tensor may move that tensor by an FP16 rounding,
-//    4e-5 of the fidelity estimate): a
-//    complex GEMM on
+//    with large N and K of a complex-half plan that stores tensors in FP16
+//    (the split tiles of kernels_split.hip are up to 1.7 times as fast and take
+//    the FP32 steps of every other plan, but each re-rounded input of an FP16
+//    tensor may move that tensor by an FP16 rounding): a complex GEMM on
 //    v_mfma_f32_32x32x2f32 through the real embedding
 //    [Ar Ai] x [[Br, Bi], [-Bi, Br]] = [Cr Ci] (8 real flops per complex
 //    MAC, so MFMA flops equal complex flops), LDS-staged, double-buffered
@@ -32,6 +30,29 @@ namespace matnc {
 
 // ---------------------------------------------------------------------------
 // MFMA complex GEMM
+
+// An operand's staged element: an FP32 pair, or a half2 word (an FP16-stored
+// child) converted exactly to FP32 and multiplied by the instance's power of
+// two 2^e.
+template <bool H>
+struct FStage;
+template <>
+struct FStage<false> {
+  typedef f32x2 type;
+  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return gmem<const f32x2>(base)[i]; }
+  static __device__ __forceinline__ float2 val(type r, float) { return make_float2(r.x, r.y); }
+};
+template <>
+struct FStage<true> {
+  typedef uint32_t type;
+  static __device__ __forceinline__ type load(uint64_t base, uint32_t i) { return ldg_u32(base, i); }
+  static __device__ __forceinline__ float2 val(type r, float c) {
+    __half2 h;
+    __builtin_memcpy(&h, &r, 4);
+    const float2 v = __half22float2(h);
+    return make_float2(v.x * c, v.y * c);
+  }
+};
 
 // Tile: TM = 32*RM*WM values of m, TN = 16*RN*WN complex n, TK complex k.
 // FAN: the tile's TN columns are TN >> nbits slots of 2^nbits columns, one

@@ -22,7 +22,6 @@
 // tiles' columns hold an instance, 129 TFLOP/s of those.  Leaving out the empty
 // 16-column blocks by a condition in the k loop gave 4% there and cost 11% on
 // 22/1/6 bits, whose tiles are full; with a loop of its own the kernel spills.
-#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -58,13 +57,21 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
   return u;
 }
 
-__device__ __forceinline__ float2 scaled(float2 v) { return make_float2(v.x * kScale, v.y * kScale); }
+__device__ __forceinline__ f32x2 load_f2(uint64_t base, uint32_t i) { return gmem<const f32x2>(base)[i]; }
 
-template <int NP>
+// elements i (even) and i + 1
+__device__ __forceinline__ void load_f2x2(uint64_t base, uint32_t i, f32x2 (&r)[2]) {
+  const f32x4 v = *(gptr<const f32x4>)((gptr<const char>)base + 8 * i);
+  r[0] = f32x2{v.x, v.y};
+  r[1] = f32x2{v.z, v.w};
+}
+
+__device__ __forceinline__ float2 scaled(f32x2 v) { return make_float2(v.x * kScale, v.y * kScale); }
+
 __device__ __forceinline__ Split3 split3(float2 v) {
   Split3 s;
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
+  for (int p = 0; p < 3; ++p) {
     s.p[p] = pack_bf16(v.x, v.y);
     v.x -= __uint_as_float(s.p[p] << 16);
     v.y -= __uint_as_float(s.p[p] & 0xffff0000u);
@@ -76,18 +83,11 @@ __device__ __forceinline__ Split3 split3(float2 v) {
 // FAN: the tile's TN columns are TN >> nbits slots of 2^nbits columns, one
 // per output instance of a fan-table row (see NodeDesc); the A tile is
 // loaded once for all of them.
-// REC (fan tiles only): also record each output instance's largest
-// |component| into its scale slot (complex-half plans, whose FP32 branch
-// tensors feed FP16 steps): half-wave reductions and one LDS atomic per
-// slot column, one global atomic per slot and tile.
-// HA, HB (complex-half plans only): A, B stored in FP16 with a per-instance
-// exponent; the output is FP32 either way.
 // LIN (every plan step): A[m + (k << mbits)], B[n + (k << nbits)] -- a thread
 // loads two neighbouring m at once and every k row's address is a scalar step
 // from the last; otherwise (a caller's own layout) an offset per element.
-template <int RM, int RN, int WM, int WN, bool FAN, bool LIN, bool REC = false, bool HA = false, bool HB = false>
+template <int RM, int RN, int WM, int WN, bool FAN, bool LIN>
 __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
-  static_assert(!REC || FAN, "maxima are recorded by fan-out tiles only");
   static_assert(LIN || !FAN, "fan-out tiles are a plan's");
   constexpr int TK = 8;
   constexpr int NT = 64 * WM * WN;
@@ -103,23 +103,18 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   static_assert(QB % NT == 0 || NT % QB == 0, "B quads must split evenly over threads, or fit in fewer");
   constexpr int EQA = QA >= NT ? QA / NT : 1;
   constexpr int EQB = QB >= NT ? QB / NT : 1;
-  // parts of each operand (an FP16 value has 11 bits: two parts)
-  constexpr int PA = HA ? 2 : 3;
-  constexpr int PB = HB ? 2 : 3;
   // LDS tiles in the register layout of the MFMA operands, one plane per
   // part: As[k/4][m][k%4] holds A's (re, im) pairs; Bs[k/4][n][d][k%4] holds
   // B's rows of the real embedding, (re, -im) for d = 0 and (im, re) for d = 1
   constexpr int AQ = 4 * TM + 16;  // words per k quad (padded)
-  __shared__ __attribute__((aligned(16))) uint32_t As[2][PA][(TK / 4) * AQ];
-  __shared__ __attribute__((aligned(16))) uint32_t Bs[2][PB][(TK / 4) * TN * 8];
+  __shared__ __attribute__((aligned(16))) uint32_t As[2][3][(TK / 4) * AQ];
+  __shared__ __attribute__((aligned(16))) uint32_t Bs[2][3][(TK / 4) * TN * 8];
   // per-tile column data, shared by the waves instead of held per lane:
   // the C offset of each of the tile's TN columns, and for fan tiles the
   // B instance (byte offset) and output instance base of each slot
   __shared__ uint32_t s_cn[TN];
   __shared__ uint64_t s_bb[FAN ? TN : 1];
   __shared__ uint64_t s_cb[FAN ? TN : 1];
-  __shared__ uint32_t s_mx[REC ? TN : 1];  // per-slot maxima (float bits)
-  __shared__ float s_fb[(FAN && HB) ? TN : 1];  // per-slot factor 2^e of an FP16 B
   // offsets of a tile's first row and column: [AM, CM, BN, CN][nibble][value];
   // of a k step's change of bits 3 .. t: [AK, BK][t]
   __shared__ uint32_t s_nib[4][8][16];
@@ -200,8 +195,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
       for (int q = 0; q < 4; ++q) boff[e][q] = on_ + dep<TAB_BK>(d, 4, 4 * bkq[e] + q);
     }
   }
-  const uint64_t a_k = (uint64_t)(HA ? 4 : 8) << d.mbits;  // LIN: bytes from one k to the next
-  const uint64_t b_k = (uint64_t)(HB ? 4 : 8) << d.nbits;
+  const uint64_t a_k = 8ull << d.mbits;  // LIN: bytes from one k to the next
+  const uint64_t b_k = 8ull << d.nbits;
   uint32_t om[RM];  // output offsets of this lane's m values
 #pragma unroll
   for (int i = 0; i < RM; ++i) om[i] = dep<TAB_CM>(d, 8, (wm * RM + i) * 32 + l32);
@@ -242,32 +237,26 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
     const uint64_t oa0 = __builtin_amdgcn_readlane(first, 0), oc0 = (uint64_t)__builtin_amdgcn_readlane(first, 8) +
                                                                      (uint64_t)__builtin_amdgcn_readlane(first, 24);
     const uint64_t ob0 = __builtin_amdgcn_readlane(first, 16);
-    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes + oa0 * (HA ? 4 : 8);
-    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes + ob0 * (HB ? 4 : 8);
+    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes + oa0 * 8;
+    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes + ob0 * 8;
     const uint64_t c_off = d.ksplit ? d.part_off + (uint64_t)part * (uint64_t)d.n_inst * d.c_inst_bytes : d.c_off;
     const gptr<f32x2> pc = gmem<f32x2>(ws + c_off + inst * d.c_inst_bytes + oc0 * 8);
-    const float ca = HA ? ldexpf(1.f, ldg_scale(ws + d.A.scale_off, ai).e) : 1.f;
-    const float cb = HB ? ldexpf(1.f, ldg_scale(ws + d.B.scale_off, bi).e) : 1.f;
     if (FAN && tid < slots) {
       // an empty slot reads slot 0's B into columns that are never stored
       const int jg = fj[tid];
       const int64_t bg = operand_instance(d.B, glB, jg < 0 ? j : jg, s, sigma);
       s_bb[tid] = d.B.off + bg * d.B.inst_bytes;
       s_cb[tid] = jg < 0 ? 0 : c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes + oc0 * 8;
-      if (REC) s_mx[tid] = 0u;
-      if (HB) s_fb[tid] = ldexpf(1.f, ldg_scale(ws + d.B.scale_off, bg).e);
     }
     if (FAN) __syncthreads();  // the column data above is read by every wave
 
     uint64_t pak[LIN ? EQA : 1], pbe[EQB];  // LIN: next k row of each block; else the instance's start
-    float cbe[EQB];                         // factor (FP16 B)
     const uint32_t k0 = part * ((uint32_t)ksteps * TK);
 #pragma unroll
     for (int e = 0; e < EQB; ++e) {
-      pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] + (uint64_t)(bnn[e] & nmask) * (HB ? 4 : 8)
-                   : pb + (LIN ? (uint64_t)bnn[e] * (HB ? 4 : 8) : 0);
+      pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] + (uint64_t)(bnn[e] & nmask) * 8
+                   : pb + (LIN ? (uint64_t)bnn[e] * 8 : 0);
       if (LIN) pbe[e] += (uint64_t)(k0 + 4 * bkq[e]) * b_k;
-      cbe[e] = FAN ? (HB ? s_fb[bnn[e] >> d.nbits] : 1.f) : cb;
     }
     if constexpr (LIN) {
 #pragma unroll
@@ -280,8 +269,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
     }
     // (a second register stage, as the FP16 tiles have, costs a workgroup per CU:
     // 20/8/9 bits on the 128 x 64 tile 6.4 ms with one, 6.9 ms with two)
-    typename FStage<HA>::type ra[EQA][4][MA];
-    typename FStage<HB>::type rb[EQB][4];
+    f32x2 ra[EQA][4][MA];
+    f32x2 rb[EQB][4];
     auto gload = [&](int ks) {
       if constexpr (!LIN) {
         if (ks > 0) {
@@ -296,11 +285,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             if constexpr (LIN && MA == 2)
-              FStage<HA>::load2(pak[e] + q * a_k, (uint32_t)amm[e], ra[e][q]);
+              load_f2x2(pak[e] + q * a_k, (uint32_t)amm[e], ra[e][q]);
             else if constexpr (LIN)
-              ra[e][q][0] = FStage<HA>::load(pak[e] + q * a_k, (uint32_t)amm[e]);
+              ra[e][q][0] = load_f2(pak[e] + q * a_k, (uint32_t)amm[e]);
             else
-              ra[e][q][0] = FStage<HA>::load(pa, aoff[e][q] + kba);
+              ra[e][q][0] = load_f2(pa, aoff[e][q] + kba);
           }
       }
       if (bstage) {
@@ -309,9 +298,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             if constexpr (LIN)
-              rb[e][q] = FStage<HB>::load(pbe[e] + q * b_k, 0);
+              rb[e][q] = load_f2(pbe[e] + q * b_k, 0);
             else
-              rb[e][q] = FStage<HB>::load(pbe[e], boff[e][q] + kbb);
+              rb[e][q] = load_f2(pbe[e], boff[e][q] + kbb);
           }
       }
       if constexpr (LIN) {
@@ -329,9 +318,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
           for (int i = 0; i < MA; ++i) {
             Split3 v[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = split3<PA>(scaled(FStage<HA>::val(ra[e][q][i], ca)));
+            for (int q = 0; q < 4; ++q) v[q] = split3(scaled(ra[e][q][i]));
 #pragma unroll
-            for (int p = 0; p < PA; ++p)
+            for (int p = 0; p < 3; ++p)
               *reinterpret_cast<uint4*>(&As[buf][p][akq[e] * AQ + 4 * (amm[e] + i)]) =
                   make_uint4(v[0].p[p], v[1].p[p], v[2].p[p], v[3].p[p]);
           }
@@ -342,10 +331,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
         for (int e = 0; e < EQB; ++e) {
           Split3 v[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = split3<PB>(scaled(FStage<HB>::val(rb[e][q], cbe[e])));
+          for (int q = 0; q < 4; ++q) v[q] = split3(scaled(rb[e][q]));
           const int base = ((bkq[e] * TN + bnn[e]) * 2) * 4;
 #pragma unroll
-          for (int p = 0; p < PB; ++p) {
+          for (int p = 0; p < 3; ++p) {
             *reinterpret_cast<uint4*>(&Bs[buf][p][base]) =
                 make_uint4(v[0].p[p] ^ 0x80000000u, v[1].p[p] ^ 0x80000000u, v[2].p[p] ^ 0x80000000u,
                            v[3].p[p] ^ 0x80000000u);
@@ -377,41 +366,41 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
       // products of parts pa, pb with pa + pb <= 2, the smallest first; the
       // fragments of the side with fewer tiles are held, the others read in turn
       if constexpr (RM <= RN) {
-        bf16x8 yv[PA][RM];
+        bf16x8 yv[3][RM];
 #pragma unroll
-        for (int p = 0; p < PA; ++p)
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
           for (int i = 0; i < RM; ++i) yv[p][i] = afrag(p, i);
 #pragma unroll
         for (int q = 0; q < RN; ++q) {
-          bf16x8 xv[PB];
+          bf16x8 xv[3];
 #pragma unroll
-          for (int p = 0; p < PB; ++p) xv[p] = bfrag(p, q);
+          for (int p = 0; p < 3; ++p) xv[p] = bfrag(p, q);
 #pragma unroll
           for (int g = 2; g >= 0; --g)
 #pragma unroll
             for (int ap = 0; ap <= g; ++ap)
-              if (ap < PA && g - ap < PB)
+              if (ap < 3 && g - ap < 3)
 #pragma unroll
                 for (int i = 0; i < RM; ++i)
                   acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[g - ap], yv[ap][i], acc[i][q], 0, 0, 0);
         }
       } else {
-        bf16x8 xv[PB][RN];
+        bf16x8 xv[3][RN];
 #pragma unroll
-        for (int p = 0; p < PB; ++p)
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
           for (int q = 0; q < RN; ++q) xv[p][q] = bfrag(p, q);
 #pragma unroll
         for (int i = 0; i < RM; ++i) {
-          bf16x8 yv[PA];
+          bf16x8 yv[3];
 #pragma unroll
-          for (int p = 0; p < PA; ++p) yv[p] = afrag(p, i);
+          for (int p = 0; p < 3; ++p) yv[p] = afrag(p, i);
 #pragma unroll
           for (int g = 2; g >= 0; --g)
 #pragma unroll
             for (int ap = 0; ap <= g; ++ap)
-              if (ap < PA && g - ap < PB)
+              if (ap < 3 && g - ap < 3)
 #pragma unroll
                 for (int q = 0; q < RN; ++q)
                   acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[g - ap][q], yv[ap], acc[i][q], 0, 0, 0);
@@ -453,16 +442,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
         const int g = FAN ? nl >> d.nbits : 0;
         if (FAN && s_cb[g] == 0) continue;
         const uint64_t pbg = FAN ? ws + s_bb[g] : pb;
-        const float cbg = FAN ? (HB ? s_fb[g] : 1.f) : cb;
         const uint32_t oa = dep<TAB_AM>(d, 8, m);
         const uint32_t ob = dep<TAB_BN>(d, 8, FAN ? (nl & nmask) : nl);
         float2 c = make_float2(0.f, 0.f);
         for (uint32_t k = k0; k < k1; ++k)
-          cmac(c, FStage<HA>::val(FStage<HA>::load(pa, oa + dep<TAB_AK>(d, d.kbits, k)), ca),
-               FStage<HB>::val(FStage<HB>::load(pbg, ob + dep<TAB_BK>(d, d.kbits, k)), cbg));
+          cmac(c, ldg_f2(pa, oa + dep<TAB_AK>(d, d.kbits, k)), ldg_f2(pbg, ob + dep<TAB_BK>(d, d.kbits, k)));
         const gptr<f32x2> dst = FAN ? gmem<f32x2>(ws + s_cb[g]) : pc;
         dst[dep<TAB_CM>(d, 8, m) + s_cn[nl]] = f32x2{c.x, c.y};
-        if (REC) atomicMax(&s_mx[g], __float_as_uint(fmaxf(fmaxf(0.f, fabsf(c.x)), fabsf(c.y))));
       }
     } else {
       // epilogue: lane holds C[m][n] (re, im) in registers (r, r+1), r even
@@ -481,120 +467,73 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
             dst = gmem<f32x2>(ws + cbs);
           }
           const uint32_t ocn = s_cn[nl];
-          float v = 0.f;
 #pragma unroll
-          for (int i = 0; i < RM; ++i) {
-            const float2 c = make_float2(acc[i][q][r] * kUnscale, acc[i][q][r + 1] * kUnscale);
-            if (live) dst[om[i] + ocn] = f32x2{c.x, c.y};
-            if (REC) v = fmaxf(v, fmaxf(fabsf(c.x), fabsf(c.y)));
-          }
-          if (REC) {
-            // the half-wave's 32 lanes hold 32 values of m of one column
-#pragma unroll
-            for (int o = 16; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-            if (l32 == 0 && live) atomicMax(&s_mx[nl >> d.nbits], __float_as_uint(v));
-          }
+          for (int i = 0; i < RM; ++i)
+            if (live) dst[om[i] + ocn] = f32x2{acc[i][q][r] * kUnscale, acc[i][q][r + 1] * kUnscale};
         }
-      }
-    }
-    if (REC) {
-      __syncthreads();
-      if (tid < slots) {
-        const int jg = fj[tid];
-        if (jg >= 0 && s_mx[tid] > 0u) max_scale_mx(ws + d.c_scale_off, s * d.w + jg, s_mx[tid]);
       }
     }
     if (FAN) __syncthreads();  // the next tile rewrites the column data
   }
 }
 
-// Adds the copies of a split sum in order; REC: and records each instance's
-// largest |component|.
-template <bool REC>
+// Adds the copies of a split sum in order.
 __global__ __launch_bounds__(256) void k_split_add(NodeDesc d, uint64_t ws) {
-  const int eb = d.mbits + d.nbits;
-  const int64_t total = d.n_inst << eb;
+  const int64_t total = d.n_inst << (d.mbits + d.nbits);
   const int parts = 1 << d.ksplit;
   const uint64_t src = ws + d.part_off, dst = ws + d.c_off;
-  const int seg = eb >= 6 ? 64 : 1 << eb;
-  for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
-    const int64_t g = base + threadIdx.x;
-    float mx = 0.f;
-    if (g < total) {
-      float2 c = ldg_f2(src, g);
-      for (int p = 1; p < parts; p += 1) {
-        const float2 v = ldg_f2(src, (uint64_t)p * total + g);
-        c.x += v.x;
-        c.y += v.y;
-      }
-      stg_f2(dst, g, c);
-      mx = fmaxf(fabsf(c.x), fabsf(c.y));
+  for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < total; g += (int64_t)gridDim.x * 256) {
+    float2 c = ldg_f2(src, g);
+    for (int p = 1; p < parts; p += 1) {
+      const float2 v = ldg_f2(src, (uint64_t)p * total + g);
+      c.x += v.x;
+      c.y += v.y;
     }
-    if (REC) {
-      for (int o = seg >> 1; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-      if (g < total && (threadIdx.x & (seg - 1)) == 0 && mx > 0.f)
-        max_scale_mx(ws + d.c_scale_off, g >> eb, __float_as_uint(mx));
-    }
+    stg_f2(dst, g, c);
   }
 }
 
 // ---------------------------------------------------------------------------
 // launchers (the tile configurations are those of kernels_c64.hip)
 
-template <bool FAN, bool LIN, bool REC, bool HA, bool HB>
+template <bool FAN, bool LIN>
 static hipError_t launch_split_s(const NodeDesc& d, int cfg, unsigned grid, uint64_t ws, const int64_t* sig,
                                 hipStream_t st) {
   switch (cfg) {
-    case 0: hipLaunchKernelGGL((k_split<2, 1, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 1: hipLaunchKernelGGL((k_split<2, 2, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 2: hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 3: hipLaunchKernelGGL((k_split<4, 1, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 4: hipLaunchKernelGGL((k_split<4, 2, 2, 2, FAN, LIN, REC, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 0: hipLaunchKernelGGL((k_split<2, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 1: hipLaunchKernelGGL((k_split<2, 2, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 2: hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 3: hipLaunchKernelGGL((k_split<4, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 4: hipLaunchKernelGGL((k_split<4, 2, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
     case 5:
       if (FAN) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_split<2, 4, 2, 2, false, LIN, false, HA, HB>), dim3(grid), dim3(256), 0, st, d, ws, sig);
+      hipLaunchKernelGGL((k_split<2, 4, 2, 2, false, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig);
       break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <bool FAN, bool REC = false>
+template <bool FAN>
 static hipError_t launch_split_t(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st) {
   if (d.n_inst == 0) return hipSuccess;
   const bool fits = FAN ? mfma_fan_config_fits(cfg, d.mbits, d.nbits, d.kbits, d.fan_tn)
                         : mfma_config_fits(cfg, d.mbits, d.nbits, d.kbits);
-  if (!fits || (FAN && (d.w <= 0 || d.n_fan <= 0))) return hipErrorInvalidValue;
+  if (!fits || (FAN && (d.w <= 0 || d.n_fan <= 0)) || d.A.half || d.B.half) return hipErrorInvalidValue;
   const int64_t units = FAN ? (d.n_inst / d.w) * d.n_fan : d.n_inst;
   const int tbits = d.mbits - mfma_config_tm_bits(cfg) + (FAN ? 0 : d.nbits - mfma_config_tn_bits(cfg));
   // persistent: see the in-tile offsets; 2048 workgroups as for the FP16 tiles
   const unsigned grid = (unsigned)std::min<int64_t>((units << tbits) << d.ksplit, 2048);
-  // FP16-stored operands occur only in complex-half plans
   hipError_t e;
-  const bool ks = d.ksplit > 0;  // the copies' sum records the maxima then
-  if (!d.linear) {  // a caller's own layout
-    if (FAN || REC || d.A.half || d.B.half) return hipErrorInvalidValue;
-    e = launch_split_s<false, false, false, false, false>(d, cfg, grid, ws, sig, st);
-  } else if (d.A.half) {
-    if (d.B.half)
-      e = REC && !ks ? launch_split_s<FAN, true, REC, true, true>(d, cfg, grid, ws, sig, st)
-                     : launch_split_s<FAN, true, false, true, true>(d, cfg, grid, ws, sig, st);
-    else
-      e = REC && !ks ? launch_split_s<FAN, true, REC, true, false>(d, cfg, grid, ws, sig, st)
-                     : launch_split_s<FAN, true, false, true, false>(d, cfg, grid, ws, sig, st);
-  } else if (d.B.half) {
-    e = REC && !ks ? launch_split_s<FAN, true, REC, false, true>(d, cfg, grid, ws, sig, st)
-                   : launch_split_s<FAN, true, false, false, true>(d, cfg, grid, ws, sig, st);
-  } else {
-    e = REC && !ks ? launch_split_s<FAN, true, REC, false, false>(d, cfg, grid, ws, sig, st)
-                   : launch_split_s<FAN, true, false, false, false>(d, cfg, grid, ws, sig, st);
-  }
-  if (e != hipSuccess || !ks) return e;
+  if (d.linear)
+    e = launch_split_s<FAN, true>(d, cfg, grid, ws, sig, st);
+  else if (FAN)
+    e = hipErrorInvalidValue;
+  else  // a caller's own layout
+    e = launch_split_s<false, false>(d, cfg, grid, ws, sig, st);
+  if (e != hipSuccess || !d.ksplit) return e;
   const unsigned g2 = grid_for(((d.n_inst << (d.mbits + d.nbits)) + 255) / 256);
-  if (REC)
-    hipLaunchKernelGGL((k_split_add<true>), dim3(g2), dim3(256), 0, st, d, ws);
-  else
-    hipLaunchKernelGGL((k_split_add<false>), dim3(g2), dim3(256), 0, st, d, ws);
+  hipLaunchKernelGGL(k_split_add, dim3(g2), dim3(256), 0, st, d, ws);
   return hipGetLastError();
 }
 
@@ -615,10 +554,6 @@ hipError_t launch_split(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* 
 
 hipError_t launch_split_fan(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st) {
   return launch_split_t<true>(d, cfg, ws, sig, st);
-}
-
-hipError_t launch_split_fan_rec(const NodeDesc& d, int cfg, uint64_t ws, const int64_t* sig, hipStream_t st) {
-  return launch_split_t<true, true>(d, cfg, ws, sig, st);
 }
 
 }  // namespace matnc

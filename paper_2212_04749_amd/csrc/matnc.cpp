@@ -102,17 +102,6 @@ constexpr uint64_t kAlign = 256;
 constexpr int64_t kAmpsPerHalfNode = 282;
 constexpr int kMaxHalfNodes = 16;
 
-// FP32-stored steps run on the split-bfloat16 kernel (kernels_split.hip),
-// which is faster and nearer to the 64-bit result than the FP32 instruction,
-// except in complex-half plans with more than this many FP16 tensors.  There a
-// change in an FP32 value's last bit decides some of the FP16 roundings after
-// it, each of which decides more of the next ones: after three or four FP16
-// tensors in a row every rounding is another one, and the amplitudes differ
-// from those of the FP32 instruction by the format's own error (1e-3; the
-// linear XEB by 4e-5) with no gain in accuracy.  Such plans keep the
-// instruction, so that their results stay the same bit for bit.
-constexpr int kMaxHalfSplit = 2;
-
 // Steps fused into one workgroup's subtree: up to 2^16 complex multiply-adds
 // (about 3 us there; a launch of its own costs 5 us and more), tensors of up
 // to 32 KiB.
@@ -376,7 +365,13 @@ void build_steps(Plan& P) {
     P.nodes[v].half_store = half[v] != 0;
     P.n_half += half[v] ? 1 : 0;
   }
-  P.split = P.n_half <= kMaxHalfSplit;
+  // FP32-stored steps run on the split-bfloat16 kernel (kernels_split.hip) except
+  // in plans that store a tensor in FP16.  There the last bit of an FP32 value
+  // decides some of the FP16 roundings after it, so another order of additions
+  // moves amplitudes by the format's own error (1e-4 after one FP16 tensor, 1e-3
+  // after four) with no gain in accuracy: such plans keep the FP32 instruction
+  // and its order of additions, and with them every bit of their results.
+  P.split = P.n_half == 0;
   for (int v = nt; v < P.n_nodes; ++v) {
     PNode& V = P.nodes[v];
     const bool hm = V.half_store;  // FP16 output: FP16-product MFMA kernels
@@ -1180,7 +1175,7 @@ void launch_node(const Plan& P, const PNode& V, const NodeDesc& d, hipStream_t s
     // raises their register use and cuts the occupancy)
     if (V.fan) {
       if (P.split)
-        e = V.rec_max ? launch_split_fan_rec(d, V.cfg, P.ws, sig, st) : launch_split_fan(d, V.cfg, P.ws, sig, st);
+        e = launch_split_fan(d, V.cfg, P.ws, sig, st);
       else
         e = V.rec_max ? launch_mfma_fan_rec(d, V.cfg, P.ws, sig, st) : launch_mfma_fan(d, V.cfg, P.ws, sig, st);
     } else {
