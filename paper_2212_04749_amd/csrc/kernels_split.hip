@@ -1,27 +1,37 @@
 // Matrix-core kernel of the FP32-stored steps (gfx950): C[m, n] = sum_k
 // A[m, k] B[k, n] as a complex GEMM whose FP32 operands are split exactly into
 // three bfloat16 parts each (8 + 8 + 8 of the 24 bits; bfloat16 has FP32's
-// exponent range, so one constant factor serves every operand).  Of the nine products of parts
-// the six with index sum <= 2 are summed on v_mfma_f32_32x32x16_bf16 in FP32;
-// the three left out are below 2^-25 of the product.  The FP32 instruction
-// (v_mfma_f32_32x32x2f32, kernels_c64.hip) rounds the accumulator once per
-// two real products; here it is rounded six times per sixteen, so the result
-// is also nearer to the 64-bit one: relative error on normal operands
-// 3.4e-8, 1.1e-7, 2.4e-7, 4.9e-7, 7.0e-7 at 3, 5, 7, 9, 10 k bits, against
-// 7.4e-8, 1.4e-7, 2.9e-7, 5.7e-7, 8.1e-7.
+// exponent range, so one constant factor serves every operand).  Of the nine
+// products of parts the eight with index sum <= 3 are summed on
+// v_mfma_f32_32x32x16_bf16; the ninth is below 2^-33 of the product.
 //
-// Bound: six bfloat16 products take 192 matrix-core cycles per 32 x 16 x 8
+// Accuracy.  The instruction drops what lies below the last bit of a nonzero
+// accumulator at each addition (up to one unit of the last place, not half).
+// The products of first parts, which are exact, have an accumulator of their
+// own, so a sum of K products meets that once per eight complex k; the seven
+// others add up in a second one 2^-8 as large, and the two are added once at the
+// end.  The FP32 instruction (v_mfma_f32_32x32x2f32, kernels_c64.hip) rounds
+// for every product.  Relative error against 64 bits at 3, 5, 7, 9, 10 k bits,
+// that instruction and this kernel: normal operands 7.4e-8, 1.5e-7, 2.9e-7,
+// 5.7e-7, 8.1e-7 and 3.2e-8, 4.9e-8, 8.9e-8, 1.9e-7, 2.7e-7; one product per
+// sum, real, 2.5e-8 (at most 5.9e-8) in both; gate-like operands (zeros, +-i,
+// cosines) 3.8e-8 .. 4.1e-7 and 2.5e-8 .. 2.1e-7; positive ones 4.7e-8 .. 4.9e-7
+// and 2.8e-8 .. 2.5e-7.  (Six products in one accumulator, which this was
+// before, left out 2^-24 of a product and rounded at full size six times per eight k: 3.5e-8, at most
+// 1.4e-7, on single products, twice the instruction's error on sparse sums.)
+//
+// Bound: eight bfloat16 products take 256 matrix-core cycles per 32 x 16 x 8
 // complex block, the FP32 instruction 512.  At 20/8/9 bits of m/n/k the step
-// runs 5.30 to 5.56 ms (198 to 208 TFLOP/s complex, 1190 to 1250 of bfloat16;
-// a large bfloat16 library product reaches 1107 on this card under its power
-// limit) against 9.1 ms for the FP32 instruction's tile.  At 22/6/6 bits the
-// step is bound by its 17 GB instead (4.4 TB/s of the 5.1 of a copy).
+// runs 7.34 ms (150 TFLOP/s complex, 1200 of bfloat16; a large bfloat16 library
+// product reaches 1107 on this card under its power limit) against 8.60 ms for
+// the FP32 instruction's best tile and 9.04 for the one that it chose.  At
+// 22/6/6 bits, 17 GB, 1.28 ms against 1.37.
 //
 // Fan-out tiles whose groups do not fill them multiply empty columns: at
 // 10/3/11 bits (8 instances on average share an A) 0.70 of the 64-column
-// tiles' columns hold an instance, 129 TFLOP/s of those.  Leaving out the empty
-// 16-column blocks by a condition in the k loop gave 4% there and cost 11% on
-// 22/1/6 bits, whose tiles are full; with a loop of its own the kernel spills.
+// tiles' columns hold an instance.  Leaving out the empty 16-column blocks by a
+// condition in the k loop gave 4% there and cost 11% on 22/1/6 bits, whose
+// tiles are full; with a loop of its own the kernel spills.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -93,10 +103,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = 32 * RM * WM;
   constexpr int TN = 16 * RN * WN;
-  // m per block of A: two where every thread then still has a block, or where
-  // registers are short (128 x 128); with half of the threads idle the smaller
-  // tiles lose 10-15% to it
-  constexpr int MA = LIN && (TM == 256 || TN == 128) ? 2 : 1;
+  // m per block of A: two where every thread then still has a block; with half
+  // of the threads idle tiles lose 7-15% to it
+  constexpr int MA = LIN && TM == 256 && NT == 256 ? 2 : 1;
   constexpr int QA = (TK / 4) * TM / MA;  // blocks of four consecutive k of the A tile
   constexpr int QB = (TK / 4) * TN;  // ... and of the B tile
   static_assert(QA % NT == 0 || NT % QA == 0, "A quads must split evenly over threads, or fit in fewer");
@@ -348,13 +357,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
       }
     };
 
-    floatx16 acc[RM][RN];
+    floatx16 acc[RM][RN], low[RM][RN];
 #pragma unroll
     for (int i = 0; i < RM; ++i)
 #pragma unroll
       for (int q = 0; q < RN; ++q)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][q][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[i][q][r] = low[i][q][r] = 0.f;
 
     auto kstep = [&](int buf) {
       auto afrag = [&](int p, int i) {
@@ -363,47 +372,44 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
       auto bfrag = [&](int p, int q) {
         return *reinterpret_cast<const bf16x8*>(&Bs[buf][p][((half * TN + (wn * RN + q) * 16 + ncol) * 2 + dsel) * 4]);
       };
-      // products of parts pa, pb with pa + pb <= 2, the smallest first; the
-      // fragments of the side with fewer tiles are held, the others read in turn
+      // products of parts pa, pb with pa + pb <= 3: those of the first parts into
+      // acc, the others, smallest first, into low; the fragments of the side
+      // with fewer tiles are held, the others read in turn
+      auto tile = [&](floatx16& a, floatx16& lo, const bf16x8(&x)[3], const bf16x8(&y)[3]) {
+#pragma unroll
+        for (int g = 3; g >= 1; --g)
+#pragma unroll
+          for (int ap = g == 3 ? 1 : 0; ap <= (g == 3 ? 2 : g); ++ap)
+            lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g - ap], y[ap], lo, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], a, 0, 0, 0);
+      };
       if constexpr (RM <= RN) {
-        bf16x8 yv[3][RM];
+        bf16x8 yv[RM][3];
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+        for (int i = 0; i < RM; ++i)
 #pragma unroll
-          for (int i = 0; i < RM; ++i) yv[p][i] = afrag(p, i);
+          for (int p = 0; p < 3; ++p) yv[i][p] = afrag(p, i);
 #pragma unroll
         for (int q = 0; q < RN; ++q) {
           bf16x8 xv[3];
 #pragma unroll
           for (int p = 0; p < 3; ++p) xv[p] = bfrag(p, q);
 #pragma unroll
-          for (int g = 2; g >= 0; --g)
-#pragma unroll
-            for (int ap = 0; ap <= g; ++ap)
-              if (ap < 3 && g - ap < 3)
-#pragma unroll
-                for (int i = 0; i < RM; ++i)
-                  acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[g - ap], yv[ap][i], acc[i][q], 0, 0, 0);
+          for (int i = 0; i < RM; ++i) tile(acc[i][q], low[i][q], xv, yv[i]);
         }
       } else {
-        bf16x8 xv[3][RN];
+        bf16x8 xv[RN][3];
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+        for (int q = 0; q < RN; ++q)
 #pragma unroll
-          for (int q = 0; q < RN; ++q) xv[p][q] = bfrag(p, q);
+          for (int p = 0; p < 3; ++p) xv[q][p] = bfrag(p, q);
 #pragma unroll
         for (int i = 0; i < RM; ++i) {
           bf16x8 yv[3];
 #pragma unroll
           for (int p = 0; p < 3; ++p) yv[p] = afrag(p, i);
 #pragma unroll
-          for (int g = 2; g >= 0; --g)
-#pragma unroll
-            for (int ap = 0; ap <= g; ++ap)
-              if (ap < 3 && g - ap < 3)
-#pragma unroll
-                for (int q = 0; q < RN; ++q)
-                  acc[i][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv[g - ap][q], yv[ap], acc[i][q], 0, 0, 0);
+          for (int q = 0; q < RN; ++q) tile(acc[i][q], low[i][q], xv[q], yv);
         }
       }
     };
@@ -433,7 +439,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
 #pragma unroll
       for (int q = 0; q < RN; ++q)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) fin = fmaf(acc[i][q][r], 0.f, fin);
+        for (int r = 0; r < 16; ++r) {
+          acc[i][q][r] += low[i][q][r];
+          fin = fmaf(acc[i][q][r], 0.f, fin);
+        }
     if (__any(fin != 0.f)) {
       const uint32_t k1 = k0 + (uint32_t)ksteps * TK;
       for (int e = lane; e < 32 * RM * 16 * RN; e += 64) {
@@ -494,7 +503,8 @@ __global__ __launch_bounds__(256) void k_split_add(NodeDesc d, uint64_t ws) {
 }
 
 // ---------------------------------------------------------------------------
-// launchers (the tile configurations are those of kernels_c64.hip)
+// launchers (the tile configurations are those of kernels_c64.hip; the two of
+// 2^13 elements take eight waves, whose four tiles each leave room for both accumulators)
 
 template <bool FAN, bool LIN>
 static hipError_t launch_split_s(const NodeDesc& d, int cfg, unsigned grid, uint64_t ws, const int64_t* sig,
@@ -504,10 +514,10 @@ static hipError_t launch_split_s(const NodeDesc& d, int cfg, unsigned grid, uint
     case 1: hipLaunchKernelGGL((k_split<2, 2, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
     case 2: hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
     case 3: hipLaunchKernelGGL((k_split<4, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 4: hipLaunchKernelGGL((k_split<4, 2, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 4: hipLaunchKernelGGL((k_split<2, 2, 4, 2, FAN, LIN>), dim3(grid), dim3(512), 0, st, d, ws, sig); break;
     case 5:
       if (FAN) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_split<2, 4, 2, 2, false, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig);
+      hipLaunchKernelGGL((k_split<2, 2, 2, 4, false, LIN>), dim3(grid), dim3(512), 0, st, d, ws, sig);
       break;
     default: return hipErrorInvalidValue;
   }
