@@ -97,7 +97,7 @@ struct HalfScale {
 // Fused subtrees of small steps (kernels_tree.hip): a table of n_comp + 1
 // word offsets, then each component's words: TreeHeader, the inputs, the
 // steps, level starts (n_levels + 1 positions in the item list), the items
-// (step << 16 | 64-output chunk) and the gather maps.  Offsets in the header
+// (step << 16 | chunk of 64 >> cut outputs) and the gather maps.  Offsets in the header
 // and in TreeStep::gmap count words from the component's first.
 constexpr int kTreeThreads = 1024;
 constexpr int kTreeWords = 6 * 1024;    // 24 KiB of description
@@ -117,7 +117,7 @@ struct TreeInput {
 };
 
 struct TreeStep {
-  uint32_t bits;            // m | n << 8 | k << 16 | (result to the arena) << 24
+  uint32_t bits;            // m | n << 8 | k << 16 | (result to the arena) << 24 | cut << 25: 2^cut lanes share a sum
   uint32_t outputs;         // w << (m + n)
   uint32_t a, b;            // operands' first elements in LDS: (k, m) and (k, n), k highest
   uint32_t c_lo, c_hi;      // LDS element, or byte offset in the workspace

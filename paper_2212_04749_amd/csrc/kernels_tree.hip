@@ -59,9 +59,10 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(uint64_t ws, uint64_t tab
   for (uint32_t l = 0; l < h.n_levels; ++l) {
     const uint32_t i1 = word(h.levels + l + 1);
     for (uint32_t i = word(h.levels + l) + wave; i < i1; i += kTreeThreads / 64) {
-      const uint32_t item = word(h.items + i);  // step << 16 | 64-output chunk
+      const uint32_t item = word(h.items + i);  // step << 16 | chunk of outputs
       const TreeStep t = *reinterpret_cast<const TreeStep*>(words + h.steps + (item >> 16) * (sizeof(TreeStep) / 4));
-      const uint32_t o = (item & 0xffffu) * 64 + lane;
+      const uint32_t cut = t.bits >> 25, ob = 6 - cut;  // 2^cut lanes share a sum
+      const uint32_t o = ((item & 0xffffu) << ob) + (lane & ((1u << ob) - 1u));
       if (o >= t.outputs) continue;
       const uint32_t mb = t.bits & 0xffu, nb = (t.bits >> 8) & 0xffu, kb = (t.bits >> 16) & 0xffu;
       const uint32_t j = o >> (mb + nb);
@@ -71,18 +72,41 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(uint64_t ws, uint64_t tab
       const float2* a = data + t.a + (ga << (mb + kb)) + m;
       const float2* b = data + t.b + (gb << (nb + kb)) + n;
       float2 c = make_float2(0.f, 0.f);
-      uint32_t k = 0;
-      for (; k + 4 <= (1u << kb); k += 4) {
-        float2 av[4], bv[4];
+      if (kb > 4) {
+        // long sums: every 2^cut-th k to a lane, four of them at a time summed
+        // on their own, the lanes' sums in a tree
+        const uint32_t k1 = 1u << kb;
+        for (uint32_t k = lane >> ob; k < k1; k += 4u << cut) {
+          float2 av[4], bv[4], g4 = make_float2(0.f, 0.f);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          av[u] = a[(k + u) << mb];
-          bv[u] = b[(k + u) << nb];
+          for (int u = 0; u < 4; ++u) {
+            av[u] = a[(k + ((uint32_t)u << cut)) << mb];
+            bv[u] = b[(k + ((uint32_t)u << cut)) << nb];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) cmac(g4, av[u], bv[u]);
+          c.x += g4.x;
+          c.y += g4.y;
         }
+        for (uint32_t x = 32; x >> ob; x >>= 1) {
+          c.x += __shfl_xor(c.x, (int)x);
+          c.y += __shfl_xor(c.y, (int)x);
+        }
+      } else {
+        uint32_t k = 0;
+        for (; k + 4 <= (1u << kb); k += 4) {
+          float2 av[4], bv[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) cmac(c, av[u], bv[u]);
+          for (int u = 0; u < 4; ++u) {
+            av[u] = a[(k + u) << mb];
+            bv[u] = b[(k + u) << nb];
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) cmac(c, av[u], bv[u]);
+        }
+        for (; k < (1u << kb); ++k) cmac(c, a[k << mb], b[k << nb]);
       }
-      for (; k < (1u << kb); ++k) cmac(c, a[k << mb], b[k << nb]);
+      if (lane >> ob) continue;
       uint32_t oc = 0;
 #pragma unroll
       for (int q = 0; q < 3; ++q)
@@ -90,7 +114,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(uint64_t ws, uint64_t tab
         for (int e = 0; e < 4; ++e) oc |= ((o >> (4 * q + e)) & (4 * q + e < (int)(mb + nb) ? 1u : 0u))
                                          << ((t.pos[q] >> (8 * e)) & 31u);
       const uint32_t inst = (j << (mb + nb)) + oc;
-      if (t.bits >> 24) {  // a component's result goes to the arena
+      if ((t.bits >> 24) & 1u) {  // a component's result goes to the arena
         const uint64_t off = (uint64_t)t.c_lo | ((uint64_t)t.c_hi << 32);
         stg_f2(ws + off, (((uint64_t)s * t.w) << (mb + nb)) + inst, c);
       } else {

@@ -530,6 +530,22 @@ void build_steps(Plan& P) {
   }
 }
 
+// log2 of the lanes that share one sum of a fused step: where the step's
+// outputs (all keys, so that key chunks do not change the order of additions)
+// leave lanes of the workgroup idle, these take a share of sums of more than
+// 16 products.  The rest of a lane's sum is at most 64 products, four at a time
+// on their own.  0/0/10 bits x 4: 1.0e-7 from 64 bits (the long-sum kernel
+// 2.9e-7, one lane in one chain 6.9e-7) in 10.0 us (10.8 and 36.8); 0/0/12: 15.5 us
+// (13.8 and 126).
+int tree_cut(const PNode& V) {
+  const int kb = (int)V.K.size();
+  int cut = 0;
+  if (kb > 4)
+    while (cut < 6 && cut < kb - 2 && ((uint64_t)V.keys.size() << (V.M.size() + V.N.size() + cut + 1)) <= kTreeThreads)
+      ++cut;
+  return cut;
+}
+
 // Marks the steps that run inside fused subtrees (kernels_tree.hip): small
 // steps all of whose operands are leaves, slice-invariant tensors read by a
 // slice-dependent step, or fused steps themselves, as long as everything the
@@ -547,13 +563,14 @@ void mark_fused(Plan& P) {
     if (V.half_store || V.rec_max || w > kFuseKeys || mb + nb > kTreeMaxBits) continue;
     if (elems(v) > kFuseElems || elems(V.a) > kFuseElems || elems(V.b) > kFuseElems) continue;
     if ((w << (mb + nb + kb)) > kFuseMacs) continue;
-    // A step that would else run on the matrix cores or as a long sum adds in
-    // another order here; it is fused only where it always is: not where key
+    // A step that would else run on the matrix cores or as a long sum (tree_cut)
+    // adds in another order here; it is fused only where it always is: not where key
     // chunks may move it out of the prologue, nor where that order must stay.
     if ((V.kernel == 1 || kb > 4) && (!P.split || !(V.dep || w == 1))) continue;
     if (!V.linear) continue;
     bool ok = true;
-    uint64_t h = elems(v), wd = sizeof(TreeStep) / 4 + w + (((w << (mb + nb)) + 63) / 64) + 1;
+    const uint64_t chunk = 64u >> tree_cut(V);  // outputs per item
+    uint64_t h = elems(v), wd = sizeof(TreeStep) / 4 + w + (((w << (mb + nb)) + chunk - 1) / chunk) + 1;
     for (int c : {V.a, V.b}) {
       const PNode& C = P.nodes[c];
       if (c >= nt && C.half_store) ok = false;
@@ -740,7 +757,8 @@ std::vector<uint32_t> tree_words(const Plan& P, const Tree& T, int c) {
       std::memset(&t, 0, sizeof(t));
       const uint32_t mb = (uint32_t)V.M.size(), nb = (uint32_t)V.N.size(), kb = (uint32_t)V.K.size();
       t.w = width(v);
-      t.bits = mb | nb << 8 | kb << 16 | (V.in_lds ? 0u : 1u << 24);
+      const uint32_t cut = (uint32_t)tree_cut(V);
+      t.bits = mb | nb << 8 | kb << 16 | (V.in_lds ? 0u : 1u << 24) | cut << 25;
       t.outputs = t.w << (mb + nb);
       t.a = lds[ca];
       t.b = lds[cb];
@@ -765,7 +783,7 @@ std::vector<uint32_t> tree_words(const Plan& P, const Tree& T, int c) {
         t.pos[q >> 2] |= (uint32_t)(uint8_t)(q < mb ? V.pos[TAB_CM][q] : V.pos[TAB_CN][q - mb]) << (8 * (q & 3));
       level[v] = std::max(level[ca], level[cb]) + 1;
       if ((int)levels.size() <= level[v]) levels.resize(level[v] + 1);
-      for (uint32_t o = 0; o < (t.outputs + 63) / 64; ++o)
+      for (uint32_t o = 0; (o << (6 - cut)) < t.outputs; ++o)
         levels[level[v]].push_back((uint32_t)desc.size() << 16 | o);
       desc.push_back(t);
     }
