@@ -103,9 +103,11 @@ constexpr int kTreeThreads = 1024;
 constexpr int kTreeWords = 6 * 1024;    // 24 KiB of description
 constexpr int kTreeElems = 16 * 1024;   // 128 KiB of tensors
 constexpr int kTreeMaxBits = 12;        // output bits of one instance
+constexpr int kTreeBig = 256;           // elements of an input that a wave loads at once
 
 struct TreeHeader {
   uint32_t n_levels, n_inputs, inputs, steps, levels, items;
+  uint32_t n_big;           // the first inputs: more than kTreeBig elements, copied by all waves
 };
 
 struct TreeInput {

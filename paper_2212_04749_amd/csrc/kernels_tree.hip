@@ -40,8 +40,10 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(uint64_t ws, uint64_t tab
   h.steps = word(3);
   h.levels = word(4);
   h.items = word(5);
-  // inputs: one wave each in turn
-  for (uint32_t i = wave; i < h.n_inputs; i += kTreeThreads / 64) {
+  h.n_big = word(6);
+  // inputs: the large ones by all waves together, of the others one to a wave
+  // (a 32 KiB tensor is 64 loads of a wave, one after another: 10 us)
+  auto copy = [&](uint32_t i, uint32_t first, uint32_t step) {
     const uint32_t at = h.inputs + i * (sizeof(TreeInput) / 4);
     const TreeInput in = *reinterpret_cast<const TreeInput*>(words + at);
     uint64_t sub = 0;
@@ -49,12 +51,22 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(uint64_t ws, uint64_t tab
       sub |= (uint64_t)((sigma >> ((words[at + 6 + (t >> 2)] >> (8 * (t & 3))) & 0xffu)) & 1) << t;
     const uint32_t emask = (1u << in.ebits) - 1u, n = in.keys << in.ebits;
     const uint64_t off = (uint64_t)in.off_lo | ((uint64_t)in.off_hi << 32);
-    for (uint32_t e = lane; e < n; e += 64) {
-      // instance key * 2^nsb + sub of the leaf (nsb = 0: a tensor without sliced indices)
-      const uint64_t inst = ((uint64_t)(e >> in.ebits) << in.nsb) + sub;
-      data[in.lds + e] = ldg_f2(ws + off, (inst << in.ebits) + (e & emask));
+    for (uint32_t e0 = first; e0 < n; e0 += 4 * step) {
+      float2 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t e = e0 + u * step;
+        // instance key * 2^nsb + sub of the leaf (nsb = 0: a tensor without sliced indices)
+        const uint64_t inst = ((uint64_t)(e >> in.ebits) << in.nsb) + sub;
+        if (e < n) v[u] = ldg_f2(ws + off, (inst << in.ebits) + (e & emask));
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (e0 + u * step < n) data[in.lds + e0 + u * step] = v[u];
     }
-  }
+  };
+  for (uint32_t i = 0; i < h.n_big; ++i) copy(i, tid, kTreeThreads);
+  for (uint32_t i = h.n_big + wave; i < h.n_inputs; i += kTreeThreads / 64) copy(i, lane, 64);
   __syncthreads();
   for (uint32_t l = 0; l < h.n_levels; ++l) {
     const uint32_t i1 = word(h.levels + l + 1);

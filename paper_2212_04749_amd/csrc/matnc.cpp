@@ -535,7 +535,7 @@ void build_steps(Plan& P) {
 // leave lanes of the workgroup idle, these take a share of sums of more than
 // 16 products.  The rest of a lane's sum is at most 64 products, four at a time
 // on their own.  0/0/10 bits x 4: 1.0e-7 from 64 bits (the long-sum kernel
-// 2.9e-7, one lane in one chain 6.9e-7) in 10.0 us (10.8 and 36.8); 0/0/12: 15.5 us
+// 2.9e-7, one lane in one chain 6.9e-7) in 7.1 us (10.8 and 36.8); 0/0/12: 8.5 us
 // (13.8 and 126).
 int tree_cut(const PNode& V) {
   const int kb = (int)V.K.size();
@@ -790,6 +790,9 @@ std::vector<uint32_t> tree_words(const Plan& P, const Tree& T, int c) {
     TreeHeader h;
     h.n_levels = (uint32_t)levels.size();
     h.n_inputs = (uint32_t)inputs.size();
+    h.n_big = (uint32_t)(std::stable_partition(inputs.begin(), inputs.end(), [](const TreeInput& in) {
+                           return (in.keys << in.ebits) > (uint32_t)kTreeBig;
+                         }) - inputs.begin());
     h.inputs = sizeof(TreeHeader) / 4;
     h.steps = h.inputs + (uint32_t)(inputs.size() * sizeof(TreeInput) / 4);
     h.levels = h.steps + (uint32_t)(desc.size() * sizeof(TreeStep) / 4);
