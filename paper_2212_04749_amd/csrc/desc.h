@@ -67,6 +67,7 @@ struct NodeDesc {
   // that instance is too large for the caches
   int32_t fan_rows;
   int32_t flat;          // 1: output instance i reads instance i of A and of B (no gather map, no slices)
+  int32_t s0;            // split sums: slices of the batch before this launch's first one
   // Instances that the choice of an order of additions goes by: a plan's keys
   // of the node, whatever the slice batch or key chunk of this launch, so that
   // results do not depend on how slices and keys are grouped

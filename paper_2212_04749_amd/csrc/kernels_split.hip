@@ -140,7 +140,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   const int nt_bits = FAN ? 0 : d.nbits - __builtin_ctz(TN);
   const int tbits = d.mbits - __builtin_ctz(TM) + nt_bits;  // tiles per unit = 2^tbits
   const int ksteps = 1 << (d.kbits - d.ksplit - __builtin_ctz(TK));  // of this part
-  const int64_t sigma0 = d.flat ? 0 : sig[0];
+  const int64_t sigma0 = d.flat ? 0 : sig[0] + d.s0;
   // work units: output instances, or (slice, fan row) pairs
   const uint32_t units = (uint32_t)(FAN ? ((uint32_t)d.n_inst / (uint32_t)d.w) * (uint32_t)d.n_fan : d.n_inst);
   const uint32_t upart = units << tbits;  // tiles of one part of the sum

@@ -114,8 +114,8 @@ constexpr uint64_t kFuseKeys = 1024;
 constexpr int64_t kTreeBatch = 1024;
 constexpr uint64_t kTreeBatchBytes = 16ull << 20;
 
-// largest region, per slice, for the parts of split sums: 1024 tiles' worth of
-// parts of the 64 KiB tiles
+// largest region for the parts of a split sum: 1024 tiles' worth of parts of the
+// 64 KiB tiles; a step whose slice batch needs more runs it in several launches
 constexpr uint64_t kMaxPartBytes = 64ull << 20;
 
 // bytes per stored element of node v: complex64 (8) unless the plan is
@@ -827,6 +827,7 @@ struct ArenaBuf {
   int node;
   uint64_t size;
   int t0, t1;
+  bool parts = false;  // the parts of the node's split sum, not its result
 };
 
 // the one kernel that looks offsets up instead of depositing bits: k_mfma
@@ -982,9 +983,9 @@ void build_memory_for(Plan& P, int n_chunks) {
   // and the root's instances allow (the caller's slice batch is sized for
   // intermediates, which such slices keep in LDS).
   P.tree_batch = 0;
-  if (P.wide_batch && P.loop.empty() && !P.loop_tree.roots.empty() && n_chunks == 1) {
+  if (P.loop.empty() && !P.loop_tree.roots.empty() && n_chunks == 1) {
     const uint64_t bytes = (uint64_t)cap_inst[root] * 8 << P.nodes[root].idx.size();
-    const int64_t n = std::min<int64_t>((int64_t)1 << P.sliced.size(), kTreeBatch);
+    const int64_t n = std::min<int64_t>((int64_t)1 << P.sliced.size(), P.max_tree_batch);
     P.tree_batch = (int)std::max<int64_t>(P.batch, std::min<int64_t>(n, (int64_t)(kTreeBatchBytes / bytes)));
   }
 
@@ -1008,6 +1009,14 @@ void build_memory_for(Plan& P, int n_chunks) {
     else
       t1 = Par.time;
     bufs.push_back({v, V.buf_bytes, V.time, t1});
+    // the parts of a split sum: dead after the step, so they take their place
+    // among the tensors
+    if (V.ksplit && !V.fused) {
+      const uint64_t bytes = (uint64_t)cap_inst[v] * V.inst_elems * 8 << V.ksplit;
+      V.part_slices =
+          V.dep ? (int)std::min<uint64_t>(P.batch, std::max<uint64_t>(1, P.max_part_bytes / bytes)) : 1;
+      bufs.push_back({v, align_up(bytes * (uint64_t)V.part_slices), V.time, V.time, true});
+    }
   }
   std::sort(bufs.begin(), bufs.end(), [](const ArenaBuf& x, const ArenaBuf& y) {
     return x.size != y.size ? x.size > y.size : x.t0 < y.t0;
@@ -1028,39 +1037,43 @@ void build_memory_for(Plan& P, int n_chunks) {
     }
     placed.push_back(&b);
     placed_range.push_back({cur, cur + b.size});
-    P.nodes[b.node].off = P.static_bytes + cur;
+    (b.parts ? P.nodes[b.node].part_off : P.nodes[b.node].off) = P.static_bytes + cur;
     arena = std::max(arena, cur + b.size);
     if (b.t1 == t_end && b.node != root) P.cache_bytes += b.size;
   }
   P.workspace_bytes = align_up(P.static_bytes + arena);
-  // room behind the arena for the parts of split sums (used within a launch
-  // only, so one region serves every node)
-  P.part_off = P.workspace_bytes;
-  uint64_t part = 0;
-  for (int v = nt; v < P.n_nodes; ++v) {
-    const PNode& V = P.nodes[v];
-    if (V.ksplit) part = std::max(part, (uint64_t)cap_inst[v] * (V.dep ? P.batch : 1) * V.inst_elems * 8 << V.ksplit);
-  }
-  P.workspace_bytes += align_up(part);
 }
 
 // smallest power-of-two chunk count whose workspace fits the budget
 void build_memory(Plan& P) {
   const int64_t nr = (int64_t)P.nodes[P.n_nodes - 1].keys.size();
+  auto over = [&] {
+    return P.memory_budget && P.workspace_bytes > P.memory_budget ? P.workspace_bytes - P.memory_budget : 0;
+  };
   auto fit = [&] {
-    int c = 1;
-    build_memory_for(P, c);
-    while (P.memory_budget && P.workspace_bytes > P.memory_budget && c < nr) {
-      c *= 2;
+    for (int c = 1;; c *= 2) {
+      P.max_tree_batch = kTreeBatch;
+      P.max_part_bytes = kMaxPartBytes;
       build_memory_for(P, c);
+      if (!over()) return true;
+      // before the keys are cut further: split sums slice by slice, and fewer
+      // slices per launch of fused slices, down to the slice batch (neither
+      // changes a result)
+      P.max_part_bytes = 0;
+      build_memory_for(P, c);
+      while (over() && P.tree_batch > P.batch) {
+        const PNode& R = P.nodes[P.n_nodes - 1];
+        const int64_t less = (int64_t)(over() / ((uint64_t)R.keys.size() * 8 << R.idx.size())) + 1;
+        P.max_tree_batch = std::max<int64_t>(P.batch, P.tree_batch - less);
+        build_memory_for(P, c);
+      }
+      if (!over()) return true;
+      if (c >= nr) return false;
     }
-    return !P.memory_budget || P.workspace_bytes <= P.memory_budget;
   };
   if (fit()) return;
-  // no room even for single keys: sums in one piece and no more slices per
-  // launch than the slice batch need less
+  // no room even for a single key's parts: sums in one piece need less
   for (PNode& V : P.nodes) V.ksplit = 0;
-  P.wide_batch = false;
   if (!fit())
     fail(MATNC_E_NOMEM, "plan needs " + std::to_string(P.workspace_bytes) + " bytes of workspace even with " +
                             std::to_string(P.n_chunks) + " key chunks; budget " + std::to_string(P.memory_budget));
@@ -1158,7 +1171,7 @@ NodeDesc node_desc(const Plan& P, int v, int nb, int c = 0) {
   d.keep_order = P.split ? 0 : 1;
   d.n_ref = (int64_t)V.keys.size();
   d.linear = V.linear ? 1 : 0;
-  d.part_off = P.part_off + P.arena_delta;
+  d.part_off = V.part_off + P.arena_delta;
   d.ksplit = V.ksplit;
   if (V.fan) {
     const int t = V.fan_tn == 64 ? 1 : 0;
@@ -1186,6 +1199,17 @@ void claim_arena(Plan& P) {
   P.share->owner = P.share_id;
 }
 
+// n slices of a step's launch, from its slice s0 on
+NodeDesc slice_range(NodeDesc d, int64_t s0, int64_t n) {
+  if (s0 == 0 && (!d.dep || d.n_inst == n * d.w)) return d;
+  d.n_inst = n * d.w;
+  d.s0 = (int32_t)s0;
+  d.c_off += (uint64_t)(s0 * d.w) * d.c_inst_bytes;
+  for (OpDesc* o : {&d.A, &d.B})
+    if (o->dep) o->off += (uint64_t)(s0 * o->w_child) * o->inst_bytes;
+  return d;
+}
+
 void launch_node(const Plan& P, const PNode& V, const NodeDesc& d, hipStream_t st) {
   const int64_t* sig = reinterpret_cast<const int64_t*>(P.ws + P.sigma_off);
   hipError_t e;
@@ -1195,13 +1219,17 @@ void launch_node(const Plan& P, const PNode& V, const NodeDesc& d, hipStream_t s
     // tiles record them in their epilogue, other tiles leave them to a
     // separate reduction pass (recording in the epilogue of the big tiles
     // raises their register use and cuts the occupancy)
-    if (V.fan) {
-      if (P.split)
-        e = launch_split_fan(d, V.cfg, P.ws, sig, st);
-      else
-        e = V.rec_max ? launch_mfma_fan_rec(d, V.cfg, P.ws, sig, st) : launch_mfma_fan(d, V.cfg, P.ws, sig, st);
+    if (P.split) {
+      const int64_t slices = V.dep && d.w > 0 ? d.n_inst / d.w : 1, step = d.ksplit ? V.part_slices : slices;
+      e = hipSuccess;
+      for (int64_t s0 = 0; s0 < slices && e == hipSuccess; s0 += step) {
+        const NodeDesc part = slice_range(d, s0, std::min(step, slices - s0));
+        e = V.fan ? launch_split_fan(part, V.cfg, P.ws, sig, st) : launch_split(part, V.cfg, P.ws, sig, st);
+      }
+    } else if (V.fan) {
+      e = V.rec_max ? launch_mfma_fan_rec(d, V.cfg, P.ws, sig, st) : launch_mfma_fan(d, V.cfg, P.ws, sig, st);
     } else {
-      e = P.split ? launch_split(d, V.cfg, P.ws, sig, st) : launch_mfma(d, V.cfg, P.ws, sig, st);
+      e = launch_mfma(d, V.cfg, P.ws, sig, st);
       if (e == hipSuccess && V.rec_max) e = launch_absmax(d, P.ws, st);
     }
   } else if (V.kernel == 1) {

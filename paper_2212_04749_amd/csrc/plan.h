@@ -62,6 +62,8 @@ struct PNode {
   std::vector<int> M, N, K;      // virtual orders of the three index classes
   bool linear = false;           // operands lie with the contracted bits highest, all classes in order
   int ksplit = 0;                // MFMA step: log2 of the parts of its sum
+  int part_slices = 1;           // ... slices per launch, for which the parts have room
+  uint64_t part_off = 0;         // ... byte offset of the parts in the workspace
   int8_t pos[TAB_COUNT][32] = {};  // storage bit of each coordinate bit, per table class
   // memory
   uint64_t inst_elems = 0;
@@ -139,14 +141,14 @@ struct Plan {
   uint64_t static_bytes = 0;
   uint64_t workspace_bytes = 0;
   uint64_t cache_bytes = 0;
-  uint64_t part_off = 0;         // parts of split sums (behind the arena)
   // node ids in schedule order: computed once per cache fill (prologue),
   // once per chunk (cpro), per slice batch and chunk (loop).  The fused
   // subtrees of prologue and loop run first, in one launch each (pro_tree,
   // loop_tree); chunked = cpro, loop_tree's nodes, loop
   Tree pro_tree, loop_tree;
   int tree_batch = 0;  // slices per launch if a slice is one fused subtree, else 0
-  bool wide_batch = true;  // room for tree_batch to exceed the slice batch
+  int64_t max_tree_batch = 0;  // bound on tree_batch (kTreeBatch, less where the budget has no room)
+  uint64_t max_part_bytes = 0; // bound on a launch's parts of split sums, unless it is of one slice
   std::vector<int> prologue, cpro, loop, chunked;
   // costs
   double cmac_single = 0, cmac_multi = 0, cmac_inv = 0, cmac_total = 0;
