@@ -22,10 +22,10 @@
 //
 // Bound: eight bfloat16 products take 256 matrix-core cycles per 32 x 16 x 8
 // complex block, the FP32 instruction 512.  At 20/8/9 bits of m/n/k the step
-// runs 7.34 ms (150 TFLOP/s complex, 1200 of bfloat16; a large bfloat16 library
+// runs 7.07 ms (155 TFLOP/s complex, 1240 of bfloat16; a large bfloat16 library
 // product reaches 1107 on this card under its power limit) against 8.60 ms for
 // the FP32 instruction's best tile and 9.04 for the one that it chose.  At
-// 22/6/6 bits, 17 GB, 1.28 ms against 1.37.
+// 22/6/6 bits 1.24 ms against 1.37.
 //
 // Fan-out tiles whose groups do not fill them multiply empty columns: at
 // 10/3/11 bits (8 instances on average share an A) 0.70 of the 64-column
@@ -49,6 +49,11 @@ namespace matnc {
 // be lost otherwise).
 constexpr float kScale = 16777216.f;             // 2^24
 constexpr float kUnscale = 1.f / (kScale * kScale);
+
+// The least component of a result that is taken from a tile computed with
+// operands scaled by 2^-24 instead: what such operands lose there is at most
+// 2^-110 each, 2^18 of a product with the largest FP32 number.
+constexpr float kLarge = 1152921504606846976.f;  // 2^60
 
 // Exact split of an FP32 pair into three packed (re, im) bfloat16 pairs:
 // value = p[0] + p[1] + p[2], each part the rest rounded to nearest (8 + 8 + 8
@@ -76,7 +81,9 @@ __device__ __forceinline__ void load_f2x2(uint64_t base, uint32_t i, f32x2 (&r)[
   r[1] = f32x2{v.z, v.w};
 }
 
-__device__ __forceinline__ float2 scaled(f32x2 v) { return make_float2(v.x * kScale, v.y * kScale); }
+__device__ __forceinline__ float2 scaled(f32x2 v, float f) { return make_float2(v.x * f, v.y * f); }
+
+__device__ __forceinline__ bool finite(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
 
 __device__ __forceinline__ Split3 split3(float2 v) {
   Split3 s;
@@ -99,6 +106,7 @@ __device__ __forceinline__ Split3 split3(float2 v) {
 template <int RM, int RN, int WM, int WN, bool FAN, bool LIN>
 __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   static_assert(LIN || !FAN, "fan-out tiles are a plan's");
+  static_assert(RM * RN <= 4, "a lane's outputs have a bit each");
   constexpr int TK = 8;
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = 32 * RM * WM;
@@ -128,6 +136,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   // of a k step's change of bits 3 .. t: [AK, BK][t]
   __shared__ uint32_t s_nib[4][8][16];
   __shared__ uint32_t s_kx[2][32];
+  // tiles with a sum out of range, one bit for this workgroup's tiles 0, 1024, ..., and so on
+  __shared__ uint32_t s_redo[33];  // [32]: there is one
 
   const gptr<const int32_t> glA = gmem<const int32_t>(ws + d.A.gmap_off);
   const gptr<const int32_t> glB = gmem<const int32_t>(ws + d.B.gmap_off);
@@ -172,6 +182,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
     if (wave == 0) s_kx[0][lane - 16] = dep<TAB_AK>(d, d.kbits, k);
     if (wave == 1) s_kx[1][lane - 16] = dep<TAB_BK>(d, d.kbits, k);
   }
+  if (tid < 33) s_redo[tid] = 0;
   if (tid < TN) s_cn[tid] = dep<TAB_CN>(d, 8, FAN ? (tid & nmask) : tid);
   const bool astage = QA >= NT || tid < QA;
   const bool bstage = QB >= NT || tid < QB;
@@ -211,278 +222,323 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   for (int i = 0; i < RM; ++i) om[i] = dep<TAB_CM>(d, 8, (wm * RM + i) * 32 + l32);
   __syncthreads();
 
-  for (uint32_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
-    // logical tile order: n tiles innermost (they share the A tile), then m
-    // tiles, then instances / fan rows (fan rows in blocks, see unit_tile);
-    // each XCD takes a contiguous range
-    uint32_t lt = xcd_tile(blk, total);
-    uint32_t part = 0;
-    if (d.ksplit) {  // tiles of one part are neighbours: they share A and B
-      part = lt / upart;
-      lt -= part * upart;
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass) {  // the tiles that were out of range once more
+      __syncthreads();
+      if (!s_redo[32]) break;
     }
-    uint32_t u, t;
-    unit_tile(lt, units, tbits, d.fan_rows > 0 ? (uint32_t)d.fan_rows : (FAN ? 2u : 1u), u, t);
-    const uint32_t m0 = (t >> nt_bits) * TM;
-    const uint32_t n0 = (t & ((1u << nt_bits) - 1u)) * TN;
-    int64_t s, j;
-    gptr<const int32_t> fj = nullptr;
-    if (FAN) {
-      s = d.dep ? u / (uint32_t)d.n_fan : 0u;
-      fj = fan + (uint64_t)(u - (uint32_t)s * (uint32_t)d.n_fan) * slots;
-      j = fj[0];
-    } else {
-      s = d.dep ? u / (uint32_t)d.w : 0u;
-      j = (int64_t)u - s * d.w;
-    }
-    const int64_t inst = s * d.w + j;  // output instance (slot 0 for fan tiles)
-    const int64_t sigma = sigma0 + s;
-    const int64_t ai = !FAN && d.flat ? inst : operand_instance(d.A, glA, j, s, sigma);
-    const int64_t bi = !FAN && d.flat ? inst : operand_instance(d.B, glB, j, s, sigma);
-    // offsets of (m0, n0): lane 8c + q looks up nibble q of class c
-    uint32_t first = s_nib[(lane >> 3) & 3][lane & 7][((lane & 16 ? n0 : m0) >> (4 * (lane & 7))) & 15u];
+    const float sc = pass ? 1.f / kScale : kScale;
+    uint32_t it = ~0u;
+    for (uint32_t blk = blockIdx.x; blk < total; blk += gridDim.x) {
+      ++it;
+      if (pass && !((s_redo[(it >> 5) & 31] >> (it & 31)) & 1u)) continue;
+      // logical tile order: n tiles innermost (they share the A tile), then m
+      // tiles, then instances / fan rows (fan rows in blocks, see unit_tile);
+      // each XCD takes a contiguous range
+      uint32_t lt = xcd_tile(blk, total);
+      uint32_t part = 0;
+      if (d.ksplit) {  // tiles of one part are neighbours: they share A and B
+        part = lt / upart;
+        lt -= part * upart;
+      }
+      uint32_t u, t;
+      unit_tile(lt, units, tbits, d.fan_rows > 0 ? (uint32_t)d.fan_rows : (FAN ? 2u : 1u), u, t);
+      const uint32_t m0 = (t >> nt_bits) * TM;
+      const uint32_t n0 = (t & ((1u << nt_bits) - 1u)) * TN;
+      int64_t s, j;
+      gptr<const int32_t> fj = nullptr;
+      if (FAN) {
+        s = d.dep ? u / (uint32_t)d.n_fan : 0u;
+        fj = fan + (uint64_t)(u - (uint32_t)s * (uint32_t)d.n_fan) * slots;
+        j = fj[0];
+      } else {
+        s = d.dep ? u / (uint32_t)d.w : 0u;
+        j = (int64_t)u - s * d.w;
+      }
+      const int64_t inst = s * d.w + j;  // output instance (slot 0 for fan tiles)
+      const int64_t sigma = sigma0 + s;
+      const int64_t ai = !FAN && d.flat ? inst : operand_instance(d.A, glA, j, s, sigma);
+      const int64_t bi = !FAN && d.flat ? inst : operand_instance(d.B, glB, j, s, sigma);
+      // offsets of (m0, n0): lane 8c + q looks up nibble q of class c
+      uint32_t first = s_nib[(lane >> 3) & 3][lane & 7][((lane & 16 ? n0 : m0) >> (4 * (lane & 7))) & 15u];
 #pragma unroll
-    for (int o = 1; o < 8; o <<= 1) first |= __shfl_xor(first, o);
-    const uint64_t oa0 = __builtin_amdgcn_readlane(first, 0), oc0 = (uint64_t)__builtin_amdgcn_readlane(first, 8) +
-                                                                     (uint64_t)__builtin_amdgcn_readlane(first, 24);
-    const uint64_t ob0 = __builtin_amdgcn_readlane(first, 16);
-    const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes + oa0 * 8;
-    const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes + ob0 * 8;
-    const uint64_t c_off = d.ksplit ? d.part_off + (uint64_t)part * (uint64_t)d.n_inst * d.c_inst_bytes : d.c_off;
-    const gptr<f32x2> pc = gmem<f32x2>(ws + c_off + inst * d.c_inst_bytes + oc0 * 8);
-    if (FAN && tid < slots) {
-      // an empty slot reads slot 0's B into columns that are never stored
-      const int jg = fj[tid];
-      const int64_t bg = operand_instance(d.B, glB, jg < 0 ? j : jg, s, sigma);
-      s_bb[tid] = d.B.off + bg * d.B.inst_bytes;
-      s_cb[tid] = jg < 0 ? 0 : c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes + oc0 * 8;
-    }
-    if (FAN) __syncthreads();  // the column data above is read by every wave
+      for (int o = 1; o < 8; o <<= 1) first |= __shfl_xor(first, o);
+      const uint64_t oa0 = __builtin_amdgcn_readlane(first, 0), oc0 = (uint64_t)__builtin_amdgcn_readlane(first, 8) +
+                                                                       (uint64_t)__builtin_amdgcn_readlane(first, 24);
+      const uint64_t ob0 = __builtin_amdgcn_readlane(first, 16);
+      const uint64_t pa = ws + d.A.off + ai * d.A.inst_bytes + oa0 * 8;
+      const uint64_t pb = ws + d.B.off + bi * d.B.inst_bytes + ob0 * 8;
+      const uint64_t c_off = d.ksplit ? d.part_off + (uint64_t)part * (uint64_t)d.n_inst * d.c_inst_bytes : d.c_off;
+      const gptr<f32x2> pc = gmem<f32x2>(ws + c_off + inst * d.c_inst_bytes + oc0 * 8);
+      if (FAN && tid < slots) {
+        // an empty slot reads slot 0's B into columns that are never stored
+        const int jg = fj[tid];
+        const int64_t bg = operand_instance(d.B, glB, jg < 0 ? j : jg, s, sigma);
+        s_bb[tid] = d.B.off + bg * d.B.inst_bytes;
+        s_cb[tid] = jg < 0 ? 0 : c_off + (uint64_t)(s * d.w + jg) * d.c_inst_bytes + oc0 * 8;
+      }
+      if (FAN) __syncthreads();  // the column data above is read by every wave
 
-    uint64_t pak[LIN ? EQA : 1], pbe[EQB];  // LIN: next k row of each block; else the instance's start
-    const uint32_t k0 = part * ((uint32_t)ksteps * TK);
+      const uint32_t k0 = part * ((uint32_t)ksteps * TK);
+      uint64_t pak[LIN ? EQA : 1], pbe[EQB];  // LIN: next k row of each block; else the instance's start
 #pragma unroll
-    for (int e = 0; e < EQB; ++e) {
-      pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] + (uint64_t)(bnn[e] & nmask) * 8
-                   : pb + (LIN ? (uint64_t)bnn[e] * 8 : 0);
-      if (LIN) pbe[e] += (uint64_t)(k0 + 4 * bkq[e]) * b_k;
-    }
-    if constexpr (LIN) {
-#pragma unroll
-      for (int e = 0; e < EQA; ++e) pak[e] = pa + (uint64_t)(k0 + 4 * akq[e]) * a_k;
-    }
-    uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded (not LIN)
-    if (!LIN && d.ksplit) {
-      kba = dep<TAB_AK>(d, d.kbits, k0);
-      kbb = dep<TAB_BK>(d, d.kbits, k0);
-    }
-    // (a second register stage, as the FP16 tiles have, costs a workgroup per CU:
-    // 20/8/9 bits on the 128 x 64 tile 6.4 ms with one, 6.9 ms with two)
-    f32x2 ra[EQA][4][MA];
-    f32x2 rb[EQB][4];
-    auto gload = [&](int ks) {
-      if constexpr (!LIN) {
-        if (ks > 0) {
-          const int t = 3 + __builtin_ctz(ks);
-          kba ^= __builtin_amdgcn_readfirstlane(s_kx[0][t]);
-          kbb ^= __builtin_amdgcn_readfirstlane(s_kx[1][t]);
-        }
-      }
-      if (astage) {
-#pragma unroll
-        for (int e = 0; e < EQA; ++e)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if constexpr (LIN && MA == 2)
-              load_f2x2(pak[e] + q * a_k, (uint32_t)amm[e], ra[e][q]);
-            else if constexpr (LIN)
-              ra[e][q][0] = load_f2(pak[e] + q * a_k, (uint32_t)amm[e]);
-            else
-              ra[e][q][0] = load_f2(pa, aoff[e][q] + kba);
-          }
-      }
-      if (bstage) {
-#pragma unroll
-        for (int e = 0; e < EQB; ++e)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if constexpr (LIN)
-              rb[e][q] = load_f2(pbe[e] + q * b_k, 0);
-            else
-              rb[e][q] = load_f2(pbe[e], boff[e][q] + kbb);
-          }
+      for (int e = 0; e < EQB; ++e) {
+        pbe[e] = FAN ? ws + s_bb[bnn[e] >> d.nbits] + (uint64_t)(bnn[e] & nmask) * 8
+                     : pb + (LIN ? (uint64_t)bnn[e] * 8 : 0);
+        if (LIN) pbe[e] += (uint64_t)(k0 + 4 * bkq[e]) * b_k;
       }
       if constexpr (LIN) {
 #pragma unroll
-        for (int e = 0; e < EQA; ++e) pak[e] += TK * a_k;
-#pragma unroll
-        for (int e = 0; e < EQB; ++e) pbe[e] += TK * b_k;
+        for (int e = 0; e < EQA; ++e) pak[e] = pa + (uint64_t)(k0 + 4 * akq[e]) * a_k;
       }
-    };
-    auto lstore = [&](int buf) {
-      if (astage) {
+      uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded (not LIN)
+      if (!LIN && d.ksplit) {
+        kba = dep<TAB_AK>(d, d.kbits, k0);
+        kbb = dep<TAB_BK>(d, d.kbits, k0);
+      }
+      // (a second register stage, as the FP16 tiles have, costs a workgroup per CU:
+      // 20/8/9 bits on the 128 x 64 tile 6.4 ms with one, 6.9 ms with two)
+      f32x2 ra[EQA][4][MA];
+      f32x2 rb[EQB][4];
+      auto gload = [&](int ks) {
+        if constexpr (!LIN) {
+          if (ks > 0) {
+            const int t = 3 + __builtin_ctz(ks);
+            kba ^= __builtin_amdgcn_readfirstlane(s_kx[0][t]);
+            kbb ^= __builtin_amdgcn_readfirstlane(s_kx[1][t]);
+          }
+        }
+        if (astage) {
 #pragma unroll
-        for (int e = 0; e < EQA; ++e) {
+          for (int e = 0; e < EQA; ++e)
 #pragma unroll
-          for (int i = 0; i < MA; ++i) {
+            for (int q = 0; q < 4; ++q) {
+              if constexpr (LIN && MA == 2)
+                load_f2x2(pak[e] + q * a_k, (uint32_t)amm[e], ra[e][q]);
+              else if constexpr (LIN)
+                ra[e][q][0] = load_f2(pak[e] + q * a_k, (uint32_t)amm[e]);
+              else
+                ra[e][q][0] = load_f2(pa, aoff[e][q] + kba);
+            }
+        }
+        if (bstage) {
+#pragma unroll
+          for (int e = 0; e < EQB; ++e)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              if constexpr (LIN)
+                rb[e][q] = load_f2(pbe[e] + q * b_k, 0);
+              else
+                rb[e][q] = load_f2(pbe[e], boff[e][q] + kbb);
+            }
+        }
+        if constexpr (LIN) {
+#pragma unroll
+          for (int e = 0; e < EQA; ++e) pak[e] += TK * a_k;
+#pragma unroll
+          for (int e = 0; e < EQB; ++e) pbe[e] += TK * b_k;
+        }
+      };
+      auto lstore = [&](int buf) {
+        if (astage) {
+#pragma unroll
+          for (int e = 0; e < EQA; ++e) {
+#pragma unroll
+            for (int i = 0; i < MA; ++i) {
+              Split3 v[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) v[q] = split3(scaled(ra[e][q][i], sc));
+#pragma unroll
+              for (int p = 0; p < 3; ++p)
+                *reinterpret_cast<uint4*>(&As[buf][p][akq[e] * AQ + 4 * (amm[e] + i)]) =
+                    make_uint4(v[0].p[p], v[1].p[p], v[2].p[p], v[3].p[p]);
+            }
+          }
+        }
+        if (bstage) {
+#pragma unroll
+          for (int e = 0; e < EQB; ++e) {
             Split3 v[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = split3(scaled(ra[e][q][i]));
+            for (int q = 0; q < 4; ++q) v[q] = split3(scaled(rb[e][q], sc));
+            const int base = ((bkq[e] * TN + bnn[e]) * 2) * 4;
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-              *reinterpret_cast<uint4*>(&As[buf][p][akq[e] * AQ + 4 * (amm[e] + i)]) =
-                  make_uint4(v[0].p[p], v[1].p[p], v[2].p[p], v[3].p[p]);
+            for (int p = 0; p < 3; ++p) {
+              *reinterpret_cast<uint4*>(&Bs[buf][p][base]) =
+                  make_uint4(v[0].p[p] ^ 0x80000000u, v[1].p[p] ^ 0x80000000u, v[2].p[p] ^ 0x80000000u,
+                             v[3].p[p] ^ 0x80000000u);
+              *reinterpret_cast<uint4*>(&Bs[buf][p][base + 4]) =
+                  make_uint4(__builtin_amdgcn_alignbit(v[0].p[p], v[0].p[p], 16),
+                             __builtin_amdgcn_alignbit(v[1].p[p], v[1].p[p], 16),
+                             __builtin_amdgcn_alignbit(v[2].p[p], v[2].p[p], 16),
+                             __builtin_amdgcn_alignbit(v[3].p[p], v[3].p[p], 16));
+            }
           }
         }
-      }
-      if (bstage) {
-#pragma unroll
-        for (int e = 0; e < EQB; ++e) {
-          Split3 v[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = split3(scaled(rb[e][q]));
-          const int base = ((bkq[e] * TN + bnn[e]) * 2) * 4;
-#pragma unroll
-          for (int p = 0; p < 3; ++p) {
-            *reinterpret_cast<uint4*>(&Bs[buf][p][base]) =
-                make_uint4(v[0].p[p] ^ 0x80000000u, v[1].p[p] ^ 0x80000000u, v[2].p[p] ^ 0x80000000u,
-                           v[3].p[p] ^ 0x80000000u);
-            *reinterpret_cast<uint4*>(&Bs[buf][p][base + 4]) =
-                make_uint4(__builtin_amdgcn_alignbit(v[0].p[p], v[0].p[p], 16),
-                           __builtin_amdgcn_alignbit(v[1].p[p], v[1].p[p], 16),
-                           __builtin_amdgcn_alignbit(v[2].p[p], v[2].p[p], 16),
-                           __builtin_amdgcn_alignbit(v[3].p[p], v[3].p[p], 16));
-          }
-        }
-      }
-    };
+      };
 
-    floatx16 acc[RM][RN], low[RM][RN];
+      floatx16 acc[RM][RN], low[RM][RN];
 #pragma unroll
-    for (int i = 0; i < RM; ++i)
-#pragma unroll
-      for (int q = 0; q < RN; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][q][r] = low[i][q][r] = 0.f;
-
-    auto kstep = [&](int buf) {
-      auto afrag = [&](int p, int i) {
-        return *reinterpret_cast<const bf16x8*>(&As[buf][p][half * AQ + 4 * ((wm * RM + i) * 32 + l32)]);
-      };
-      auto bfrag = [&](int p, int q) {
-        return *reinterpret_cast<const bf16x8*>(&Bs[buf][p][((half * TN + (wn * RN + q) * 16 + ncol) * 2 + dsel) * 4]);
-      };
-      // products of parts pa, pb with pa + pb <= 3: those of the first parts into
-      // acc, the others, smallest first, into low; the fragments of the side
-      // with fewer tiles are held, the others read in turn
-      auto tile = [&](floatx16& a, floatx16& lo, const bf16x8(&x)[3], const bf16x8(&y)[3]) {
-#pragma unroll
-        for (int g = 3; g >= 1; --g)
-#pragma unroll
-          for (int ap = g == 3 ? 1 : 0; ap <= (g == 3 ? 2 : g); ++ap)
-            lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g - ap], y[ap], lo, 0, 0, 0);
-        a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], a, 0, 0, 0);
-      };
-      if constexpr (RM <= RN) {
-        bf16x8 yv[RM][3];
-#pragma unroll
-        for (int i = 0; i < RM; ++i)
-#pragma unroll
-          for (int p = 0; p < 3; ++p) yv[i][p] = afrag(p, i);
-#pragma unroll
-        for (int q = 0; q < RN; ++q) {
-          bf16x8 xv[3];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) xv[p] = bfrag(p, q);
-#pragma unroll
-          for (int i = 0; i < RM; ++i) tile(acc[i][q], low[i][q], xv, yv[i]);
-        }
-      } else {
-        bf16x8 xv[RN][3];
+      for (int i = 0; i < RM; ++i)
 #pragma unroll
         for (int q = 0; q < RN; ++q)
 #pragma unroll
-          for (int p = 0; p < 3; ++p) xv[q][p] = bfrag(p, q);
-#pragma unroll
-        for (int i = 0; i < RM; ++i) {
-          bf16x8 yv[3];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) yv[p] = afrag(p, i);
-#pragma unroll
-          for (int q = 0; q < RN; ++q) tile(acc[i][q], low[i][q], xv[q], yv);
-        }
-      }
-    };
+          for (int r = 0; r < 16; ++r) acc[i][q][r] = low[i][q][r] = 0.f;
 
-    gload(0);
-    lstore(0);
-    __syncthreads();
-    // (the last step, which loads nothing, has a copy of its own: a load under a
-    // condition makes the compiler wait for more than it needs)
-    int ks = 0;
-    for (; ks + 1 < ksteps; ++ks) {
-      gload(ks + 1);
-      kstep(ks & 1);
-      lstore((ks + 1) & 1);
-      __syncthreads();
-    }
-    kstep(ks & 1);
-    __syncthreads();
-
-    // A sum with an infinite or NaN input, or one whose scaled value leaves
-    // FP32's range (an operand above 2^104, a sum above 2^80), is not what
-    // FP32 products give: a wave that holds a non-finite value computes its
-    // part of the tile again with FP32 operations.
-    float fin = 0.f;
+      auto kstep = [&](int buf) {
+        auto afrag = [&](int p, int i) {
+          return *reinterpret_cast<const bf16x8*>(&As[buf][p][half * AQ + 4 * ((wm * RM + i) * 32 + l32)]);
+        };
+        auto bfrag = [&](int p, int q) {
+          return *reinterpret_cast<const bf16x8*>(&Bs[buf][p][((half * TN + (wn * RN + q) * 16 + ncol) * 2 + dsel) * 4]);
+        };
+        // products of parts pa, pb with pa + pb <= 3: those of the first parts into
+        // acc, the others, smallest first, into low; the fragments of the side
+        // with fewer tiles are held, the others read in turn
+        auto tile = [&](floatx16& a, floatx16& lo, const bf16x8(&x)[3], const bf16x8(&y)[3]) {
 #pragma unroll
-    for (int i = 0; i < RM; ++i)
+          for (int g = 3; g >= 1; --g)
 #pragma unroll
-      for (int q = 0; q < RN; ++q)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[i][q][r] += low[i][q][r];
-          fin = fmaf(acc[i][q][r], 0.f, fin);
-        }
-    if (__any(fin != 0.f)) {
-      const uint32_t k1 = k0 + (uint32_t)ksteps * TK;
-      for (int e = lane; e < 32 * RM * 16 * RN; e += 64) {
-        const int nl = wn * RN * 16 + e / (32 * RM);
-        const uint32_t m = wm * RM * 32 + e % (32 * RM);
-        const int g = FAN ? nl >> d.nbits : 0;
-        if (FAN && s_cb[g] == 0) continue;
-        const uint64_t pbg = FAN ? ws + s_bb[g] : pb;
-        const uint32_t oa = dep<TAB_AM>(d, 8, m);
-        const uint32_t ob = dep<TAB_BN>(d, 8, FAN ? (nl & nmask) : nl);
-        float2 c = make_float2(0.f, 0.f);
-        for (uint32_t k = k0; k < k1; ++k)
-          cmac(c, ldg_f2(pa, oa + dep<TAB_AK>(d, d.kbits, k)), ldg_f2(pbg, ob + dep<TAB_BK>(d, d.kbits, k)));
-        const gptr<f32x2> dst = FAN ? gmem<f32x2>(ws + s_cb[g]) : pc;
-        dst[dep<TAB_CM>(d, 8, m) + s_cn[nl]] = f32x2{c.x, c.y};
-      }
-    } else {
-      // epilogue: lane holds C[m][n] (re, im) in registers (r, r+1), r even
-#pragma unroll
-      for (int q = 0; q < RN; ++q) {
-#pragma unroll
-        for (int rr = 0; rr < 8; ++rr) {
-          const int r = 2 * rr;
-          const int row = 8 * (rr >> 1) + 4 * half + 2 * (rr & 1);
-          const int nl = (wn * RN + q) * 16 + (row >> 1);  // column within the tile
-          gptr<f32x2> dst = pc;
-          bool live = true;
-          if (FAN) {
-            const uint64_t cbs = s_cb[nl >> d.nbits];  // uniform over the 32 lanes of a half-wave (one n)
-            live = cbs != 0;
-            dst = gmem<f32x2>(ws + cbs);
-          }
-          const uint32_t ocn = s_cn[nl];
+            for (int ap = g == 3 ? 1 : 0; ap <= (g == 3 ? 2 : g); ++ap)
+              lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g - ap], y[ap], lo, 0, 0, 0);
+          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], a, 0, 0, 0);
+        };
+        if constexpr (RM <= RN) {
+          bf16x8 yv[RM][3];
 #pragma unroll
           for (int i = 0; i < RM; ++i)
-            if (live) dst[om[i] + ocn] = f32x2{acc[i][q][r] * kUnscale, acc[i][q][r + 1] * kUnscale};
+#pragma unroll
+            for (int p = 0; p < 3; ++p) yv[i][p] = afrag(p, i);
+#pragma unroll
+          for (int q = 0; q < RN; ++q) {
+            bf16x8 xv[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) xv[p] = bfrag(p, q);
+#pragma unroll
+            for (int i = 0; i < RM; ++i) tile(acc[i][q], low[i][q], xv, yv[i]);
+          }
+        } else {
+          bf16x8 xv[RN][3];
+#pragma unroll
+          for (int q = 0; q < RN; ++q)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) xv[q][p] = bfrag(p, q);
+#pragma unroll
+          for (int i = 0; i < RM; ++i) {
+            bf16x8 yv[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) yv[p] = afrag(p, i);
+#pragma unroll
+            for (int q = 0; q < RN; ++q) tile(acc[i][q], low[i][q], xv[q], yv);
+          }
+        }
+      };
+
+      gload(0);
+      lstore(0);
+      __syncthreads();
+      // (the last step, which loads nothing, has a copy of its own: a load under a
+      // condition makes the compiler wait for more than it needs)
+      int ks = 0;
+      for (; ks + 1 < ksteps; ++ks) {
+        gload(ks + 1);
+        kstep(ks & 1);
+        lstore((ks + 1) & 1);
+        __syncthreads();
+      }
+      kstep(ks & 1);
+      __syncthreads();
+
+      // A sum with an infinite or NaN input, or one whose scaled value leaves
+      // FP32's range (an operand above 2^104, a sum above 2^80), is not what
+      // FP32 products give.  Its tile is computed a second time after the
+      // workgroup's others, with operands scaled down, for the outputs that are not
+      // finite yet, and of these the ones that are still not right (see kLarge)
+      // with FP32 operations: with operands of 1e13 everywhere, 12/6/9 bits x 64,
+      // 1.09 ms against 0.50 in range (54 ms one output after another).
+      float fin = 0.f;
+#pragma unroll
+      for (int i = 0; i < RM; ++i)
+#pragma unroll
+        for (int q = 0; q < RN; ++q)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            acc[i][q][r] += low[i][q][r];
+            fin = fmaf(acc[i][q][r], 0.f, fin);
+          }
+      // (the epilogue: a lane holds C[m][n] (re, im) in registers (r, r+1), r even)
+      if (pass == 0) {
+        if (__any(fin != 0.f) && lane == 0) {
+          atomicOr(&s_redo[(it >> 5) & 31], 1u << (it & 31));
+          s_redo[32] = 1;
+        }
+#pragma unroll
+        for (int q = 0; q < RN; ++q) {
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr) {
+            const int r = 2 * rr;
+            const int row = 8 * (rr >> 1) + 4 * half + 2 * (rr & 1);
+            const int nl = (wn * RN + q) * 16 + (row >> 1);  // column within the tile
+            gptr<f32x2> dst = pc;
+            bool live = true;
+            if (FAN) {
+              const uint64_t cbs = s_cb[nl >> d.nbits];  // uniform over the 32 lanes of a half-wave (one n)
+              live = cbs != 0;
+              dst = gmem<f32x2>(ws + cbs);
+            }
+            const uint32_t ocn = s_cn[nl];
+#pragma unroll
+            for (int i = 0; i < RM; ++i)
+              if (live) dst[om[i] + ocn] = f32x2{acc[i][q][r] * kUnscale, acc[i][q][r + 1] * kUnscale};
+          }
+        }
+      } else {
+        uint32_t redo = 0;  // this lane's outputs that need FP32 operations
+#pragma unroll
+        for (int q = 0; q < RN; ++q) {
+#pragma unroll
+          for (int rr = 0; rr < 8; ++rr) {
+            const int r = 2 * rr;
+            const int row = 8 * (rr >> 1) + 4 * half + 2 * (rr & 1);
+            const int nl = (wn * RN + q) * 16 + (row >> 1);  // column within the tile
+            gptr<f32x2> dst = pc;
+            bool live = true;
+            if (FAN) {
+              const uint64_t cbs = s_cb[nl >> d.nbits];  // uniform over the 32 lanes of a half-wave (one n)
+              live = cbs != 0;
+              dst = gmem<f32x2>(ws + cbs);
+            }
+            const uint32_t ocn = s_cn[nl];
+#pragma unroll
+            for (int i = 0; i < RM; ++i) {
+              if (!live) continue;
+              const f32x2 was = dst[om[i] + ocn];
+              if (finite(was.x) && finite(was.y)) continue;
+              const f32x2 c = f32x2{acc[i][q][r] * (kScale * kScale), acc[i][q][r + 1] * (kScale * kScale)};
+              if (finite(acc[i][q][r]) && finite(acc[i][q][r + 1]) && fabsf(c.x) >= kLarge && fabsf(c.y) >= kLarge)
+                dst[om[i] + ocn] = c;
+              else
+                redo |= 1u << ((q * 8 + rr) * RM + i);
+            }
+          }
+        }
+        for (; redo; redo &= redo - 1) {
+          const int bit = __builtin_ctz(redo), i = bit % RM, rr = bit / RM % 8, q = bit / RM / 8;
+          const int nl = (wn * RN + q) * 16 + 4 * (rr >> 1) + 2 * half + (rr & 1);
+          const uint32_t m = (wm * RM + i) * 32 + l32;
+          const int g = FAN ? nl >> d.nbits : 0;
+          const uint64_t pbg = FAN ? ws + s_bb[g] : pb;
+          const uint32_t oa = dep<TAB_AM>(d, 8, m);
+          const uint32_t ob = dep<TAB_BN>(d, 8, FAN ? (nl & nmask) : nl);
+          float2 c = make_float2(0.f, 0.f);
+          for (uint32_t k = k0; k < k0 + (uint32_t)ksteps * TK; ++k)
+            cmac(c, ldg_f2(pa, oa + dep<TAB_AK>(d, d.kbits, k)), ldg_f2(pbg, ob + dep<TAB_BK>(d, d.kbits, k)));
+          const gptr<f32x2> dst = FAN ? gmem<f32x2>(ws + s_cb[g]) : pc;
+          dst[dep<TAB_CM>(d, 8, m) + s_cn[nl]] = f32x2{c.x, c.y};
         }
       }
+      if (FAN) __syncthreads();  // the next tile rewrites the column data
     }
-    if (FAN) __syncthreads();  // the next tile rewrites the column data
   }
 }
 

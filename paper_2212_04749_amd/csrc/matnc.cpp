@@ -304,16 +304,17 @@ int32_t plain_block_units(const std::vector<int32_t>& ga, uint64_t a_inst_bytes)
 }
 
 // Split-bfloat16 tile configuration of a step, -1 if none fits: the largest of
-// 256 x 64 (sums of 2^8 and more), 128 x 64, 128 x 32 and 64 x 32 that still
+// 256 x 64 (sums of 2^7 and more), 128 x 64, 128 x 32 and 64 x 32 that still
 // gives every CU two workgroups, or one where the sum is long enough to be cut
-// into parts (its tiles then refill the chip), else the smallest.  20/8/9 bits: 256 x 64 7.34 ms,
-// 128 x 128 7.67, 128 x 64 7.79, 128 x 32 9.76; 22/6/6: 128 x 64 1.286 ms, 256 x 64 1.290;
-// 16/6/4 x 8: 90 us and 95; 11/7/6 x 5 (40 of the 256 x 64 tiles): 20, 16.7, 16.3 and 16.6 us.
+// into parts (its tiles then refill the chip), else the smallest.  20/8/9 bits: 256 x 64 7.07 ms,
+// 128 x 128 7.51, 128 x 64 7.62, 128 x 32 9.52; 14/7/7 x 64: 1.04, 1.07, 1.05 and 1.31;
+// 22/6/6: 256 x 64 1.250 ms, 128 x 64 1.241; 16/6/4 x 8: 96 us and 89; 11/7/6 x 5 (40 of
+// the 256 x 64 tiles): 256 x 64 19.5 us, 128 x 64 16.3, 128 x 32 16.2, 64 x 32 16.2.
 int split_config(int64_t instances, int nm, int nn, int nk, bool parts) {
   int last = -1;
   const int pb = parts && nk > 7 ? nk - 7 : 0;  // parts a long sum may be cut into (split_bits)
   for (int k : {4, 1, 0, 2}) {
-    if (!mfma_config_fits(k, nm, nn, nk) || (k == 4 && nk < 8)) continue;
+    if (!mfma_config_fits(k, nm, nn, nk) || (k == 4 && nk < 7)) continue;
     last = k;
     if ((instances << (nm - mfma_config_tm_bits(k) + nn - mfma_config_tn_bits(k) + pb)) >= (pb ? 256 : 512)) break;
   }
