@@ -292,10 +292,6 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
         for (int e = 0; e < EQA; ++e) pak[e] = pa + (uint64_t)(k0 + 4 * akq[e]) * a_k;
       }
       uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded (not LIN)
-      if (!LIN && d.ksplit) {
-        kba = dep<TAB_AK>(d, d.kbits, k0);
-        kbb = dep<TAB_BK>(d, d.kbits, k0);
-      }
       // (a second register stage, as the FP16 tiles have, costs a workgroup per CU:
       // 20/8/9 bits on the 128 x 64 tile 6.4 ms with one, 6.9 ms with two)
       f32x2 ra[EQA][4][MA];
@@ -593,7 +589,7 @@ static hipError_t launch_split_t(const NodeDesc& d, int cfg, uint64_t ws, const 
   hipError_t e;
   if (d.linear)
     e = launch_split_s<FAN, true>(d, cfg, grid, ws, sig, st);
-  else if (FAN)
+  else if (FAN || d.ksplit)
     e = hipErrorInvalidValue;
   else  // a caller's own layout
     e = launch_split_s<false, false>(d, cfg, grid, ws, sig, st);

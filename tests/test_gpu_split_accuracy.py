@@ -74,3 +74,28 @@ def test_a_single_product_is_rounded_once(kernel):
     got, ref = multiply(torch, rng, A + 0j, B + 0j, kernel)
     assert np.all(np.abs(got.real - ref.real) <= (2.0 ** -24 + 2.0 ** -28) * np.abs(ref.real))
     assert not got.imag.any()
+
+
+@pytest.mark.parametrize("kernel", [-1, 0] + list(range(100, 106)))
+def test_plan_layout_at_an_8_byte_address(kernel):
+    """Operands in a plan's layout whose addresses are not a multiple of 16 bytes: the same bits as at one that is."""
+    torch = require_gpu()
+    from paper_2212_04749_amd import api
+    rng = np.random.default_rng(11)
+    nm, nn, nk, batch = 9, 7, 4, 3
+    pos = plan_layout(rng, nm, nn, nk)
+    a, b = torch.randn(batch * (2 << (nm + nk)), device="cuda"), torch.randn(batch * (2 << (nn + nk)), device="cuda")
+    out = []
+    for shift in (0, 2):
+        A, B = torch.zeros(a.numel() + 2, device="cuda"), torch.zeros(b.numel() + 2, device="cuda")
+        C = torch.full((batch * (2 << (nm + nn)) + 2,), float("nan"), device="cuda")
+        A[shift:shift + a.numel()], B[shift:shift + b.numel()] = a, b
+        x, y = A[shift:shift + a.numel()], B[shift:shift + b.numel()]
+        c = C[shift:shift + (batch * (2 << (nm + nn)))]
+        assert x.data_ptr() % 16 == 4 * shift
+        keep = api.contract_pair(x, y, c, pos, kernel=kernel)
+        torch.cuda.synchronize()
+        del keep
+        out.append(c.cpu().numpy())
+    assert np.isfinite(out[0]).all()
+    assert np.array_equal(out[0], out[1])
