@@ -274,17 +274,20 @@ def matnc_mfma_config_count() -> int:
 
 def _positions(posA_m, posA_k, posB_k, posB_n, posC_m, posC_n):
     """The six position lists back to back: the array (to keep alive) and each list's address.  (One array
-    instead of six ctypes ones: 3 us of a 13 us call.)"""
+    instead of six ctypes ones: 3 us of a 13 us call.)  The A lists and posB_n say how many bits a class has;
+    further entries of the others are ignored."""
+    nm, nn, nk = len(posA_m), len(posB_n), len(posA_k)
     lists = (posA_m, posA_k, posB_k, posB_n, posC_m, posC_n)
+    if len(posB_k) != nk or len(posC_m) != nm or len(posC_n) != nn:
+        if len(posB_k) < nk or len(posC_m) < nm or len(posC_n) < nn:
+            raise MatncError(MATNC_E_INVALID, "a position list is shorter than its index class")
+        lists = [list(x)[:n] for x, n in zip(lists, (nm, nk, nk, nn, nm, nn))]
     arr = array("i")
     try:
         for x in lists:
             arr.extend(x)
-    except TypeError:
-        arr = array("i", [int(v) for x in lists for v in x])
-    nm, nn, nk = len(posA_m), len(posB_n), len(posA_k)
-    if len(posB_k) != nk or len(posC_m) != nm or len(posC_n) != nn:
-        raise MatncError(MATNC_E_INVALID, "position lists of one index class differ in length")
+    except (TypeError, OverflowError):  # floats, other arrays; numbers that the library refuses
+        arr = array("i", [c_int(int(v)).value for x in lists for v in x])
     p = arr.buffer_info()[0]
     m, n, k = 4 * nm, 4 * nn, 4 * nk
     return arr, nm, nn, nk, (p, p + m, p + m + k, p + m + 2 * k, p + m + 2 * k + n, p + 2 * m + 2 * k + n)
