@@ -261,7 +261,8 @@ int matnc_plan_destroy(matnc_plan plan);
  * bound stream) and keeping the fastest configuration; for fan-out steps the configuration's N width (32 or 64 complex
  * columns) also picks the fan table.  The launch graphs are re-captured at
  * the next execute.  Choices are keyed by shape class (precision, storage,
- * fan-out, m/n/k bits, instance count rounded to a power of two) and, if
+ * fan-out, m/n/k bits, instance count rounded to a power of two, and whether
+ * and in how many parts the step runs on the split tiles) and, if
  * cache_path is not NULL, read from and written back to that JSON file
  * (classes already in the file are not re-timed).  Overwrites intermediate
  * tensors (the stem cache is recomputed at the next execute).  Waits for the

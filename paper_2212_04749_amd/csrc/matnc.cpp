@@ -1428,10 +1428,14 @@ void launch_pass(Plan& P, int64_t b, int64_t e, double* amps, hipStream_t st) {
   }
 }
 
-// shape class of an MFMA step for the tuning cache
+// shape class of an MFMA step for the tuning cache.  The last number is log2 of
+// the instances, plus 100 (1 + log2 of the parts of its sum) for a step on the
+// split tiles: choices measured on the FP32 instruction, with the same m/n/k and
+// instances, are other ones (and files written before the split tiles say nothing about them).
 std::string tune_key(const Plan& P, const PNode& V, int64_t n_inst) {
   int lg = 0;
   while ((1LL << lg) < n_inst) ++lg;
+  if (P.split && !V.half_store) lg += 100 * (1 + V.ksplit);
   return std::string(P.precision == MATNC_C64 ? "c64" : "chalf") + (V.half_store ? "/h" : "/f") +
          (V.fan ? "/fan" : "") + "/" +
          std::to_string(V.M.size()) + "," + std::to_string(V.N.size()) + "," + std::to_string(V.K.size()) + "/" +
