@@ -470,6 +470,9 @@ __global__ __launch_bounds__(NT) void k_kfew(NodeDesc d, uint64_t ws, const int6
 // take every such k each; the groups' sums meet in a tree of lane exchanges.
 // No LDS, no barrier, and four instances per block: a block per instance
 // spent its time on its set-up and on adding 256 partial sums one by one.
+// Eight products at a time are summed on their own: a wave has fewer lanes than
+// a block, and one chain of 64 products per lane (3/3/9 bits x 1024) was 2.1e-7
+// from 64 bits, where a block's lanes with 16 each gave 1.5e-7; 1.0e-7 now.
 template <int FL, int NB>
 __global__ __launch_bounds__(256) void k_kdot(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   const int lane = threadIdx.x & 63;
@@ -494,11 +497,19 @@ __global__ __launch_bounds__(256) void k_kdot(NodeDesc d, uint64_t ws, const int
       float2 a[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) a[u] = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k + u * KS));
+      float2 part[NB];
+#pragma unroll
+      for (int n = 0; n < NB; ++n) part[n] = make_float2(0.f, 0.f);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k + u * KS);
 #pragma unroll
-        for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, obk + tbn[n]));
+        for (int n = 0; n < NB; ++n) cmac(part[n], a[u], ldop<FL, 2>(ip.pb, obk + tbn[n]));
+      }
+#pragma unroll
+      for (int n = 0; n < NB; ++n) {
+        acc[n].x += part[n].x;
+        acc[n].y += part[n].y;
       }
     }
     for (; k + grp < kcount; k += KS) {

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nm,nn,nk,batch", [(1, 0, 11, 223), (0, 0, 9, 500), (0, 0, 12, 300), (3, 3, 9, 100), (2, 1, 7, 511),
-                                            (0, 0, 9, 1500), (3, 1, 5, 1024), (5, 2, 8, 64), (9, 4, 5, 3), (6, 0, 12, 40)])
+                                            (0, 0, 9, 1500), (3, 1, 5, 1024), (5, 2, 8, 64), (9, 4, 5, 3), (6, 0, 12, 40),
+                                            (3, 3, 9, 1024), (3, 0, 11, 1100), (0, 0, 12, 1024), (2, 2, 8, 1030)])
 def test_no_further_off_than_lane_sums_one_by_one(nm, nn, nk, batch):
     torch = require_gpu()
     rng = np.random.default_rng(100 * nk + nm)
