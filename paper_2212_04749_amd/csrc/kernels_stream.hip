@@ -10,9 +10,9 @@
 //  * k_narrow<FL, KB>      the same for instances smaller than 256 elements:
 //    one lane per (instance, column group, m).
 //  * k_kred<FL, NB>        large K: lanes own m (coalesced reads of A along
-//    its low bits), groups of lanes split K, partial sums meet in LDS.
-//
-//  * k_kfew, k_kdot  large K and at most 8 values of m: see there.
+//    its low bits), groups of lanes split K, partial sums meet in LDS; B in LDS.
+//  * k_kdir<FL, NB>        the same with B read where it lies.
+//  * k_kdot<FL, NB>        large K, few outputs: one wave per instance.
 //
 // Bound: bytes, of small steps the launch.  Whole calls of a single contraction
 // (m/n/k bits x instances) with an offset table read per access, uploaded for
@@ -412,111 +412,192 @@ __global__ __launch_bounds__(256) void k_kred(NodeDesc d, uint64_t ws, const int
   }
 }
 
-// The same sums (groups and order) for at most 8 values of m: too few share B
-// for LDS, and a lane's loads are spaced so far apart that the 256-wide steps
-// of k_kred would leave one in flight; here it is eight.  NT lanes: 256, or 512
-// where there are fewer instances than CUs can hold blocks.
-template <int FL, int NB, int NT>
-__global__ __launch_bounds__(NT) void k_kfew(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
-  __shared__ float2 sb[NT * NB];
+// k of a lane in flight in k_kdir and k_kdot.  With more, the loads of a k's
+// columns take so many registers that fewer waves hide them: eight instead of
+// four or two cost 5-17%.
+constexpr int k_in_flight(int columns) { return columns <= 2 ? 4 : 2; }
+
+// How the offset of k changes where the bits from `shift` on are counted up by
+// one and t of them carry: lane t holds it.  (A deposit of every k, though of
+// scalars, took longer than its loads: 3/0/13 bits x 1 65 us instead of 25.)
+template <int CLS>
+__device__ __forceinline__ uint32_t k_carry(const NodeDesc& d, int shift) {
+  const int t = threadIdx.x & 63;
+  const uint32_t bits = t + shift < 31 ? ((2u << t) - 1u) << shift : 0u;
+  return dep<CLS>(d, d.kbits, bits);
+}
+
+// The same sums (groups and order) with B read where it lies: a block takes 2^mb
+// values of m of one instance, all of its NB columns.  Where the order is free, lanes of a
+// wave that share an output meet in a tree of lane exchanges, and only the
+// waves' sums go through LDS.
+template <int FL, int NB>
+__global__ __launch_bounds__(256) void k_kdir(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
+  constexpr int U = k_in_flight(NB), LU = U == 4 ? 2 : 1;
+  __shared__ float2 sb[256 * NB];
   const int tid = threadIdx.x;
-  const int M = 1 << d.mbits, KS = 1 << d.ks_bits;
-  const uint32_t m = tid & (M - 1), grp = tid >> d.mbits;  // grp >= KS: an idle lane
-  const uint32_t kcount = 1u << d.kbits;
-  const uint32_t oa = dep<TAB_AM>(d, 3, m) + dep<TAB_AK>(d, 12, grp & (KS - 1));
+  const int ksb = d.ks_bits, KS = 1 << ksb;
+  const int mb = d.mbits < 8 - ksb ? d.mbits : 8 - ksb;
+  const int M = 1 << mb;
+  const int mch = d.mbits - mb;  // m chunks per instance = 2^mch
+  const uint32_t mloc = tid & (M - 1), grp = tid >> mb;  // grp >= KS: an idle lane
+  const uint32_t kcount = 1u << d.kbits, runs = kcount >> (ksb + LU);
+  const uint32_t oa = dep<TAB_AM>(d, 8, mloc) + dep<TAB_AK>(d, 12, grp & (KS - 1));
   const uint32_t ob = dep<TAB_BK>(d, 12, grp & (KS - 1));
-  uint32_t tbn[NB];
+  uint32_t tbn[NB], ta[U], tb[U];
 #pragma unroll
   for (int n = 0; n < NB; ++n) tbn[n] = dep<TAB_BN>(d, 3, n);
-  const uint32_t oc = dep<TAB_CM>(d, 3, (uint32_t)tid / NB) + dep<TAB_CN>(d, 3, (uint32_t)tid % NB);
-  for (int64_t inst = blockIdx.x; inst < d.n_inst; inst += gridDim.x) {
-    const InstPtrs ip = instance_ptrs(d, ws, inst, sig);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    ta[u] = dep<TAB_AK>(d, d.kbits, (uint32_t)u << ksb);
+    tb[u] = dep<TAB_BK>(d, d.kbits, (uint32_t)u << ksb);
+  }
+  const uint32_t da = k_carry<TAB_AK>(d, ksb + LU), db = k_carry<TAB_BK>(d, ksb + LU);
+  const bool tree = d.keep_order == 0;
+  const int64_t nblk = d.n_inst << mch;
+  for (int64_t blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    const InstPtrs ip = instance_ptrs(d, ws, blk >> mch, sig);
+    const uint32_t m0 = ((uint32_t)blk & ((1u << mch) - 1u)) << mb;
+    const uint32_t om = oa + dep<TAB_AM>(d, d.mbits, m0);
+    float2 acc[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) acc[n] = make_float2(0.f, 0.f);
     if (grp < (uint32_t)KS) {
-      float2 acc[NB];
+      if (runs > 0) {
+        uint32_t ha = 0, hb = 0;
+        for (uint32_t r = 1;; ++r) {
+          float2 a[U];
 #pragma unroll
-      for (int n = 0; n < NB; ++n) acc[n] = make_float2(0.f, 0.f);
-      uint32_t k = 0;
-      for (; k + 8 * KS <= kcount; k += 8 * KS) {
-        float2 a[8];
+          for (int u = 0; u < U; ++u) a[u] = ldop<FL, 1>(ip.pa, om + (ha + ta[u]));
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k + u * KS));
+          for (int u = 0; u < U; ++u) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k + u * KS);
+            for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, ob + (hb + tb[u] + tbn[n])));
+          }
+          if (r == runs) break;
+          ha ^= __builtin_amdgcn_readlane(da, __builtin_ctz(r));
+          hb ^= __builtin_amdgcn_readlane(db, __builtin_ctz(r));
+        }
+      } else {  // fewer to a lane, also in flight together
+        float2 a[U / 2];
 #pragma unroll
-          for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, obk + tbn[n]));
+        for (int u = 0; u < U / 2; ++u)
+          if (((uint32_t)u << ksb) < kcount) a[u] = ldop<FL, 1>(ip.pa, om + ta[u]);
+#pragma unroll
+        for (int u = 0; u < U / 2; ++u)
+          if (((uint32_t)u << ksb) < kcount) {
+#pragma unroll
+            for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, ob + tb[u] + tbn[n]));
+          }
+      }
+    }
+    const OutScale s = out_scale<FL>(d, ws, ip.ai, ip.bi);
+    float mx = 0.f;
+    if (mb == 8) {
+      const uint32_t oc = dep<TAB_CM>(d, d.mbits, m0 + mloc);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) mx = fmaxf(mx, put<FL>(ip.pc, oc + dep<TAB_CN>(d, 3, n), acc[n], s));
+      block_record<FL>(d, ws, ip.inst, s, mx, m0 == 0);
+      continue;
+    }
+    int groups = KS;
+    if (tree && M < 64) {
+      for (int o = M; o < 64; o <<= 1) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          acc[n].x += __shfl_xor(acc[n].x, o);
+          acc[n].y += __shfl_xor(acc[n].y, o);
         }
       }
-      for (; k < kcount; k += KS) {
-        const float2 a = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k));
-        const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k);
+      groups = 4;
+      const int lane = tid & 63;
+      if (lane < M) {
 #pragma unroll
-        for (int n = 0; n < NB; ++n) cmac(acc[n], a, ldop<FL, 2>(ip.pb, obk + tbn[n]));
+        for (int n = 0; n < NB; ++n) sb[((tid >> 6) * M + lane) * NB + n] = acc[n];
       }
+    } else {
 #pragma unroll
       for (int n = 0; n < NB; ++n) sb[tid * NB + n] = acc[n];
     }
     __syncthreads();
-    const OutScale s = out_scale<FL>(d, ws, ip.ai, ip.bi);
-    float mx = 0.f;
-    if (tid < M * NB) mx = put<FL>(ip.pc, oc, add_groups(sb, tid, M * NB, KS, d.keep_order != 0), s);
-    if (tid < 64) block_record<FL>(d, ws, inst, s, mx, true);
+    for (int o = tid; o < M * NB; o += 256) {
+      const uint32_t oc = dep<TAB_CM>(d, d.mbits, m0 + (uint32_t)o / NB) + dep<TAB_CN>(d, 3, (uint32_t)o % NB);
+      mx = fmaxf(mx, put<FL>(ip.pc, oc, add_groups(sb, o, M * NB, groups, !tree), s));
+    }
+    block_record<FL>(d, ws, ip.inst, s, mx, m0 == 0);
     __syncthreads();  // the partial sums are rewritten next iteration
   }
 }
 
-// Large K, few outputs (at most 8 m and 8 columns per instance): one wave per
+// Large K, few outputs (at most 64 m and 8 columns per instance): one wave per
 // instance, whose lanes are 2^mbits values of m times 64 / 2^mbits groups that
 // take every such k each; the groups' sums meet in a tree of lane exchanges.
 // No LDS, no barrier, and four instances per block: a block per instance
 // spent its time on its set-up and on adding 256 partial sums one by one.
-// Eight products at a time are summed on their own: a wave has fewer lanes than
+// A few products at a time are summed on their own: a wave has fewer lanes than
 // a block, and one chain of 64 products per lane (3/3/9 bits x 1024) was 2.1e-7
-// from 64 bits, where a block's lanes with 16 each gave 1.5e-7; 1.0e-7 now.
+// from 64 bits, where a block's lanes with 16 each gave 1.5e-7.
 template <int FL, int NB>
 __global__ __launch_bounds__(256) void k_kdot(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
+  constexpr int U = k_in_flight(NB), LU = U == 4 ? 2 : 1;
   const int lane = threadIdx.x & 63;
   const int gb = 6 - d.mbits;
   const uint32_t m = lane & ((1 << d.mbits) - 1);
   const uint32_t grp = lane >> d.mbits;
   const uint32_t KS = 1u << gb, kcount = 1u << d.kbits;
-  const uint32_t oa = dep<TAB_AM>(d, 3, m) + dep<TAB_AK>(d, 6, grp);
+  const uint32_t oa = dep<TAB_AM>(d, 6, m) + dep<TAB_AK>(d, 6, grp);
   const uint32_t ob = dep<TAB_BK>(d, 6, grp);
-  uint32_t tbn[NB];
+  uint32_t tbn[NB], ta[U], tb[U];
 #pragma unroll
   for (int n = 0; n < NB; ++n) tbn[n] = dep<TAB_BN>(d, 3, n);
-  const uint32_t oc = dep<TAB_CM>(d, 3, m);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    ta[u] = dep<TAB_AK>(d, d.kbits, (uint32_t)u << gb);
+    tb[u] = dep<TAB_BK>(d, d.kbits, (uint32_t)u << gb);
+  }
+  const uint32_t oc = dep<TAB_CM>(d, 6, m);
+  const uint32_t da = k_carry<TAB_AK>(d, gb + LU), db = k_carry<TAB_BK>(d, gb + LU);
+  const uint32_t runs = kcount >> (gb + LU);
   const int64_t stride = (int64_t)gridDim.x * 4;
-  for (int64_t inst = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); inst < d.n_inst; inst += stride) {
+  for (int64_t inst = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); inst < d.n_inst;
+       inst += stride) {
     const InstPtrs ip = instance_ptrs(d, ws, inst, sig);
     float2 acc[NB];
 #pragma unroll
     for (int n = 0; n < NB; ++n) acc[n] = make_float2(0.f, 0.f);
-    uint32_t k = 0;
-    for (; k + 8 * KS <= kcount; k += 8 * KS) {
-      float2 a[8];
+    if (runs > 0) {
+      uint32_t ha = 0, hb = 0;
+      for (uint32_t r = 1;; ++r) {
+        float2 a[U], part[NB];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k + u * KS));
-      float2 part[NB];
+        for (int n = 0; n < NB; ++n) part[n] = make_float2(0.f, 0.f);
 #pragma unroll
-      for (int n = 0; n < NB; ++n) part[n] = make_float2(0.f, 0.f);
+        for (int u = 0; u < U; ++u) a[u] = ldop<FL, 1>(ip.pa, oa + (ha + ta[u]));
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k + u * KS);
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
-        for (int n = 0; n < NB; ++n) cmac(part[n], a[u], ldop<FL, 2>(ip.pb, obk + tbn[n]));
+          for (int n = 0; n < NB; ++n) cmac(part[n], a[u], ldop<FL, 2>(ip.pb, ob + (hb + tb[u] + tbn[n])));
+        }
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          acc[n].x += part[n].x;
+          acc[n].y += part[n].y;
+        }
+        if (r == runs) break;
+        ha ^= __builtin_amdgcn_readlane(da, __builtin_ctz(r));
+        hb ^= __builtin_amdgcn_readlane(db, __builtin_ctz(r));
       }
+    } else if (grp < kcount) {  // (of fewer than 64 / 2^mbits k some lanes have none)
+      float2 a[U / 2];
 #pragma unroll
-      for (int n = 0; n < NB; ++n) {
-        acc[n].x += part[n].x;
-        acc[n].y += part[n].y;
-      }
-    }
-    for (; k + grp < kcount; k += KS) {
-      const float2 a = ldop<FL, 1>(ip.pa, oa + dep<TAB_AK>(d, d.kbits, k));
-      const uint32_t obk = ob + dep<TAB_BK>(d, d.kbits, k);
+      for (int u = 0; u < U / 2; ++u)
+        if (((uint32_t)u << gb) < kcount) a[u] = ldop<FL, 1>(ip.pa, oa + ta[u]);
 #pragma unroll
-      for (int n = 0; n < NB; ++n) cmac(acc[n], a, ldop<FL, 2>(ip.pb, obk + tbn[n]));
+      for (int u = 0; u < U / 2; ++u)
+        if (((uint32_t)u << gb) < kcount) {
+#pragma unroll
+          for (int n = 0; n < NB; ++n) cmac(acc[n], a[u], ldop<FL, 2>(ip.pb, ob + (tb[u] + tbn[n])));
+        }
     }
     for (int o = 1 << d.mbits; o < 64; o <<= 1) {
 #pragma unroll
@@ -569,9 +650,26 @@ static hipError_t launch_small(const NodeDesc& d, uint64_t ws, const int64_t* si
   return hipGetLastError();
 }
 
+// One wave per instance (and 64 m) pays where a lane's share of the sum is short:
+// 3/0/10 bits x 1024, 128 k a lane, 36 us against 19 with a block per instance;
+// 2/1/7 x 5000, 8 k, 10 against 20.  Few instances leave a wave nothing to
+// overlap with, and the line moves by two bits.
+constexpr int kDotBits = 12;
+// B through LDS pays where a block has many values of m to share it and the sum
+// several fills of it: 6/3/10 bits x 1 44 us against 160, 5/3/8 x 64 12 and 27;
+// but 5/0/5 x 500 10.1 against 7.8, 3/0/13 x 1 65 against 25.  With many columns
+// and a block for every CU it does for shorter sums too (8/3/6 x 1024 30 and 70).
+inline bool stage_b(const NodeDesc& d) {
+  const int m = d.mbits, n = d.nbits;
+  const bool busy = d.n_ref >> 8 || (m > 8 && (d.n_ref << (m - 8)) >> 8);
+  const int least = m < 6 ? 8 - (busy && n >= 2 ? m + n - 6 : 0) : n < 2 ? 8 : busy ? 5 : 7;
+  return m >= 4 && m + n >= 6 && d.kbits >= least;
+}
+
 template <int FL>
 static hipError_t launch_kred(const NodeDesc& d0, uint64_t ws, const int64_t* sig, hipStream_t st) {
-  if (!d0.keep_order && d0.mbits <= 3 && d0.nbits <= 3 && d0.n_ref >= kDotInstances) {
+  if (!d0.keep_order && d0.mbits <= 6 && d0.nbits <= 3 &&
+      d0.kbits + d0.mbits + d0.nbits <= (d0.n_ref >= kDotInstances ? kDotBits : kDotBits - 2)) {
     const dim3 g((unsigned)std::min<int64_t>((d0.n_inst + 3) / 4, kBlocks)), b(256);
     switch (d0.nbits) {
       case 0: hipLaunchKernelGGL((k_kdot<FL, 1>), g, b, 0, st, d0, ws, sig); break;
@@ -598,23 +696,12 @@ static hipError_t launch_kred(const NodeDesc& d0, uint64_t ws, const int64_t* si
   const int m2 = d.mbits < 8 - d.ks_bits ? d.mbits : 8 - d.ks_bits;
   const int64_t blocks = d.n_inst << (d.mbits - m2 + d.nbits - nb);
   const dim3 g((unsigned)std::min<int64_t>(blocks, kBlocks)), b(256);
-  if (d.mbits <= 3 && d.nbits <= 3) {
-    if (!d.keep_order && d.n_ref < 512 && d.kbits > d.ks_bits && d.ks_bits + d.mbits == 8) {
-      ++d.ks_bits;
-      const dim3 b2(512);
-      switch (nb) {
-        case 0: hipLaunchKernelGGL((k_kfew<FL, 1, 512>), g, b2, 0, st, d, ws, sig); break;
-        case 1: hipLaunchKernelGGL((k_kfew<FL, 2, 512>), g, b2, 0, st, d, ws, sig); break;
-        case 2: hipLaunchKernelGGL((k_kfew<FL, 4, 512>), g, b2, 0, st, d, ws, sig); break;
-        default: hipLaunchKernelGGL((k_kfew<FL, 8, 512>), g, b2, 0, st, d, ws, sig); break;
-      }
-      return hipGetLastError();
-    }
+  if (d.nbits <= 3 && !stage_b(d)) {
     switch (nb) {
-      case 0: hipLaunchKernelGGL((k_kfew<FL, 1, 256>), g, b, 0, st, d, ws, sig); break;
-      case 1: hipLaunchKernelGGL((k_kfew<FL, 2, 256>), g, b, 0, st, d, ws, sig); break;
-      case 2: hipLaunchKernelGGL((k_kfew<FL, 4, 256>), g, b, 0, st, d, ws, sig); break;
-      default: hipLaunchKernelGGL((k_kfew<FL, 8, 256>), g, b, 0, st, d, ws, sig); break;
+      case 0: hipLaunchKernelGGL((k_kdir<FL, 1>), g, b, 0, st, d, ws, sig); break;
+      case 1: hipLaunchKernelGGL((k_kdir<FL, 2>), g, b, 0, st, d, ws, sig); break;
+      case 2: hipLaunchKernelGGL((k_kdir<FL, 4>), g, b, 0, st, d, ws, sig); break;
+      default: hipLaunchKernelGGL((k_kdir<FL, 8>), g, b, 0, st, d, ws, sig); break;
     }
     return hipGetLastError();
   }
