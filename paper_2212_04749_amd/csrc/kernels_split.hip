@@ -103,7 +103,11 @@ __device__ __forceinline__ Split3 split3(float2 v) {
 // LIN (every plan step): A[m + (k << mbits)], B[n + (k << nbits)] -- a thread
 // loads two neighbouring m at once and every k row's address is a scalar step
 // from the last; otherwise (a caller's own layout) an offset per element.
-template <int RM, int RN, int WM, int WN, bool FAN, bool LIN>
+// S: k steps in flight.  One, except for few tiles of the smallest size, whose
+// workgroups have a CU to themselves and wait for their loads (see kFewTiles);
+// elsewhere a second stage costs a workgroup per CU (20/8/9 bits on the 128 x 64
+// tile 6.4 ms with one, 6.9 ms with two).
+template <int RM, int RN, int WM, int WN, bool FAN, bool LIN, int S = 1>
 __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t ws, const int64_t* __restrict__ sig) {
   static_assert(LIN || !FAN, "fan-out tiles are a plan's");
   static_assert(RM * RN <= 4, "a lane's outputs have a bit each");
@@ -185,7 +189,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   if (tid < 33) s_redo[tid] = 0;
   if (tid < TN) s_cn[tid] = dep<TAB_CN>(d, 8, FAN ? (tid & nmask) : tid);
   const bool astage = QA >= NT || tid < QA;
-  const bool bstage = QB >= NT || tid < QB;
+  // (B by other threads than A's where there are enough: 6/5/10 bits x 1 101 -> 78 us)
+  const int btid = QA + QB <= NT ? (tid + NT - QA) % NT : tid;
+  const bool bstage = QB >= NT || btid < QB;
 
   // A block e of this thread covers m = amm[e] .. amm[e] + MA - 1, k = 4 akq[e]
   // .. 4 akq[e] + 3 of the tile; likewise B blocks over n
@@ -206,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
   }
 #pragma unroll
   for (int e = 0; e < EQB; ++e) {
-    const int flat = bstage ? e * NT + tid : 0;
+    const int flat = bstage ? e * NT + btid : 0;
     bnn[e] = flat % TN;
     bkq[e] = flat / TN;
     if constexpr (!LIN) {
@@ -292,11 +298,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
         for (int e = 0; e < EQA; ++e) pak[e] = pa + (uint64_t)(k0 + 4 * akq[e]) * a_k;
       }
       uint32_t kba = 0, kbb = 0;  // offsets of the k step being loaded (not LIN)
-      // (a second register stage, as the FP16 tiles have, costs a workgroup per CU:
-      // 20/8/9 bits on the 128 x 64 tile 6.4 ms with one, 6.9 ms with two)
-      f32x2 ra[EQA][4][MA];
-      f32x2 rb[EQB][4];
-      auto gload = [&](int ks) {
+      f32x2 ra[S][EQA][4][MA];
+      f32x2 rb[S][EQB][4];
+      // loads k step ks into stage st (where there are several, by every thread:
+      // a load under a condition makes the compiler wait for all of them)
+      auto gload = [&](int st, int ks) {
         if constexpr (!LIN) {
           if (ks > 0) {
             const int t = 3 + __builtin_ctz(ks);
@@ -304,28 +310,28 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
             kbb ^= __builtin_amdgcn_readfirstlane(s_kx[1][t]);
           }
         }
-        if (astage) {
+        if (S > 1 || astage) {
 #pragma unroll
           for (int e = 0; e < EQA; ++e)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               if constexpr (LIN && MA == 2)
-                load_f2x2(pak[e] + q * a_k, (uint32_t)amm[e], ra[e][q]);
+                load_f2x2(pak[e] + q * a_k, (uint32_t)amm[e], ra[st][e][q]);
               else if constexpr (LIN)
-                ra[e][q][0] = load_f2(pak[e] + q * a_k, (uint32_t)amm[e]);
+                ra[st][e][q][0] = load_f2(pak[e] + q * a_k, (uint32_t)amm[e]);
               else
-                ra[e][q][0] = load_f2(pa, aoff[e][q] + kba);
+                ra[st][e][q][0] = load_f2(pa, aoff[e][q] + kba);
             }
         }
-        if (bstage) {
+        if (S > 1 || bstage) {
 #pragma unroll
           for (int e = 0; e < EQB; ++e)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               if constexpr (LIN)
-                rb[e][q] = load_f2(pbe[e] + q * b_k, 0);
+                rb[st][e][q] = load_f2(pbe[e] + q * b_k, 0);
               else
-                rb[e][q] = load_f2(pbe[e], boff[e][q] + kbb);
+                rb[st][e][q] = load_f2(pbe[e], boff[e][q] + kbb);
             }
         }
         if constexpr (LIN) {
@@ -335,7 +341,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
           for (int e = 0; e < EQB; ++e) pbe[e] += TK * b_k;
         }
       };
-      auto lstore = [&](int buf) {
+      auto lstore = [&](int buf, int st) {
         if (astage) {
 #pragma unroll
           for (int e = 0; e < EQA; ++e) {
@@ -343,7 +349,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
             for (int i = 0; i < MA; ++i) {
               Split3 v[4];
 #pragma unroll
-              for (int q = 0; q < 4; ++q) v[q] = split3(scaled(ra[e][q][i], sc));
+              for (int q = 0; q < 4; ++q) v[q] = split3(scaled(ra[st][e][q][i], sc));
 #pragma unroll
               for (int p = 0; p < 3; ++p)
                 *reinterpret_cast<uint4*>(&As[buf][p][akq[e] * AQ + 4 * (amm[e] + i)]) =
@@ -356,7 +362,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
           for (int e = 0; e < EQB; ++e) {
             Split3 v[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = split3(scaled(rb[e][q], sc));
+            for (int q = 0; q < 4; ++q) v[q] = split3(scaled(rb[st][e][q], sc));
             const int base = ((bkq[e] * TN + bnn[e]) * 2) * 4;
 #pragma unroll
             for (int p = 0; p < 3; ++p) {
@@ -430,20 +436,35 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
         }
       };
 
-      gload(0);
-      lstore(0);
+      // stages 0 .. S-1 hold k steps 0 .. S-1
+      gload(0, 0);
+#pragma unroll
+      for (int u = 1; u < S; ++u)
+        if (u < ksteps) gload(u, u);
+      lstore(0, 0);
       __syncthreads();
-      // (the last step, which loads nothing, has a copy of its own: a load under a
-      // condition makes the compiler wait for more than it needs)
+      // Stage u held step k and was written to LDS at the end of step k - 1: it
+      // now takes step k + S.  (The last S steps, which load nothing, have a copy
+      // of their own.)
       int ks = 0;
-      for (; ks + 1 < ksteps; ++ks) {
-        gload(ks + 1);
-        kstep(ks & 1);
-        lstore((ks + 1) & 1);
-        __syncthreads();
+      for (; ks + S < ksteps; ks += S) {
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+          gload(u, ks + u + S);
+          kstep((ks + u) & 1);
+          lstore((ks + u + 1) & 1, (u + 1) % S);
+          __syncthreads();
+        }
       }
-      kstep(ks & 1);
-      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        const int k = ks + u;
+        if (k < ksteps) {
+          kstep(k & 1);
+          if (k + 1 < ksteps) lstore((k + 1) & 1, (u + 1) % S);
+          __syncthreads();
+        }
+      }
 
       // A sum with an infinite or NaN input, or one whose scaled value leaves
       // FP32's range (an operand above 2^104, a sum above 2^80), is not what
@@ -558,13 +579,23 @@ __global__ __launch_bounds__(256) void k_split_add(NodeDesc d, uint64_t ws) {
 // launchers (the tile configurations are those of kernels_c64.hip; the two of
 // 2^13 elements take eight waves, whose four tiles each leave room for both accumulators)
 
+// Tiles of the smallest size up to which four k steps are in flight, for sums of
+// at least 16: 6/6/10 bits x 40 (80 tiles) 85 -> 79 us, x 150 (300) 96 -> 84, but
+// 6/5/8 x 600 (600) 36 -> 39 and 6/5/6 x 150 (150) 10.3 -> 10.4.
+constexpr unsigned kFewTiles = 512;
+
 template <bool FAN, bool LIN>
 static hipError_t launch_split_s(const NodeDesc& d, int cfg, unsigned grid, uint64_t ws, const int64_t* sig,
                                 hipStream_t st) {
   switch (cfg) {
     case 0: hipLaunchKernelGGL((k_split<2, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
     case 1: hipLaunchKernelGGL((k_split<2, 2, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
-    case 2: hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
+    case 2:
+      if (grid <= kFewTiles && d.kbits - d.ksplit >= 7)
+        hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN, 4>), dim3(grid), dim3(256), 0, st, d, ws, sig);
+      else
+        hipLaunchKernelGGL((k_split<1, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig);
+      break;
     case 3: hipLaunchKernelGGL((k_split<4, 1, 2, 2, FAN, LIN>), dim3(grid), dim3(256), 0, st, d, ws, sig); break;
     case 4: hipLaunchKernelGGL((k_split<2, 2, 4, 2, FAN, LIN>), dim3(grid), dim3(512), 0, st, d, ws, sig); break;
     case 5:

@@ -99,3 +99,20 @@ def test_plan_layout_at_an_8_byte_address(kernel):
         out.append(c.cpu().numpy())
     assert np.isfinite(out[0]).all()
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("nm,nn,nk,batch", [(6, 5, 6, 3), (6, 5, 7, 3), (6, 6, 9, 2), (7, 6, 8, 1), (6, 5, 7, 600)])
+@pytest.mark.parametrize("layout", ["plan", "shuffled"])
+def test_few_tiles_with_several_k_steps_in_flight(nm, nn, nk, batch, layout):
+    """Below and from the least sum on, and with more tiles than that is for: the bits of the next larger tile (none
+    where m or n are too small for one), and the accuracy of FP32 sums."""
+    torch = require_gpu()
+    from test_gpu_contract import make_case, reference
+    rng = np.random.default_rng(17 * nk + batch)
+    pos, A, B = make_case(rng, nm, nn, nk, batch)
+    if layout == "plan":
+        pos = plan_layout(rng, nm, nn, nk)
+    got = run(torch, pos, A, B, nm, nn, nk, 102)
+    if nm > 6:
+        assert np.array_equal(got, run(torch, pos, A, B, nm, nn, nk, 100))
+    assert rel_err(got, reference(pos, A, B, nm, nn, nk)) < 1.05 * ROUNDING * np.sqrt(2.0 ** nk + 0.5)
