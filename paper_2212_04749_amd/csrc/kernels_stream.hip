@@ -50,8 +50,9 @@ namespace matnc {
 // tracked); bit 0 / 1 / 2 = A / B / C stored as FP16 (else FP32).
 constexpr int kMixBit = 8;
 
-// lanes that fill the chip: 256 CUs x 1024
-constexpr int64_t kNarrowLanes = 256 * 1024;
+// lanes that fill the chip, 256 CUs x 512; with twice as many a lane's A serves
+// fewer columns (7/3/3 bits x 500 11.4 -> 8.2 us)
+constexpr int64_t kNarrowLanes = 256 * 512;
 // blocks that keep HBM busy in a long sum
 constexpr int64_t kKredBlocks = 1024;
 // persistent blocks of the long-sum kernels: 8 per CU, so that the offsets in
@@ -270,12 +271,17 @@ __global__ __launch_bounds__(256) void k_narrow(NodeDesc d, uint64_t ws, const i
 #pragma unroll
       for (int k = 0; k < KB; ++k) a[k] = ldop<FL, 1>(ip.pa, oa + tak[k]);
       s = out_scale<FL>(d, ws, ip.ai, ip.bi);
-      for (int n = 0; n < NPL; ++n) {
-        const uint32_t bn = dep<TAB_BN>(d, d.nbits, n0 + n);
+      auto column = [&](uint32_t n) {
+        const uint32_t bn = dep<TAB_BN>(d, d.nbits, n);
         float2 c = make_float2(0.f, 0.f);
 #pragma unroll
         for (int k = 0; k < KB; ++k) cmac(c, a[k], ldop<FL, 2>(ip.pb, bn + tbk[k]));
-        mx = fmaxf(mx, put<FL>(ip.pc, oc + dep<TAB_CN>(d, d.nbits, n0 + n), c, s));
+        mx = fmaxf(mx, put<FL>(ip.pc, oc + dep<TAB_CN>(d, d.nbits, n), c, s));
+      };
+      if (nplbits == d.nbits) {  // (all columns: their offsets are scalars)
+        for (int n = 0; n < NPL; ++n) column(n);
+      } else {
+        for (int n = 0; n < NPL; ++n) column(n0 + n);
       }
     }
     if constexpr ((FL & kMixBit) != 0) {
@@ -622,24 +628,28 @@ __global__ __launch_bounds__(256) void k_kdot(NodeDesc d, uint64_t ws, const int
 // ---------------------------------------------------------------------------
 // dispatch
 
+// Columns share their block's B and A in k_wide; with fewer than a block for
+// every fourth CU, or 256 m whose few products do not pay for a barrier, lanes
+// with a row or an output each are faster: 10/5/3 bits x 1 (2 blocks) 12.4 -> 5.0
+// us, 12/6/0 x 1 (16) 11.6 -> 5.2, 8/0/0 x 5000 18.8 -> 15.7; from 64 blocks on it is
+// the other way round (18/2/2 x 1, 14/2/2 x 9, 12/2/2 x 64: by 5% and more).
+constexpr int64_t kWideBlocks = 64;
+
 template <int FL, int KB>
 static hipError_t launch_small(const NodeDesc& d, uint64_t ws, const int64_t* sig, hipStream_t st) {
-  if (d.mbits >= 8) {
-    // R m-chunks per lane: as many as the instance allows, up to 4 (2 when
-    // K is 16, to bound registers)
-    constexpr int RMAX = KB >= 16 ? 2 : 4;
-    const int extra = d.mbits - 8;
-    const int ng = d.nbits < 4 ? 0 : d.nbits - 4;  // column groups of 16
-    if (RMAX >= 4 && extra >= 2) {
-      const int64_t blocks = d.n_inst << (d.mbits - 10 + ng);
-      hipLaunchKernelGGL((k_wide<FL, KB, 4>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
-    } else if (extra >= 1) {
-      const int64_t blocks = d.n_inst << (d.mbits - 9 + ng);
-      hipLaunchKernelGGL((k_wide<FL, KB, 2>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
-    } else {
-      const int64_t blocks = d.n_inst << ng;
-      hipLaunchKernelGGL((k_wide<FL, KB, 1>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig);
-    }
+  // R m-chunks per lane: as many as the instance allows, up to 4 (2 when
+  // K is 16, to bound registers)
+  constexpr int RMAX = KB >= 16 ? 1 : 2;
+  const int lr = std::min(RMAX, d.mbits - 8);
+  const int ng = d.nbits < 4 ? 0 : d.nbits - 4;  // column groups of 16
+  const int64_t wide = d.mbits >= 8 ? d.n_inst << (d.mbits - 8 - lr + ng) : 0;
+  if (wide >= kWideBlocks && (d.mbits > 8 || d.kbits + 2 * d.nbits > 2)) {
+    if (lr == 2)
+      hipLaunchKernelGGL((k_wide<FL, KB, KB >= 16 ? 2 : 4>), dim3(grid_for(wide)), dim3(256), 0, st, d, ws, sig);
+    else if (lr == 1)
+      hipLaunchKernelGGL((k_wide<FL, KB, 2>), dim3(grid_for(wide)), dim3(256), 0, st, d, ws, sig);
+    else
+      hipLaunchKernelGGL((k_wide<FL, KB, 1>), dim3(grid_for(wide)), dim3(256), 0, st, d, ws, sig);
   } else {
     // as many columns per lane as still leave kNarrowLanes lanes
     int npl = d.nbits;
