@@ -17,15 +17,16 @@
 // sum, real, 2.5e-8 (at most 5.9e-8) in both; gate-like operands (zeros, +-i,
 // cosines) 3.8e-8 .. 4.1e-7 and 2.5e-8 .. 2.1e-7; positive ones 4.7e-8 .. 4.9e-7
 // and 2.8e-8 .. 2.5e-7.  (Six products in one accumulator, which this was
-// before, left out 2^-24 of a product and rounded at full size six times per eight k: 3.5e-8, at most
-// 1.4e-7, on single products, twice the instruction's error on sparse sums.)
+// before, left out 2^-24 of a product and rounded at full size six times per
+// eight k: 3.5e-8, at most 1.4e-7, on single products, twice the instruction's
+// error on sparse sums.)
 //
 // Bound: eight bfloat16 products take 256 matrix-core cycles per 32 x 16 x 8
 // complex block, the FP32 instruction 512.  At 20/8/9 bits of m/n/k the step
-// runs 7.07 ms (155 TFLOP/s complex, 1240 of bfloat16; a large bfloat16 library
+// runs 6.97 ms (158 TFLOP/s complex, 1262 of bfloat16; a large bfloat16 library
 // product reaches 1107 on this card under its power limit) against 8.60 ms for
 // the FP32 instruction's best tile and 9.04 for the one that it chose.  At
-// 22/6/6 bits 1.24 ms against 1.37.
+// 22/6/6 bits 1.25 ms against 1.37.
 //
 // Fan-out tiles whose groups do not fill them multiply empty columns: at
 // 10/3/11 bits (8 instances on average share an A) 0.70 of the 64-column
@@ -405,6 +406,11 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
               lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[g - ap], y[ap], lo, 0, 0, 0);
           a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], y[0], a, 0, 0, 0);
         };
+        // In fan-out tiles the compiler moves the splitting of the next step's first
+        // element, and with it the wait for its load, ahead of the products: 10/3/11
+        // bits x 16372 20.9 -> 23.1 ms, 22/1/6 x 128 5.55 -> 6.04.  So not before the
+        // last tiles' (elsewhere such a fence costs up to 2%).
+        auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
         if constexpr (RM <= RN) {
           bf16x8 yv[RM][3];
 #pragma unroll
@@ -416,6 +422,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
             bf16x8 xv[3];
 #pragma unroll
             for (int p = 0; p < 3; ++p) xv[p] = bfrag(p, q);
+            if (FAN && RN > 1 && q == RN - 1) fence();
 #pragma unroll
             for (int i = 0; i < RM; ++i) tile(acc[i][q], low[i][q], xv, yv[i]);
           }
@@ -430,6 +437,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
             bf16x8 yv[3];
 #pragma unroll
             for (int p = 0; p < 3; ++p) yv[p] = afrag(p, i);
+            if (FAN && i == RM - 1) fence();
 #pragma unroll
             for (int q = 0; q < RN; ++q) tile(acc[i][q], low[i][q], xv[q], yv);
           }
@@ -445,7 +453,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
       __syncthreads();
       // Stage u held step k and was written to LDS at the end of step k - 1: it
       // now takes step k + S.  (The last S steps, which load nothing, have a copy
-      // of their own.)
+      // of their own; a single one without conditions, which cost 12% on the
+      // 256 x 64 tile, 20/8/9 bits 6.97 -> 7.88 ms.)
       int ks = 0;
       for (; ks + S < ksteps; ks += S) {
 #pragma unroll
@@ -456,13 +465,18 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_split(NodeDesc d, uint64_t 
           __syncthreads();
         }
       }
+      if constexpr (S == 1) {
+        kstep(ks & 1);
+        __syncthreads();
+      } else {
 #pragma unroll
-      for (int u = 0; u < S; ++u) {
-        const int k = ks + u;
-        if (k < ksteps) {
-          kstep(k & 1);
-          if (k + 1 < ksteps) lstore((k + 1) & 1, (u + 1) % S);
-          __syncthreads();
+        for (int u = 0; u < S; ++u) {
+          const int k = ks + u;
+          if (k < ksteps) {
+            kstep(k & 1);
+            if (k + 1 < ksteps) lstore((k + 1) & 1, (u + 1) % S);
+            __syncthreads();
+          }
         }
       }
 
