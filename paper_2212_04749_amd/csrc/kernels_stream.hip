@@ -254,6 +254,12 @@ __global__ __launch_bounds__(256) void k_narrow(NodeDesc d, uint64_t ws, const i
   const int64_t total = d.n_inst << gb;
   const uint32_t mmask = (1u << d.mbits) - 1u, gmask = (1u << gb) - 1u;
   const int seg = gb >= 6 ? 64 : (1 << gb);
+  // A lane keeps its m: its turns are a multiple of 256 apart, and where an
+  // instance has more than 256 there is one turn only.  (With 16 k the two
+  // offsets that are kept cost 7%.)
+  constexpr bool kKept = KB < 16;
+  const uint32_t m0 = (blockIdx.x * 256 + threadIdx.x) & mmask;
+  const uint32_t oa0 = kKept ? dep<TAB_AM>(d, d.mbits, m0) : 0, oc0 = kKept ? dep<TAB_CM>(d, d.mbits, m0) : 0;
   for (int64_t base = (int64_t)blockIdx.x * 256; base < total; base += (int64_t)gridDim.x * 256) {
     const int64_t g = base + threadIdx.x;
     const bool live = g < total;
@@ -265,8 +271,8 @@ __global__ __launch_bounds__(256) void k_narrow(NodeDesc d, uint64_t ws, const i
       const uint32_t m = (uint32_t)g & mmask;
       const uint32_t n0 = (((uint32_t)g & gmask) >> d.mbits) << nplbits;
       const InstPtrs ip = instance_ptrs(d, ws, inst, sig);
-      const uint32_t oa = dep<TAB_AM>(d, d.mbits, m);
-      const uint32_t oc = dep<TAB_CM>(d, d.mbits, m);
+      const uint32_t oa = kKept ? oa0 : dep<TAB_AM>(d, d.mbits, m);
+      const uint32_t oc = kKept ? oc0 : dep<TAB_CM>(d, d.mbits, m);
       float2 a[KB];
 #pragma unroll
       for (int k = 0; k < KB; ++k) a[k] = ldop<FL, 1>(ip.pa, oa + tak[k]);
@@ -640,22 +646,29 @@ static hipError_t launch_small(const NodeDesc& d, uint64_t ws, const int64_t* si
   // R m-chunks per lane: as many as the instance allows, up to 4 (2 when
   // K is 16, to bound registers)
   constexpr int RMAX = KB >= 16 ? 1 : 2;
+  // Thousands of small instances with few columns: kBlocks blocks take several
+  // each, since a block's offsets cost as much as its outputs (8/0/0 bits x 5000
+  // 15.9 -> 9.6 us, 8/1/1 19.3 -> 16.7, 10/0/0 21.0 -> 18.3; with offset tables 12.9,
+  // 15.4, 18.6).  More work per block wants them all in flight (8/3/3 27.9 -> 31.4,
+  // 8/0/4 28.0 -> 30.2, 10/0/1 21.7 -> 23.3).
+  auto grid = [](int64_t blocks, bool turns) { return dim3(turns ? (unsigned)std::min(blocks, kBlocks) : grid_for(blocks)); };
+  const bool turns = KB < 16 && d.nbits <= 2, turns_r = d.mbits + d.kbits + d.nbits <= 10;
   const int lr = std::min(RMAX, d.mbits - 8);
   const int ng = d.nbits < 4 ? 0 : d.nbits - 4;  // column groups of 16
   const int64_t wide = d.mbits >= 8 ? d.n_inst << (d.mbits - 8 - lr + ng) : 0;
   if (wide >= kWideBlocks && (d.mbits > 8 || d.kbits + 2 * d.nbits > 2)) {
     if (lr == 2)
-      hipLaunchKernelGGL((k_wide<FL, KB, KB >= 16 ? 2 : 4>), dim3(grid_for(wide)), dim3(256), 0, st, d, ws, sig);
+      hipLaunchKernelGGL((k_wide<FL, KB, KB >= 16 ? 2 : 4>), grid(wide, turns_r), dim3(256), 0, st, d, ws, sig);
     else if (lr == 1)
-      hipLaunchKernelGGL((k_wide<FL, KB, 2>), dim3(grid_for(wide)), dim3(256), 0, st, d, ws, sig);
+      hipLaunchKernelGGL((k_wide<FL, KB, 2>), grid(wide, turns_r), dim3(256), 0, st, d, ws, sig);
     else
-      hipLaunchKernelGGL((k_wide<FL, KB, 1>), dim3(grid_for(wide)), dim3(256), 0, st, d, ws, sig);
+      hipLaunchKernelGGL((k_wide<FL, KB, 1>), grid(wide, turns), dim3(256), 0, st, d, ws, sig);
   } else {
     // as many columns per lane as still leave kNarrowLanes lanes
     int npl = d.nbits;
     while (npl > 0 && (d.n_inst << (d.mbits + d.nbits - npl)) < kNarrowLanes) --npl;
     const int64_t blocks = ((d.n_inst << (d.mbits + d.nbits - npl)) + 255) / 256;
-    hipLaunchKernelGGL((k_narrow<FL, KB>), dim3(grid_for(blocks)), dim3(256), 0, st, d, ws, sig, npl);
+    hipLaunchKernelGGL((k_narrow<FL, KB>), grid(blocks, turns), dim3(256), 0, st, d, ws, sig, npl);
   }
   return hipGetLastError();
 }
