@@ -200,12 +200,14 @@ int matnc_plan_set_tensor(matnc_plan plan, int t, const double *data_c128);
 /*
  * matnc_plan_bind -- attach the caller's device workspace (at least
  * workspace_bytes, 256-byte aligned) and HIP stream (hipStream_t, may be
- * NULL for the null stream), upload leaf variants, gather maps and offset
- * tables.  The workspace holds the static memory plan of the reuse tree
+ * NULL for the null stream), upload leaf variants, gather maps and the
+ * tables that the steps' kernels read.  The workspace holds the static memory plan of the reuse tree
  * (Supplementary Sec. III.C: with the reuse tree fixed before running, the
- * place and lifetime of every intermediate is known in advance).  The per-batch launch sequence of each chunk is captured as a HIP
- * graph on the first execute over a full batch (non-null stream only) and
- * replayed for every later full batch into the same amplitude buffer.
+ * place and lifetime of every intermediate is known in advance).  The
+ * per-batch launch sequence of each chunk is captured as a HIP graph on the
+ * first execute over a full batch (non-null stream only) and replayed for
+ * every later full batch into the same amplitude buffer; the slice-invariant
+ * steps are captured when they run for the second time after a binding.
  * The workspace must stay allocated until the plan is destroyed or re-bound.
  * Errors: MATNC_E_NOMEM, MATNC_E_HIP, MATNC_E_INVALID (misaligned).
  */
@@ -285,9 +287,11 @@ int matnc_plan_reset_cache(matnc_plan plan);
  * n_tensors - 1) it writes
  *   time_ms[j]  elapsed time of that launch (-1 if the node has no work;
  *               steps fused into one launch get equal shares of it),
- *   kernel[j]   0 = streaming kernel, 100 + c = FP32 MFMA tile
- *               configuration c, 200 + c = FP32 MFMA configuration c as
- *               fan-out tiles (the output instances that share an A
+ *   kernel[j]   0 = streaming kernel or part of a fused launch, 100 + c =
+ *               MFMA tile configuration c of a step stored in FP32 (on the
+ *               split bfloat16 tiles, or in complex-half plans that store
+ *               tensors in FP16 on the FP32 instruction), 200 + c = the same
+ *               as fan-out tiles (the output instances that share an A
  *               instance computed as one GEMM); 300 + c and 400 + c the
  *               same for the FP16 MFMA kernels of complex-half steps whose
  *               result is stored in FP16,
@@ -321,7 +325,7 @@ int matnc_queue_destroy(matnc_queue q);
 
 /*
  * matnc_queue_workspace_bytes -- device workspace matnc_queue_bind needs:
- * the static regions of all plans (leaf data, gather maps, offset tables,
+ * the static regions of all plans (leaf data, gather maps, kernels' tables,
  * scale slots) side by side, then ONE arena for the intermediates, as large
  * as the largest plan's -- the plans of a queue run one after another, so
  * their intermediates (stem caches included) never need to coexist.

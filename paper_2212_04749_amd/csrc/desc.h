@@ -4,10 +4,10 @@
 // element offset is a sum of independent bit contributions: the element at
 // coordinates (m, n, k) of the pairwise step C[m, n] = sum_k A[m, k] B[k, n]
 // sits at offset T_Am(m) + T_Ak(k) in A, T_Bk(k) + T_Bn(n) in B and
-// T_Cm(m) + T_Cn(n) in C.  Each T_* is stored as four 256-entry tables of
-// 8 coordinate bits each (uint32 element offsets; ranks <= 32), which is
-// how the index permutation of every operand is fused into its loads and
-// stores.
+// T_Cm(m) + T_Cn(n) in C, which is how the index permutation of every operand
+// is fused into its loads and stores.  Kernels form T_* from the storage bit of
+// each coordinate bit (NodeDesc::pos, uint32 element offsets; ranks <= 32);
+// k_mfma alone reads it from four 256-entry tables of 8 coordinate bits each.
 #pragma once
 #include <stdint.h>
 
@@ -45,7 +45,7 @@ struct NodeDesc {
   OpDesc A, B;
   uint64_t c_off;        // byte offset of output instance 0
   uint64_t c_inst_bytes; // bytes per output instance
-  uint64_t tab_off;      // byte offset of the TAB_COUNT x kTabSize uint32 tables
+  uint64_t tab_off;      // steps on k_mfma: byte offset of the TAB_COUNT x kTabSize uint32 tables (no others have any)
   uint64_t c_scale_off;  // complex-half: byte offset of the output's {e, max} pairs
   int64_t n_inst;        // instances in this launch = w * (dep ? batch : 1)
   int32_t w;             // reuse-tree width w(v)
@@ -75,10 +75,12 @@ struct NodeDesc {
   int32_t keep_order;    // 1: sums keep the order of additions fixed by the shape (plans with FP16 tensors)
   int32_t linear;        // 1: A[m + (k << mbits)] and B[n + (k << nbits)]
   int32_t ks_bits;       // long-sum kernel: 2^ks_bits lane groups share a sum
-  // split sums (matrix-core steps with few tiles and a long sum): the sum is
-  // cut into 2^ksplit parts, each a tile of its own writing to its own copy of
-  // the output at part_off (c layout, n_inst instances per part); a second
-  // kernel adds the copies in order
+  // split sums (matrix-core steps of a plan with few tiles and a long sum): the
+  // sum is cut into 2^ksplit parts, each a tile of its own writing to its own
+  // copy of the output at part_off (c layout, n_inst instances per part); a
+  // second kernel adds the copies in order.  The copies lie in the arena for as
+  // long as the step runs; where they have room for fewer slices than the batch
+  // has, the step runs in several launches (s0)
   int32_t ksplit;
   uint64_t part_off;
   // storage bit of coordinate bit t, per table class: offsets from these cost
